@@ -334,11 +334,11 @@ gp_status gp_count_async(const gp_graph* g, const gp_plan* p, const gp_launch* l
 /*
  * For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): gp_count_async
- * that allocates nothing. The task cursor, the per-group candidate buffers
+ * that allocates nothing. The task queue, the per-group candidate buffers
  * and, when room is left, the memo (leaf mode 4's per-root counts per group,
  * or an IEP plan's shared table of inner set sizes) come from one static device
- * workspace of 32 MiB that every GPU the library runs on holds until the
- * process ends; the grid shrinks so the buffers fit it. dev_out (device
+ * workspace (32 MiB, and 16 KiB for the queue) that every GPU the library runs
+ * on holds until the process ends; the grid shrinks so the buffers fit it. dev_out (device
  * memory, 2 uint64, caller-owned) receives {count, flags} as in
  * gp_count_async. GP_ERR_NOMEM when the plan's candidate buffers for one
  * block of groups alone exceed the workspace (a graph whose second-largest

@@ -41,14 +41,29 @@ BatchFn pick_batch_kernel(int kmin, int kmax, int group, int leaf, int iep) {
 }
 
 namespace {
-__global__ void init_counters(unsigned long long* p, int n) {
-    int i = threadIdx.x;
-    if (i < n) p[i] = 0;
+// A launch's counters cleared: n words at p, nr at r, nb at b (one block; r
+// and b may be null with nr, nb 0).
+__global__ void init_counters(unsigned long long* p, int n, unsigned long long* r, int nr, unsigned long long* b,
+                              int nb) {
+    for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0;
+    if ((int)threadIdx.x < nr) r[threadIdx.x] = 0;
+    if ((int)threadIdx.x < nb) b[threadIdx.x] = 0;
 }
 
-// A solo batch run's high count word into its plan's result words.
-__global__ void move_high_word(const unsigned long long* from, unsigned long long* to) {
-    if (threadIdx.x == 0) *to = *from;
+// Batch plan blockIdx.x's slots summed into its result words {count low word,
+// flags, busy clock ticks, count high word}.
+__global__ void collect_batch(const unsigned long long* queues, unsigned long long* result) {
+    const unsigned long long* q = queues + (int64_t)blockIdx.x * kQueueWords;
+    uint64_t lo, hi, busy = q[(int64_t)__lane_id() * kSlotWords + SLOT_BUSY];
+    slot_sum128(q, lo, hi);
+    busy = Group<64>().sum(busy);
+    if (threadIdx.x == 0) {
+        unsigned long long* r = result + 4 * (int64_t)blockIdx.x;
+        r[0] = lo;
+        r[1] = 0;
+        r[2] = busy;
+        r[3] = hi;
+    }
 }
 
 KernelFn pick_kernel(int k, int group, int leaf, int mode, int iep) {
@@ -104,30 +119,36 @@ bool memo_eligible(const GpPlanDesc& d) {
     return (ll.inj & ~(uint32_t)d.lv[d.k - 2].parents) == 0;
 }
 
-// The count's last step: the 128-bit total (queue[1], result[0]) divided by
-// the IEP over-count (1 for plain counts), with the overflow flag set only if
-// the quotient does not fit in 64 bits; check: flag a remainder (a whole
-// count must divide exactly).
+// The count's last step (one wavefront): the sum of the queue's 128-bit totals
+// divided by the IEP over-count (1 for plain counts), with the overflow flag
+// set only if the quotient does not fit in 64 bits; check: flag a remainder (a
+// whole count must divide exactly).
 __global__ void finish_count(unsigned long long* result, const unsigned long long* queue, unsigned long long div,
                              int check) {
+    uint64_t lo, hi;
+    slot_sum128(queue, lo, hi);
     if (threadIdx.x == 0) {
         const unsigned long long flags = result[1];
-        finish128(&result[0], &result[1], queue[1], div);
+        result[0] = lo;
+        finish128(&result[0], &result[1], hi, div);
         if (!check) result[1] = (result[1] & ~2ull) | (flags & 2ull);
     }
 }
 
 // The counting kernels' accumulation on given values: each lane adds its
 // share with add_count (carries counted), the wavefronts sum exactly in 128
-// bits and publish into w[2] (low word) and w[1] (high word), as a count's
-// wavefronts publish into result[0] and queue[1].
-__global__ void sum_check_kernel(const unsigned long long* vals, int64_t n, unsigned long long* w) {
+// bits and publish into the queue's slots, as a count's wavefronts do.
+__global__ void sum_check_kernel(const unsigned long long* vals, int64_t n, unsigned long long* queue) {
     uint64_t acc = 0, carry = 0;
     const int64_t step = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += step)
         add_count(acc, vals[i], carry);
     wave_sum128(acc, carry);
-    if (__lane_id() == 0) publish128(&w[2], &w[1], acc, carry);
+    if (__lane_id() == 0) {
+        const int wave = (int)((blockIdx.x * blockDim.x + threadIdx.x) / 64);
+        unsigned long long* slot = queue + (int64_t)(wave & (kSlots - 1)) * kSlotWords;
+        publish128(&slot[SLOT_LO], &slot[SLOT_HI], acc, carry);
+    }
 }
 }  // namespace
 }  // namespace gpcount
@@ -228,6 +249,7 @@ int64_t task_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCfg& c
 
 namespace {
 constexpr size_t kAlign = 256;
+constexpr size_t kQueueBytes = sizeof(unsigned long long) * kQueueWords;  // a multiple of kAlign
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 }  // namespace
 
@@ -266,7 +288,7 @@ gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCf
     const int64_t per_block = d.nbuf > 0 ? groups_per_block * d.nbuf * cap * 4 : 0;
     // keep scratch within a fixed budget (or the caller's workspace): fewer
     // resident groups if needed
-    const int64_t budget = ws ? (int64_t)ws->bytes - (int64_t)kAlign : int64_t(16) << 30;
+    const int64_t budget = ws ? (int64_t)ws->bytes - (int64_t)kQueueBytes : int64_t(16) << 30;
     if (ws && budget < 0) return GP_ERR_ARG;
     if (per_block > 0) {
         if (ws && per_block > budget) return GP_ERR_NOMEM;  // not even one block's buffers fit
@@ -296,10 +318,10 @@ gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCf
     if (ws) {
         char* base = (char*)ws->base;
         queue = (unsigned long long*)base;
-        if (scratch_bytes) scratch = (int32_t*)(base + kAlign);
-        if (use_memo) memo = (unsigned long long*)(base + kAlign + align_up(scratch_bytes));
+        if (scratch_bytes) scratch = (int32_t*)(base + kQueueBytes);
+        if (use_memo) memo = (unsigned long long*)(base + kQueueBytes + align_up(scratch_bytes));
     } else {
-        GP_HIP_TRY(hipMallocAsync((void**)&queue, sizeof(unsigned long long) * kQueueWords, stream));
+        GP_HIP_TRY(hipMallocAsync((void**)&queue, kQueueBytes, stream));
         if (scratch_bytes) {
             if (hipMallocAsync((void**)&scratch, scratch_bytes, stream) != hipSuccess) {
                 (void)hipFreeAsync(queue, stream);
@@ -317,9 +339,8 @@ gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCf
     if (use_memo)
         hipLaunchKernelGGL(zero_u64, dim3((unsigned)std::min<int64_t>(4096, (memo_words + 255) / 256)), dim3(256), 0,
                            stream, memo, memo_words);
-    hipLaunchKernelGGL(init_counters, dim3(1), dim3(64), 0, stream, queue, kQueueWords);
-    hipLaunchKernelGGL(init_counters, dim3(1), dim3(64), 0, stream, result_dev, account ? 3 : 2);
-    if (busy) hipLaunchKernelGGL(init_counters, dim3(1), dim3(64), 0, stream, busy, 3);
+    hipLaunchKernelGGL(init_counters, dim3(1), dim3(1024), 0, stream, queue, kQueueWords, result_dev, account ? 3 : 2,
+                       busy, busy ? 3 : 0);
 
     CountArgs a;
     a.row_ptr = g.row_ptr;
@@ -327,6 +348,7 @@ gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCf
     a.roots = roots;
     a.n_roots = n_roots;
     a.n_tasks = n_tasks;
+    a.n_chunks = (n_tasks + cfg.chunk - 1) / cfg.chunk;
     a.split_roots = split_roots;
     a.split_ways = split_ways;
     a.budget_ticks = busy && cfg.budget_ms > 0 ? (uint64_t)(cfg.budget_ms * g.wall_khz) : 0;
@@ -365,23 +387,25 @@ gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCf
 gp_status check_sum(const uint64_t* values, int64_t n, uint64_t div, hipStream_t stream, uint64_t* out,
                     uint32_t* flags) {
     if (n < 0 || (n > 0 && !values) || div < 1) return GP_ERR_ARG;
-    unsigned long long* w = nullptr;  // {cursor (unused), high word, low word, flags}, then the values
-    GP_HIP_TRY(hipMallocAsync((void**)&w, sizeof(unsigned long long) * (4 + (size_t)n), stream));
-    unsigned long long h[4] = {0, 0, 0, 0};
+    unsigned long long* w = nullptr;  // the queue's slots, {low word, flags}, then the values
+    GP_HIP_TRY(hipMallocAsync((void**)&w, kQueueBytes + sizeof(unsigned long long) * (2 + (size_t)n), stream));
+    unsigned long long* res = w + kQueueWords;
+    unsigned long long h[2] = {0, 0};
     hipError_t e = hipSuccess;
-    hipLaunchKernelGGL(init_counters, dim3(1), dim3(64), 0, stream, w, 4);
+    hipLaunchKernelGGL(init_counters, dim3(1), dim3(1024), 0, stream, w, kQueueWords, res, 2,
+                       (unsigned long long*)nullptr, 0);
     if (n > 0)
-        e = hipMemcpyAsync(w + 4, values, sizeof(unsigned long long) * (size_t)n, hipMemcpyHostToDevice, stream);
+        e = hipMemcpyAsync(res + 2, values, sizeof(unsigned long long) * (size_t)n, hipMemcpyHostToDevice, stream);
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(sum_check_kernel, dim3(4), dim3(kBlock), 0, stream, w + 4, n, w);
-        hipLaunchKernelGGL(finish_count, dim3(1), dim3(64), 0, stream, w + 2, w, (unsigned long long)div, 1);
+        hipLaunchKernelGGL(sum_check_kernel, dim3(4), dim3(kBlock), 0, stream, res + 2, n, w);
+        hipLaunchKernelGGL(finish_count, dim3(1), dim3(64), 0, stream, res, w, (unsigned long long)div, 1);
         e = hipGetLastError();
     }
-    if (e == hipSuccess) e = hipMemcpyAsync(h, w, sizeof h, hipMemcpyDeviceToHost, stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(h, res, sizeof h, hipMemcpyDeviceToHost, stream);
     (void)hipFreeAsync(w, stream);
     if (hipStreamSynchronize(stream) != hipSuccess || e != hipSuccess) return GP_ERR_HIP;
-    *out = h[2];
-    *flags = (uint32_t)h[3];
+    *out = h[0];
+    *flags = (uint32_t)h[1];
     return GP_OK;
 }
 
@@ -389,7 +413,7 @@ gp_status check_sum(const uint64_t* values, int64_t n, uint64_t div, hipStream_t
 // copy of this array until the process ends. In host code its name is only a
 // stand-in; the device address of each GPU's copy comes from
 // hipGetSymbolAddress, taken once per device.
-static __device__ __align__(256) unsigned char scratch[kNoallocWorkspaceBytes];
+static __device__ __align__(256) unsigned char scratch[kNoallocWorkspaceBytes + kNoallocQueueBytes];
 
 namespace {
 std::mutex g_scratch_mu;
@@ -417,7 +441,8 @@ gp_status launch_count_noalloc(const DeviceGraph& g, const GpPlanDesc& d, const 
     if (st != GP_OK) return st;
     Workspace ws;
     ws.base = base;
-    ws.bytes = kNoallocWorkspaceBytes;
+    static_assert(kQueueBytes <= kNoallocQueueBytes, "room for the queue");
+    ws.bytes = kNoallocWorkspaceBytes + kQueueBytes;
     return launch_count(g, d, cfg, stream, result_dev, nullptr, false, nullptr, &ws);
 }
 
@@ -432,7 +457,6 @@ void batch_release(BatchState* st) {
     (void)hipFree(st->memo);
     (void)hipFree(st->queues);
     (void)hipFree(st->result);
-    (void)hipFree(st->run_queues);
     *st = BatchState{};
 }
 
@@ -497,6 +521,8 @@ static gp_status batch_layout(const DeviceGraph& g, const GpPlanDesc* descs, con
         bp.split_roots = sp.roots;
         bp.split_ways = sp.ways;
         batch_shape(descs[i], cfgs[i], min_group_floor, &bp);
+        const int64_t grab = (int64_t)(64 / bp.group) * bp.chunk;
+        bp.n_chunks = (cnt + grab - 1) / grab;
         // consecutive plans of one shape share a launch (up to kRunMaxPlans:
         // their descriptors are its kernel arguments)
         const int iep_depth = descs[i].iep;
@@ -593,8 +619,7 @@ gp_status batch_prepare(const DeviceGraph& g, const GpPlanDesc* descs, const Lau
                 const int l = iep_memo_log2(g.n_hubs, kIepMemoBytes / 8);
                 if (l >= 0) b.memo_words = std::max(b.memo_words, (int64_t)g.n_hubs << l);
             }
-    if (hipMalloc((void**)&b.queues, sizeof(unsigned long long) * np) != hipSuccess ||
-        hipMalloc((void**)&b.run_queues, sizeof(unsigned long long) * kBatchMaxPlans * kQueueWords) != hipSuccess ||
+    if (hipMalloc((void**)&b.queues, kQueueBytes * np) != hipSuccess ||
         hipMalloc((void**)&b.result, 4 * sizeof(unsigned long long) * np) != hipSuccess ||
         (b.nbuf > 0 && hipMalloc((void**)&b.scratch, (size_t)(slots * b.nbuf * b.cap * 4)) != hipSuccess) ||
         (b.memo_words > 0 && hipMalloc((void**)&b.memo, (size_t)b.memo_words * 8) != hipSuccess))
@@ -633,11 +658,8 @@ gp_status batch_enqueue(const DeviceGraph& g, const BatchState& st, hipStream_t 
     if (st.runs.empty()) return GP_ERR_ARG;
     for (const BatchRun& r : st.runs)
         if (!pick_batch_kernel(r.kmin, r.kmax, r.group, r.leaf, r.iep) || r.blocks < 1) return GP_ERR_UNSUPPORTED;
-    for (int i = 0; i < st.np; i += 64)
-        hipLaunchKernelGGL(init_counters, dim3(1), dim3(64), 0, stream, st.queues + i, std::min(64, st.np - i));
-    for (int i = 0; i < 4 * st.np; i += 64)
-        hipLaunchKernelGGL(init_counters, dim3(1), dim3(64), 0, stream, st.result + i,
-                           std::min(64, 4 * st.np - i));
+    hipLaunchKernelGGL(zero_u64, dim3((unsigned)(st.np * (kQueueWords / 256))), dim3(256), 0, stream, st.queues,
+                       (int64_t)st.np * kQueueWords);
     if (st.memo_words > 0)
         hipLaunchKernelGGL(zero_u64, dim3((unsigned)std::min<int64_t>(4096, (st.memo_words + 255) / 256)), dim3(256),
                            0, stream, st.memo, st.memo_words);
@@ -647,21 +669,18 @@ gp_status batch_enqueue(const DeviceGraph& g, const BatchState& st, hipStream_t 
     for (size_t ri = 0; ri < st.runs.size(); ++ri) {
         const BatchRun& r = st.runs[ri];
         if (r.solo) {
-            // the plain counting kernel over the plan's whole task space; its
-            // queue words are the run's own, and the high count word is moved
-            // into the plan's result words after it
+            // the plain counting kernel over the plan's whole task space
             const int p = r.p0;
             const GpPlanDesc& d = st.h_descs[p];
             KernelFn fn = pick_kernel(d.k, r.group, r.leaf, MODE_PLAIN, d.iep);
             if (!fn) return GP_ERR_UNSUPPORTED;
-            unsigned long long* q = st.run_queues + ri * kQueueWords;
-            hipLaunchKernelGGL(init_counters, dim3(1), dim3(64), 0, stream, q, kQueueWords);
             CountArgs a;
             a.row_ptr = g.row_ptr;
             a.col = g.col;
             a.roots = r.roots;
             a.n_roots = r.n_roots;
             a.n_tasks = r.n_tasks;
+            a.n_chunks = (r.n_tasks + r.chunk - 1) / r.chunk;
             a.split_roots = r.split_roots;
             a.split_ways = r.split_ways;
             a.budget_ticks = 0;
@@ -672,7 +691,7 @@ gp_status batch_enqueue(const DeviceGraph& g, const BatchState& st, hipStream_t 
             a.root_stride = r.root_stride;
             a.scratch = st.scratch;
             a.buf_cap = st.cap;
-            a.queue = q;
+            a.queue = st.queues + (int64_t)p * kQueueWords;
             a.result = st.result + 4 * p;
             a.per_root = nullptr;
             a.busy = nullptr;
@@ -687,7 +706,6 @@ gp_status batch_enqueue(const DeviceGraph& g, const BatchState& st, hipStream_t 
             a.xcd_block = 0;
             if (r.n_tasks > 0)
                 hipLaunchKernelGGL(fn, dim3((unsigned)r.blocks), dim3(kBlock), 0, stream, d, a);
-            hipLaunchKernelGGL(move_high_word, dim3(1), dim3(64), 0, stream, q + 1, st.result + 4 * p + 3);
             continue;
         }
         BatchArgs a;
@@ -702,8 +720,7 @@ gp_status batch_enqueue(const DeviceGraph& g, const BatchState& st, hipStream_t 
         a.nbuf = st.nbuf;
         a.slots_per_wave = 64 / r.group;
         a.memo = st.memo_words > 0 ? st.memo : nullptr;
-        a.queues = st.queues + r.p0;
-        a.result = st.result + 4 * r.p0;
+        a.queues = st.queues + (int64_t)r.p0 * kQueueWords;
         RunDescs rd;
         std::memset(&rd, 0, sizeof rd);
         for (int p = r.p0; p < r.p1; ++p) {
@@ -713,6 +730,7 @@ gp_status batch_enqueue(const DeviceGraph& g, const BatchState& st, hipStream_t 
         hipLaunchKernelGGL(pick_batch_kernel(r.kmin, r.kmax, r.group, r.leaf, r.iep), dim3((unsigned)r.blocks), dim3(kBlock),
                            0, stream, a, rd);
     }
+    hipLaunchKernelGGL(collect_batch, dim3((unsigned)st.np), dim3(64), 0, stream, st.queues, st.result);
     return hipGetLastError() == hipSuccess ? GP_OK : GP_ERR_HIP;
 }
 
@@ -727,9 +745,7 @@ gp_status arena_create(const DeviceGraph& g, int nbuf_cap, int waves_per_cu, int
     a.blocks_cap = batch_blocks(g, waves_per_cu, 64 / a.min_group, a.nbuf_cap, b.cap, true);
     a.slots_cap = a.blocks_cap * (kBlock / 64) * (64 / a.min_group);
     a.memo_words_cap = g.n_hubs > 0 ? a.slots_cap * (int64_t)g.n_hubs : 0;
-    bool ok = hipMalloc((void**)&b.queues, sizeof(unsigned long long) * kBatchMaxPlans) == hipSuccess &&
-              hipMalloc((void**)&b.run_queues, sizeof(unsigned long long) * kBatchMaxPlans * kQueueWords) ==
-                  hipSuccess &&
+    bool ok = hipMalloc((void**)&b.queues, kQueueBytes * kBatchMaxPlans) == hipSuccess &&
               hipMalloc((void**)&b.result, 4 * sizeof(unsigned long long) * kBatchMaxPlans) == hipSuccess &&
               (a.nbuf_cap == 0 ||
                hipMalloc((void**)&b.scratch, (size_t)(a.slots_cap * a.nbuf_cap * b.cap * 4)) == hipSuccess) &&

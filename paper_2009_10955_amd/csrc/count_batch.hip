@@ -6,10 +6,10 @@
 // 32, 16 or 8), leaf mode (1, 3 or 4) and inclusion-exclusion depth, plus its
 // tasks per grab. The plans of one shape and one pattern size (k <= 6; sizes
 // 7 and 8 share) run in ONE persistent launch of a kernel compiled for that
-// shape and size only, with a task cursor per plan:
+// shape and size only, with a queue of task cursors per plan:
 // wavefronts take the plans in order, grab a piece of the current plan's
 // tasks (64/G groups, bp.chunk tasks each), and move to the next plan once
-// its cursor is exhausted, so plans of uneven cost fill each other's tails
+// its cursors are exhausted, so plans of uneven cost fill each other's tails
 // (Section IV-E's task partitioning, across patterns). One kernel per shape,
 // not one kernel for all shapes: a body that branches over several shapes
 // keeps the register allocation of their union, and the spills that follow
@@ -108,19 +108,24 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(occupanc
     int32_t* lens_base = &s_len[wave * (64 / G)][0];
     constexpr int64_t kGroups = 64 / G;
 
+    const Group<64> wg;
+    __shared__ int s_cur[kBlock / 64];
+    s_cur[wave] = (int)(wave_global & (kCursors - 1));
+    group_fence();
     int p = 0;
     while (p < a.np) {
         const BatchPlan& bp = rd.bp[p];
         const int64_t W = kGroups * bp.chunk;
-        unsigned long long q = 0;
-        if (lane == 0) q = atomicAdd(&a.queues[p], (unsigned long long)W);
-        const int64_t t0 = uni64<64>((int64_t)__shfl(q, 0, 64));
-        const int64_t n_tasks = bp.n_tasks;
-        if (t0 >= n_tasks) {
+        unsigned long long* queue = a.queues + (int64_t)p * kQueueWords;
+        // a plan that is all handed out costs one load
+        const bool done = __hip_atomic_load(&queue[kDoneWord], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+        const int64_t q = uni<64>(done) ? -1 : next_chunk<64>(wg, queue, bp.n_chunks, &s_cur[wave]);
+        if (q < 0) {
             ++p;
             continue;
         }
-        const int64_t t1 = min(t0 + W, n_tasks);
+        const int64_t t0 = q * W;
+        const int64_t t1 = min(t0 + W, bp.n_tasks);
         const GpPlanDesc& d = rd.d[p];
         const uint64_t clk0 = wall_clock64();
         uint64_t acc = 0, carry = 0;
@@ -139,8 +144,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(occupanc
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
     for (int i = lane; i < a.np; i += 64) {
-        publish128(&a.result[4 * i], &a.result[4 * i + 3], s_lo[wave][i], s_hi[wave][i]);
-        if (s_busy[wave][i]) atomicAdd(&a.result[4 * i + 2], s_busy[wave][i]);
+        unsigned long long* slot = a.queues + (int64_t)i * kQueueWords + (wave_global & (kSlots - 1)) * kSlotWords;
+        publish128(&slot[SLOT_LO], &slot[SLOT_HI], s_lo[wave][i], s_hi[wave][i]);
+        if (s_busy[wave][i]) atomicAdd(&slot[SLOT_BUSY], s_busy[wave][i]);
     }
 }
 

@@ -10,12 +10,12 @@
 // inclusion-exclusion (Section IV-D, Algorithm 2).
 //
 // How it maps to the machine:
-//   * Tasks are root edges (v0, v1) = the first two loops fused, taken from a
-//     device-wide atomic queue in chunks (the fine-grained task partitioning
-//     of Section IV-E, as a lock-free queue instead of a master thread). Root
-//     arrays are ordered by their smaller (higher-degree) endpoint, so hubs
-//     go first, and the heaviest roots can be split over their level-2
-//     candidates into several tasks.
+//   * Tasks are root edges (v0, v1) = the first two loops fused, taken in
+//     chunks from a device-wide queue of kCursors cursors (the fine-grained task
+//     partitioning of Section IV-E, as a lock-free queue instead of a master
+//     thread). Root arrays are ordered by their smaller (higher-degree)
+//     endpoint, so hubs go first, and the heaviest roots can be split over
+//     their level-2 candidates into several tasks.
 //   * A group of G lanes (G in {64, 32, 16, 8}) of one wavefront shares one
 //     search path. Intersections are group-cooperative (each lane
 //     binary-searches one element of the smaller list in the larger one;
@@ -36,9 +36,9 @@
 //   * The last level is never enumerated: its count is
 //     |C ∩ [lo, hi)| minus the earlier bound vertices that fall in it.
 //   * Counts: a 64-bit total and a carry count per lane, an exact 128-bit
-//     wavefront sum, one pair of atomics per wavefront into a 128-bit device
-//     total; a last step divides it by the IEP over-count and flags a
-//     quotient that does not fit in 64 bits.
+//     wavefront sum, one pair of atomics per wavefront into one of kSlots
+//     128-bit device totals; a last step adds these, divides the sum by the
+//     IEP over-count and flags a quotient that does not fit in 64 bits.
 //   * Byte accounting (MODE_ACCOUNT) is the same search, leaf mode and memo
 //     with a per-lane byte counter added where memory is touched: it measures
 //     the bytes of the path the timed launch takes.
@@ -63,6 +63,29 @@ enum { MODE_PLAIN = 0, MODE_PER_ROOT = 1, MODE_ACCOUNT = 2 };
 // Inclusion-exclusion over at most this many innermost levels.
 constexpr int kIepMaxN = GP_IEP_MAX_INNER;
 
+// A launch's queue: kSlots slots of kSlotWords words (256 bytes, so that slots
+// lie in different memory channels). Every slot holds a partial 128-bit total
+// and, in batches, busy clock ticks; every kCursorStep-th also a task cursor.
+// Chunk q of the task space belongs to cursor q mod kCursors, so all cursors
+// together still walk the tasks in order, heaviest first.
+//
+// Why many: atomics with a return value on one address complete one after
+// another at the memory side, 12 ns each, whoever issues them. One cursor
+// bounded every launch of small tasks (R-MAT 18 4-clique per root, 488K grabs:
+// 6.0 ms, 5.9 of them the cursor), and 8,192 wavefronts ending against it, and
+// adding their totals to one word, cost 0.1 ms each even on the smallest
+// graph. Why not more cursors: a group that finds its own dry reads all of
+// them, and thousands of groups do so as a launch ends (a batch of small
+// launches: 47 ms with one cursor per plan, 63 with 64).
+constexpr int kSlots = 64;
+constexpr int kSlotWords = 32;
+constexpr int kQueueWords = kSlots * kSlotWords;
+constexpr int kCursors = 16;
+constexpr int kCursorStep = kSlots / kCursors;
+enum { SLOT_CURSOR = 0, SLOT_LO = 1, SLOT_HI = 2, SLOT_BUSY = 3 };
+// set once every cursor is exhausted (a word of a slot without a cursor)
+constexpr int kDoneWord = 2 * kSlotWords + 4;
+
 struct CountArgs {
     const int64_t* row_ptr;
     const int32_t* col;
@@ -75,6 +98,7 @@ struct CountArgs {
     // j-th of which binds only every split_ways-th level-2 candidate from j on.
     // Tasks: split_roots * split_ways split ones, then one per remaining root.
     int64_t n_tasks;
+    int64_t n_chunks;  // ceil(n_tasks / chunk)
     int64_t split_roots;
     int32_t split_ways;
     const uint32_t* hub_bits;  // n_hubs dense bitmaps of hub_words words
@@ -82,10 +106,8 @@ struct CountArgs {
     int32_t n_hubs;
     int32_t* scratch;
     int64_t buf_cap;
-    // {task cursor, high word of the 128-bit total, then with xcd_block > 0
-    // one task cursor per XCD}
-    unsigned long long* queue;
-    unsigned long long* result;    // {count (low word), flags, bytes}
+    unsigned long long* queue;     // kQueueWords words; with xcd_block > 0 cursor x is XCD x's
+    unsigned long long* result;    // {count (low word, set by finish_count), flags, bytes}
     unsigned long long* per_root;  // optional, indexed by CSR entry of (v0, v1)
     // optional {sum over wavefronts of active clock ticks, wavefronts, longest
     // chunk of tasks in ticks}: the balanced run time of a sample and its tail
@@ -118,6 +140,7 @@ struct BatchPlan {
     int64_t root_offset;  // sampled roots: roots[root_offset + r * root_stride]
     int64_t root_stride;
     int64_t n_tasks;      // tasks of this plan in the launch
+    int64_t n_chunks;     // wavefront grabs: ceil(n_tasks / (64 / group * chunk))
     int64_t task_offset;  // where in the plan's own task space the launch starts
     int64_t split_roots;  // as in CountArgs: the first split_roots roots run as
     int32_t split_ways;   // split_ways tasks each
@@ -151,8 +174,7 @@ struct BatchArgs {
     int32_t nbuf;            // buffer slots per group (max over plans)
     int32_t slots_per_wave;  // 64 / (the smallest group of any plan)
     unsigned long long* memo;     // per wavefront: slots_per_wave x n_hubs words (or null)
-    unsigned long long* queues;   // np task cursors
-    unsigned long long* result;   // per plan {count low word, flags, busy clock ticks, high word}
+    unsigned long long* queues;   // per plan: kSlots slots
 };
 
 typedef void (*BatchFn)(BatchArgs, RunDescs);
@@ -306,8 +328,8 @@ __device__ __forceinline__ void wave_sum128(uint64_t& lo, uint64_t& hi) {
     }
 }
 
-// Add a 128-bit value to a device-wide total held as two words: the low word
-// at *lo_word, the high word at *hi_word. Called by one lane.
+// Add a 128-bit value to a total in device memory held as two words: the low
+// word at *lo_word, the high word at *hi_word. Called by one lane.
 __device__ __forceinline__ void publish128(unsigned long long* lo_word, unsigned long long* hi_word, uint64_t lo,
                                            uint64_t hi) {
     if (lo) {
@@ -315,6 +337,15 @@ __device__ __forceinline__ void publish128(unsigned long long* lo_word, unsigned
         hi += (old + lo < old) ? 1u : 0u;
     }
     if (hi) atomicAdd(hi_word, (unsigned long long)hi);
+}
+
+// Sum of a queue's kSlots 128-bit totals; every lane of the wavefront gets it.
+__device__ __forceinline__ void slot_sum128(const unsigned long long* queue, uint64_t& lo, uint64_t& hi) {
+    static_assert(kSlots == 64, "one slot per lane");
+    const unsigned long long* s = queue + (int64_t)__lane_id() * kSlotWords;
+    lo = s[SLOT_LO];
+    hi = s[SLOT_HI];
+    wave_sum128(lo, hi);
 }
 
 // The end of every count: the 128-bit total (hi, *lo_word) divided by div
@@ -1223,8 +1254,6 @@ __device__ __forceinline__ void run_tasks(const GpPlanDesc& d, Ctx<G>& c, const 
 // XCDs of the device; workgroups are dealt to them round robin in launch
 // order, so block b of a grid runs on XCD b mod kXcds.
 constexpr int kXcds = 8;
-// Words of a launch's queue: cursor, high count word, one cursor per XCD.
-constexpr int kQueueWords = 2 + kXcds;
 
 // Tasks of XCD x when n tasks are dealt in blocks of B tasks, block b to
 // XCD b mod kXcds.
@@ -1240,35 +1269,81 @@ __device__ __forceinline__ int64_t xcd_task(int64_t j, int64_t B, int x) {
     return (b * kXcds + x) * B + (j - b * B);
 }
 
-// Next grab of a group: `chunk` tasks [*t0, *t1) from one cursor, or false
-// once every cursor is exhausted. With XCD blocks the group starts at its
-// own XCD's cursor (*q = 0) and moves on to the next XCD's when it runs dry;
-// it never comes back to one that was dry.
+// Next chunk of a group from the queue's cursors, or -1 once all are
+// exhausted. *cur (in LDS: kept in a register through the search it cost
+// spills): the cursor the group takes from (at first its home). When that one
+// runs dry the group reads the others at once (plain loads, which do not queue
+// up as atomics do) and moves on to the next one with chunks left, in cyclic
+// order, so groups that run dry together spread out. Cursors only grow, so the
+// search ends; the first group to see all of them dry says so in one word,
+// which later ones read instead.
+template <int G>
+__device__ __forceinline__ int64_t next_chunk(const Group<G>& grp, unsigned long long* queue, int64_t n_chunks,
+                                              int* cur) {
+    // opaque, so that nothing computed from the lane for a grab is kept in
+    // registers through the search between grabs
+    int gl = grp.gl;
+    asm volatile("" : "+v"(gl));
+    for (;;) {
+        const int c = uni<G>(*cur);
+        unsigned long long v = 0;
+        if (gl == 0) v = atomicAdd(&queue[c * (kCursorStep * kSlotWords) + SLOT_CURSOR], 1ull);
+        const int64_t q = uni64<G>((int64_t)grp.bcast(v, 0)) * kCursors + c;
+        if (q < n_chunks) return q;
+        if (__hip_atomic_load(&queue[kDoneWord], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return -1;
+        uint32_t left = 0;
+#pragma unroll 1
+        for (int base = 0; base < kCursors; base += G) {
+            const int i = base + gl;
+            bool some = false;
+            if (i < kCursors) {
+                const unsigned long long t = __hip_atomic_load(&queue[i * (kCursorStep * kSlotWords) + SLOT_CURSOR],
+                                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                some = (int64_t)t * kCursors + i < n_chunks;
+            }
+            left |= (uint32_t)grp.ballot(some) << base;
+        }
+        if (left == 0) {
+            if (gl == 0)
+                __hip_atomic_store(&queue[kDoneWord], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return -1;
+        }
+        const uint32_t from = (uint32_t)(c + 1) & (kCursors - 1);
+        const uint32_t rot = (left >> from) | (left << (kCursors - from));
+        group_fence();
+        *cur = (int)((from + (uint32_t)__builtin_ctz(rot)) & (kCursors - 1));
+        group_fence();
+    }
+}
+
+// Next grab of a group: `chunk` tasks [*t0, *t1), or false once every cursor
+// is exhausted. With XCD blocks the group starts at its own XCD's cursor
+// (*q = 0) and moves on to the next XCD's when it runs dry; it never comes
+// back to one that was dry.
 template <int G>
 __device__ __forceinline__ bool grab_tasks(const Group<G>& grp, unsigned long long* queue, int64_t n_tasks,
-                                           int64_t chunk, int64_t xcd_block, int* q, int64_t* t0, int64_t* t1) {
+                                           int64_t n_chunks, int64_t chunk, int64_t xcd_block, int* q, int64_t* t0,
+                                           int64_t* t1) {
     if (xcd_block <= 0) {
-        unsigned long long v = 0;
-        if (grp.gl == 0) v = atomicAdd(queue, (unsigned long long)chunk);
-        const int64_t a = uni64<G>((int64_t)grp.bcast(v, 0));
-        if (a >= n_tasks) return false;
-        *t0 = a;
-        *t1 = min(a + chunk, n_tasks);
+        const int64_t a = next_chunk<G>(grp, queue, n_chunks, q);
+        if (a < 0) return false;
+        *t0 = a * chunk;
+        *t1 = min(*t0 + chunk, n_tasks);
         return true;
     }
     const int home = (int)(blockIdx.x % kXcds);
-    while (*q < kXcds) {
-        const int x = (home + *q) % kXcds;
+    for (int tries = *q; tries < kXcds; ++tries) {
+        const int x = (home + tries) % kXcds;
         const int64_t nx = xcd_tasks(n_tasks, xcd_block, x);
         unsigned long long v = 0;
-        if (grp.gl == 0) v = atomicAdd(&queue[2 + x], (unsigned long long)chunk);
+        if (grp.gl == 0) v = atomicAdd(&queue[x * (kCursorStep * kSlotWords) + SLOT_CURSOR], (unsigned long long)chunk);
         const int64_t j = uni64<G>((int64_t)grp.bcast(v, 0));
         if (j < nx) {
             *t0 = xcd_task(j, xcd_block, x);
             *t1 = *t0 + min(chunk, nx - j);
+            *q = tries;
             return true;
         }
-        ++*q;
     }
     return false;
 }
@@ -1282,7 +1357,8 @@ constexpr int occupancy_target(int K, int G, int LEAF, int IEP = 0) {
 
 template <int K, int G, int LEAF, int MODE, int IEP>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(occupancy_target(K, G, LEAF, IEP)))) void count_kernel(GpPlanDesc d, CountArgs a) {
-    __shared__ int32_t s_len[kBlock / G][GP_DESC_MAX_BUILDS];
+    // a group's buffer lengths, then its task cursor's index
+    __shared__ int32_t s_len[kBlock / G][GP_DESC_MAX_BUILDS + 1];
     Ctx<G> c;
     c.row_ptr = a.row_ptr;
     c.col = a.col;
@@ -1317,10 +1393,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(occupanc
     uint64_t acc = 0, carry = 0;
     const int64_t chunk = a.chunk;
 
-    int q = 0;
+    c.lens[GP_DESC_MAX_BUILDS] = a.xcd_block > 0 ? 0 : (int)(group_id & (kCursors - 1));
+    group_fence();
     for (;;) {
         int64_t t0 = 0, t1 = 0;
-        if (!grab_tasks<G>(c.g, a.queue, a.n_tasks, chunk, a.xcd_block, &q, &t0, &t1)) break;
+        if (!grab_tasks<G>(c.g, a.queue, a.n_tasks, a.n_chunks, chunk, a.xcd_block, c.lens + GP_DESC_MAX_BUILDS, &t0, &t1)) break;
         const uint64_t t_chunk = a.busy ? wall_clock64() : 0;
         run_tasks<K, G, LEAF, MODE, IEP>(d, c, ts, t0, t1, acc, carry, a.per_root);
         if (a.busy) {
@@ -1345,7 +1422,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(occupanc
     for (int off = 32; off >= 1; off >>= 1) cm = max(cm, (uint64_t)__shfl_xor(cm, off, 64));
     const bool any_stop = __ballot(stopped) != 0;
     if (__lane_id() == 0) {
-        publish128(&a.result[0], &a.queue[1], s, s_hi);
+        unsigned long long* slot = a.queue + (blockIdx.x & (kSlots - 1)) * kSlotWords;
+        publish128(&slot[SLOT_LO], &slot[SLOT_HI], s, s_hi);
         if (any_stop) atomicOr(&a.result[1], 4ull);
         if constexpr (MODE == MODE_ACCOUNT) atomicAdd(&a.result[2], (unsigned long long)bytes);
         if (a.busy) {

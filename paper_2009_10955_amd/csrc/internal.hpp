@@ -56,8 +56,8 @@ struct LaunchCfg {
 // grab, or 0 for one cursor (the default).
 int64_t xcd_block_tasks(const DeviceGraph& g, const LaunchCfg& cfg, int group);
 
-// Device memory a launch may use instead of allocating its own: the task
-// cursor and high count word, the per-group candidate buffers and, when room
+// Device memory a launch may use instead of allocating its own: the queue
+// of task cursors, the per-group candidate buffers and, when room
 // is left, leaf mode 4's memo. The grid shrinks so the buffers fit.
 struct Workspace {
     void* base = nullptr;  // 256-byte aligned
@@ -76,11 +76,12 @@ gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCf
                        unsigned long long* per_root, bool account = false,
                        unsigned long long* busy = nullptr, const Workspace* ws = nullptr);
 
-// launch_count without allocating: the task cursor, candidate buffers and
-// memo come from one static device array of kNoallocWorkspaceBytes per GPU
+// launch_count without allocating: the queue (kNoallocQueueBytes), candidate
+// buffers and memo (kNoallocWorkspaceBytes) come from one static device array per GPU
 // (the grid shrinks so they fit; GP_ERR_NOMEM when not even one block's
 // buffers fit). Calls that overlap on one GPU share that array and race.
 constexpr size_t kNoallocWorkspaceBytes = size_t(32) << 20;
+constexpr size_t kNoallocQueueBytes = size_t(16) << 10;
 gp_status launch_count_noalloc(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCfg& cfg,
                                hipStream_t stream, unsigned long long* result_dev);
 
@@ -122,9 +123,8 @@ struct BatchState {
     int64_t memo_words = 0;
     int32_t* scratch = nullptr;
     unsigned long long* memo = nullptr;
-    unsigned long long* queues = nullptr;  // np task cursors
+    unsigned long long* queues = nullptr;  // per plan: a queue of task cursors and partial totals
     unsigned long long* result = nullptr;  // 4*np: count low word, flags, busy clock ticks, count high word
-    unsigned long long* run_queues = nullptr;  // kBatchMaxPlans * kQueueWords: solo runs' queue words
     std::vector<BatchRun> runs;            // host: the launches, in batch order
     std::vector<GpPlanDesc> h_descs;       // host copies: launches take them as kernel arguments
     std::vector<char> h_plans;             // the per-plan task ranges and shapes, likewise

@@ -50,7 +50,8 @@ struct ListArgs {
     int32_t n_hubs;
     int32_t* scratch;
     int64_t buf_cap;
-    unsigned long long* queue;
+    unsigned long long* queue;  // gpcount::kQueueWords
+    int64_t n_chunks;           // ceil(n_roots / chunk)
     // count pass: embeddings of root task t; write pass: its first row
     unsigned long long* task_rows;
     int32_t* out;               // out_cap rows of k int32
@@ -281,16 +282,18 @@ __global__ __launch_bounds__(kBlock) void list_kernel(GpPlanDesc d, ListArgs a) 
     c.tag = 0;
     c.memo_log2 = 0;
     const int64_t chunk = a.chunk;
+    __shared__ int s_cur[kBlock / G];
+    s_cur[grp] = (int)(group_id & (gpcount::kCursors - 1));
+    gpcount::group_fence();
     for (;;) {
-        unsigned long long t0 = 0;
-        if (c.g.gl == 0) t0 = atomicAdd(a.queue, (unsigned long long)chunk);
-        t0 = (unsigned long long)gpcount::uni64<G>((int64_t)c.g.bcast(t0, 0));
-        if ((int64_t)t0 >= a.n_roots) break;
-        const int64_t t1 = min((int64_t)t0 + chunk, a.n_roots);
+        const int64_t q = gpcount::next_chunk<G>(c.g, a.queue, a.n_chunks, &s_cur[grp]);
+        if (q < 0) break;
+        const int64_t t0 = q * chunk;
+        const int64_t t1 = min(t0 + chunk, a.n_roots);
         if constexpr (K == 2) {
             // every root edge is an embedding: lanes take different roots
             static_assert(WRITE, "edges need no count pass");
-            for (int64_t base = (int64_t)t0; base < t1; base += G) {
+            for (int64_t base = t0; base < t1; base += G) {
                 const int64_t r = base + c.g.gl;
                 if (r < t1 && r < a.out_cap) {
                     const int2 e = a.roots[a.root_offset + r * a.root_stride];
@@ -300,7 +303,7 @@ __global__ __launch_bounds__(kBlock) void list_kernel(GpPlanDesc d, ListArgs a) 
                 }
             }
         } else {
-            for (int64_t t = (int64_t)t0; t < t1; ++t) {
+            for (int64_t t = t0; t < t1; ++t) {
                 const int2 e = a.roots[a.root_offset + t * a.root_stride];
                 int32_t v[K];
 #pragma unroll
@@ -325,7 +328,7 @@ __global__ void invert_ids(const int32_t* new_id, int64_t n, int32_t* orig) {
 }
 
 __global__ void zero_words(unsigned long long* p, int n) {
-    if ((int)threadIdx.x < n) p[threadIdx.x] = 0;
+    for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0;
 }
 
 // found = {total rows, 0}: the last offset plus the last task's count
@@ -420,7 +423,7 @@ gp_status launch_list(const DeviceGraph& g, const GpPlanDesc& d, const int32_t* 
         hipcub::DeviceScan::ExclusiveSum(nullptr, scan_bytes, (unsigned long long*)nullptr,
                                          (unsigned long long*)nullptr, (int)n_roots, stream) != hipSuccess)
         return GP_ERR_HIP;
-    if (!get((void**)&queue, sizeof(unsigned long long)) || !get((void**)&orig, sizeof(int32_t) * g.n) ||
+    if (!get((void**)&queue, sizeof(unsigned long long) * gpcount::kQueueWords) || !get((void**)&orig, sizeof(int32_t) * g.n) ||
         (scratch_bytes && !get((void**)&scratch, scratch_bytes)) ||
         (two_pass && (!get((void**)&cnt, sizeof(unsigned long long) * n_roots) ||
                       !get((void**)&off, sizeof(unsigned long long) * n_roots) || !get(&scan_tmp, scan_bytes)))) {
@@ -444,6 +447,7 @@ gp_status launch_list(const DeviceGraph& g, const GpPlanDesc& d, const int32_t* 
     a.scratch = scratch;
     a.buf_cap = cap;
     a.queue = queue;
+    a.n_chunks = need;
     a.task_rows = nullptr;
     a.out = out;
     a.out_cap = out_cap;
@@ -453,7 +457,7 @@ gp_status launch_list(const DeviceGraph& g, const GpPlanDesc& d, const int32_t* 
     if (two_pass) {
         // rows per root task, their offsets, the total; then the rows
         a.task_rows = cnt;
-        hipLaunchKernelGGL(zero_words, dim3(1), dim3(64), 0, stream, queue, 1);
+        hipLaunchKernelGGL(zero_words, dim3(1), dim3(1024), 0, stream, queue, gpcount::kQueueWords);
         hipLaunchKernelGGL(count_fn, dim3((unsigned)blocks), dim3(kBlock), 0, stream, d, a);
         if (hipcub::DeviceScan::ExclusiveSum(scan_tmp, scan_bytes, cnt, off, (int)n_roots, stream) != hipSuccess) {
             release();
@@ -461,12 +465,12 @@ gp_status launch_list(const DeviceGraph& g, const GpPlanDesc& d, const int32_t* 
         }
         hipLaunchKernelGGL(list_total, dim3(1), dim3(64), 0, stream, cnt, off, n_roots, found_dev);
         a.task_rows = off;
-        hipLaunchKernelGGL(zero_words, dim3(1), dim3(64), 0, stream, queue, 1);
+        hipLaunchKernelGGL(zero_words, dim3(1), dim3(1024), 0, stream, queue, gpcount::kQueueWords);
         hipLaunchKernelGGL(write_fn, dim3((unsigned)blocks), dim3(kBlock), 0, stream, d, a);
     } else if (n_roots > 0) {
         // edges: root t is row t
         hipLaunchKernelGGL(set_total, dim3(1), dim3(64), 0, stream, found_dev, n_roots);
-        hipLaunchKernelGGL(zero_words, dim3(1), dim3(64), 0, stream, queue, 1);
+        hipLaunchKernelGGL(zero_words, dim3(1), dim3(1024), 0, stream, queue, gpcount::kQueueWords);
         hipLaunchKernelGGL(write_fn, dim3((unsigned)blocks), dim3(kBlock), 0, stream, d, a);
     } else {
         hipLaunchKernelGGL(zero_words, dim3(1), dim3(64), 0, stream, found_dev, 2);
