@@ -91,17 +91,16 @@ __global__ void zero_u64(unsigned long long* p, int64_t n) {
 // IEP plans: some inner set is left unbuilt as N(a) & N(x) with a an outer
 // vertex's list and no cut, so its size depends on (a, x) alone and the
 // kernel keeps it in a table shared by the launch's groups
-// (count_kernel.hpp, iep_subset_count).
+// (count_kernel.hpp, pair_count); likewise the sizes that iep_pair_sum adds.
 bool iep_memo_eligible(const GpPlanDesc& d) {
     if (!d.iep) return false;
-    for (int j = d.k - d.iep; j < d.k; ++j) {
-        const GpLevel& lv = d.lv[j];
-        if (lv.last_list >= 0 && lv.pre_buf < 0 && lv.pre_list >= 0 && (lv.hi_src | lv.lo_src) == 0) return true;
-    }
-    return false;
+    for (int m = 0; m < (1 << d.iep) - 1; ++m)
+        if (d.it[m].memo && d.it[m].alias < 0) return true;
+    const GpLevel& lv = d.lv[d.k - d.iep - 1];
+    return d.iep_sum && lv.list >= 0 && (lv.hi_src | lv.lo_src) == 0;
 }
 
-// log2 of the IEP memo's words per hub: the most ways, up to
+// log2 of the IEP memo's rows of n_hubs words: the most ways, up to
 // kIepMemoWaysMax, whose table of n_hubs x ways words fits words_cap
 // words; -1 if not even one way fits.
 int iep_memo_log2(int64_t n_hubs, int64_t words_cap) {
@@ -161,7 +160,10 @@ LaunchCfg default_launch(const GpPlanDesc& d) {
     LaunchCfg cfg;
     cfg.group = 64;
     cfg.waves_per_cu = 32;
-    cfg.chunk = d.k <= 3 ? 256 : 4;
+    // where lanes take different root edges (k <= 3, or IEP over every level
+    // after the root) a grab fills the lanes of a group: the 4-star with IEP on
+    // R-MAT (91K vertices, 907K edges) takes 116 ms at 4 per grab, 0.13 at 64
+    cfg.chunk = d.k <= 3 || d.iep == d.k - 2 ? 64 : 4;
     cfg.leaf = 1;
     cfg.split_ways = 16;
     cfg.split_vertices = 256;
@@ -720,6 +722,9 @@ gp_status batch_enqueue(const DeviceGraph& g, const BatchState& st, hipStream_t 
         a.nbuf = st.nbuf;
         a.slots_per_wave = 64 / r.group;
         a.memo = st.memo_words > 0 ? st.memo : nullptr;
+        a.iep_memo_log2 = r.iep && st.memo_words > 0
+                              ? iep_memo_log2(g.n_hubs, std::min(st.memo_words, kIepMemoBytes / 8))
+                              : -1;
         a.queues = st.queues + (int64_t)r.p0 * kQueueWords;
         RunDescs rd;
         std::memset(&rd, 0, sizeof rd);

@@ -51,9 +51,13 @@ __device__ void run_piece(const BatchArgs& a, const GpPlanDesc& d, const BatchPl
     c.sj = 0;
     c.sJ = 1;
     c.deadline = 0;
-    c.memo = (a.memo && bp.tag_base) ? a.memo + slot * (int64_t)a.n_hubs : nullptr;
+    // leaf mode 4: a table per group; IEP: one table for the launch
+    c.memo = IEP > 0 ? (a.iep_memo_log2 >= 0 ? a.memo : nullptr)
+                     : ((a.memo && bp.tag_base) ? a.memo + slot * (int64_t)a.n_hubs : nullptr);
     c.tag = 0;
-    c.memo_log2 = 0;
+    c.memo_log2 = max(a.iep_memo_log2, 0);
+    __shared__ uint32_t s_cnt[IEP > 0 ? ((1 << IEP) - 1) * kBlock : 1];
+    c.cnt = &s_cnt[IEP > 0 ? threadIdx.x : 0];
     TaskSpace ts;
     ts.roots = bp.roots;
     ts.offset = bp.root_offset;

@@ -118,7 +118,7 @@ struct CountArgs {
     // optional (leaf mode 4, plans the host found eligible): per group,
     // n_hubs words {root tag, |N(x) & pre & cut|} for hub candidates x
     // or (IEP plans the host found eligible) one table for the launch of
-    // n_hubs << memo_ways_log2 words {a + 1 with the high bit set, |N(a) & N(x)|}
+    // 2^memo_ways_log2 rows of n_hubs words {a + 1 with the high bit set, |N(a) & N(x)|}
     unsigned long long* memo;
     int32_t chunk;
     int32_t memo_ways_log2;
@@ -173,7 +173,8 @@ struct BatchArgs {
     int64_t buf_cap;
     int32_t nbuf;            // buffer slots per group (max over plans)
     int32_t slots_per_wave;  // 64 / (the smallest group of any plan)
-    unsigned long long* memo;     // per wavefront: slots_per_wave x n_hubs words (or null)
+    unsigned long long* memo;     // leaf mode 4: per wavefront slots_per_wave x n_hubs words; IEP: one table (or null)
+    int32_t iep_memo_log2;        // IEP: log2 of the table's rows of n_hubs words; -1: none
     unsigned long long* queues;   // per plan: kSlots slots
 };
 
@@ -247,7 +248,8 @@ struct Ctx {
     uint64_t deadline;  // clock tick after which every search loop stops (0: none)
     unsigned long long* memo;  // this group's last-level memo, or the launch's IEP memo (null: none)
     uint32_t tag;              // memo validity tag of the current root
-    int32_t memo_log2;         // IEP memo: log2 of its words per hub
+    int32_t memo_log2;         // IEP memo: log2 of its rows
+    uint32_t* cnt;             // IEP: this lane's subset sizes in LDS, kBlock words apart
     Group<G> g;
 
     __device__ __forceinline__ bool expired() const {
@@ -274,9 +276,9 @@ struct Ctx {
 // v[idx] for a runtime idx without dynamic register indexing.
 template <int K>
 __device__ __forceinline__ int32_t pick(const int32_t (&v)[K], int idx) {
-    int32_t r = v[0];
+    int32_t r = 0;
 #pragma unroll
-    for (int j = 1; j < K; ++j) r = (idx == j) ? v[j] : r;
+    for (int j = 0; j < K; ++j) r |= (idx == j) ? v[j] : 0;
     return r;
 }
 
@@ -538,180 +540,223 @@ __device__ __forceinline__ uint32_t leaf_group(const GpPlanDesc& d, const Ctx<G>
 // component's sets|. Terms whose graphs have the same components are
 // collected here: a partition of the N levels into blocks contributes
 // prod over blocks B of (-1)^(|B|-1) (|B|-1)! |∩_{j in B} S_j| (the sum of
-// (-1)^edges over the connected graphs on |B| vertices). GRP: computed by the
-// whole group (same value in every lane), else by one lane. The value fits
+// (-1)^edges over the connected graphs on |B| vertices). The value fits
 // in 128 bits (each |S_j| < 2^31, N <= 4).
 //
-// A set S_j is either explicit (one neighbor list, or a buffer built by the
-// builds) or, when its last parent is the last outer level, left unbuilt as
-// pre & N(x) (pre: a list or buffer; x: that outer vertex), like the last
-// level of a plain count. Each |∩ S_j| walks the shortest operand of the
-// sets involved, cut to the common range, and tests every element in the
-// other operands (a bit in a hub's bitmap, else a binary search).
-// The IEP memo: one table per launch, shared by every group, of W = 2^l
-// words per hub (l = CountArgs::memo_ways_log2). Word x * W + (a mod W)
-// holds |N(a) & N(x)| tagged a. The host takes the most ways, up to
+// How |∩_{j in M} S_j| is computed is laid down per subset M by the planner
+// (GpIepTerm): the fewest operands that cover the parents (a set built from
+// N(v0) needs no test against N(v0)), the outer images that may lie in the
+// intersection and are subtracted, and an earlier subset with the same set
+// (inner levels with the same parents: one walk instead of three for N = 2,
+// seven for N = 3). One loop over the subsets, not unrolled: the kernel carries
+// one copy of the walk, where a copy per subset for lanes and for groups spilled
+// up to 3.6 KB per lane.
+//
+// Every lane holds one binding. A lane walks the shorter operand alone when it
+// has at most kIepLaneWork elements; longer walks are taken by the whole group,
+// one lane's after another, and only those: the lane keeps its binding and the
+// other subsets' sizes.
+//
+// The memo: one table per launch, shared by every group, of W = 2^l rows of
+// n_hubs words (l = CountArgs::memo_ways_log2). Word (a mod W) * n_hubs + x
+// holds {a + 1 with the high bit set (apart from leaf mode 4's root tags),
+// |N(a) & N(x)|} for hubs a and x: a size that depends on (a, x) alone, the
+// same for every plan, group and launch on the graph. Rows by a, the endpoint
+// bound first: the lanes look up ascending x of one a, in neighbouring words
+// that stay in L2 while groups work on roots of a (rows by x: every lookup a
+// line of its own, 512 KB apart). Tag and size share one 64-bit word, written
+// and read whole, so a word another group overwrote, or one not yet visible,
+// only ever reads as a miss. The host takes the most ways, up to
 // kIepMemoWaysMax, whose table fits kIepMemoBytes (or the room left).
 constexpr int64_t kIepMemoWaysMax = 4096;
 constexpr int64_t kIepMemoBytes = int64_t(2) << 30;
+constexpr int32_t kIepLaneWork = 96;
 
-constexpr int low_bit(int m) {
-    int i = 0;
-    while (!((m >> i) & 1)) ++i;
-    return i;
+// The memo word of hubs (a, x), or null.
+template <int G>
+__device__ __forceinline__ unsigned long long* iep_memo_word(const Ctx<G>& c, int32_t a, int32_t x) {
+    if (!c.memo || a >= c.n_hubs || x >= c.n_hubs) return nullptr;
+    return c.memo + (int64_t)(a & ((int32_t(1) << c.memo_log2) - 1)) * c.n_hubs + x;
 }
 
-// |∩_{j in M} S_j| for one subset M of the inner levels (compile-time).
-template <int K, int G, int MODE, int N, bool GRP, int M>
-__device__ __forceinline__ uint64_t iep_subset_count(const GpPlanDesc& d, const Ctx<G>& c, const int32_t (&v)[K],
-                                                     uint64_t& bytes) {
-    constexpr int F = K - N;  // first inner level
-    // the operands of the sets in M (two per unbuilt set, else one; an absent
-    // second operand has p == nullptr) and the common range
-    Set X[2 * N];
-    int32_t L = 0, H = 0x7fffffff;
-    uint32_t im = 0;
-#pragma unroll
-    for (int j = 0; j < N; ++j) {
-        X[2 * j] = Set{nullptr, 0x7fffffff, nullptr};
-        X[2 * j + 1] = Set{nullptr, 0x7fffffff, nullptr};
-        if (!((M >> j) & 1)) continue;
-        const GpLevel& lv = d.lv[F + j];
-        int32_t lo, hi;
-        bounds<K>(lv.hi_src, lv.lo_src, v, lo, hi);
-        L = max(L, lo);
-        H = min(H, hi);
-        im |= lv.inj;
-        if (lv.last_list >= 0) {
-            if constexpr (GRP) {
-                X[2 * j] = lv.pre_buf >= 0 ? c.buf_u(lv.pre_buf) : c.nbr_u(pick<K>(v, lv.pre_list));
-                X[2 * j + 1] = c.nbr_u(pick<K>(v, lv.last_list));
+// Whether data vertices u and v are adjacent: a bit of the higher-degree one's
+// bitmap, else a search in the shorter list.
+template <int G, int MODE>
+__device__ __forceinline__ bool adjacent(const Ctx<G>& c, int32_t u, int32_t v) {
+    const int32_t h = min(u, v), o = max(u, v);
+    if (h < c.n_hubs) {
+        if constexpr (MODE == MODE_ACCOUNT) *c.bytes += 4;
+        return (c.hub_bits[(int64_t)h * c.hub_words + (o >> 5)] >> (o & 31)) & 1u;
+    }
+    const Set s = c.nbr(o);
+    if constexpr (MODE == MODE_ACCOUNT) *c.bytes += probe_bytes(s.n);
+    return contains(s.p, s.n, h);
+}
+
+// What one pair_count call counts: |A & B & E1 & E2 & [lo, hi)|, A and B per
+// lane, E1 and E2 group-uniform and ne of them used (ne < 0: A alone); cut:
+// whether lo, hi restrict. memo: the word that keeps the size (uncut pairs),
+// or null, its tag alongside.
+struct PairOps {
+    Set A, B, E1, E2;
+    int ne;
+    bool cut;
+    int32_t lo, hi;
+    unsigned long long* memo;
+    uint32_t tag;
+};
+
+// The size of every active lane's p. Called by all lanes of the group together.
+template <int G, int MODE>
+__device__ __forceinline__ uint32_t pair_count(const Ctx<G>& c, const PairOps& p, bool active) {
+    Set A = p.A, B = p.B;
+    const Set &E1 = p.E1, &E2 = p.E2;
+    const int ne = p.ne;
+    const bool cut = p.cut;
+    const int32_t lo = p.lo, hi = p.hi;
+    unsigned long long* memo = p.memo;
+    const uint32_t tag = p.tag;
+    uint32_t r = 0;
+    bool longw = false;
+    if (ne < 0) {
+        if (active) {
+            if (cut) {
+                if constexpr (MODE == MODE_ACCOUNT) *c.bytes += cut_bytes(A, lo, hi);
+                A = trim(A, lo, hi);
+            }
+            r = (uint32_t)A.n;
+        }
+        return r;
+    }
+    if (active) {
+        bool walk = true;
+        if (memo) {
+            const unsigned long long e = __hip_atomic_load(memo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if constexpr (MODE == MODE_ACCOUNT) *c.bytes += 8;
+            if ((uint32_t)(e >> 32) == tag) {
+                r = (uint32_t)e;
+                memo = nullptr;
+                walk = false;
+            }
+        }
+        if (walk) {
+            if (B.n < A.n) {
+                const Set t = A;
+                A = B;
+                B = t;
+            }
+            if (cut) {
+                if constexpr (MODE == MODE_ACCOUNT) *c.bytes += cut_bytes(A, lo, hi);
+                A = trim(A, lo, hi);
+            }
+            if constexpr (MODE == MODE_ACCOUNT) *c.bytes += (uint64_t)A.n * (4 + test_bytes(B));
+            if (A.n > kIepLaneWork) {
+                longw = true;
+            } else if (ne == 0) {
+                r = intersect_count_serial(A, B);
             } else {
-                X[2 * j] = lv.pre_buf >= 0 ? c.buf(lv.pre_buf) : c.nbr(pick<K>(v, lv.pre_list));
-                X[2 * j + 1] = c.nbr(pick<K>(v, lv.last_list));
+                for (int32_t i = 0; i < A.n; ++i) {
+                    const int32_t y = A.p[i];
+                    r += member(B, y) && member(E1, y) && (ne < 2 || member(E2, y));
+                }
+            }
+        }
+    }
+    uint64_t m = c.g.ballot(longw);
+    while (m) {
+        const int src = __builtin_ctzll(m);
+        m &= m - 1;
+        const int32_t* ap = (const int32_t*)uni64<G>(c.g.bcast((long long)A.p, src));
+        const int32_t* bp = (const int32_t*)uni64<G>(c.g.bcast((long long)B.p, src));
+        const uint32_t* bb = (const uint32_t*)uni64<G>(c.g.bcast((long long)B.bits, src));
+        const int32_t an = uni<G>(c.g.bcast(A.n, src)), bn = uni<G>(c.g.bcast(B.n, src));
+        const Set W{bp, bn, bb};
+        uint32_t mine = 0;
+        if (ne == 0 && bb) {
+            // four elements per lane in flight
+            int32_t i = c.g.gl;
+            for (; i + 3 * G < an; i += 4 * G) {
+                const int32_t y0 = ap[i], y1 = ap[i + G], y2 = ap[i + 2 * G], y3 = ap[i + 3 * G];
+                const uint32_t w0 = bb[y0 >> 5], w1 = bb[y1 >> 5], w2 = bb[y2 >> 5], w3 = bb[y3 >> 5];
+                mine += ((w0 >> (y0 & 31)) & 1u) + ((w1 >> (y1 & 31)) & 1u) + ((w2 >> (y2 & 31)) & 1u) +
+                        ((w3 >> (y3 & 31)) & 1u);
+            }
+            for (; i < an; i += G) {
+                const int32_t y = ap[i];
+                mine += (bb[y >> 5] >> (y & 31)) & 1u;
             }
         } else {
-            if constexpr (GRP) X[2 * j] = lv.list >= 0 ? c.nbr_u(pick<K>(v, lv.list)) : c.buf_u(lv.buf);
-            else X[2 * j] = lv.list >= 0 ? c.nbr(pick<K>(v, lv.list)) : c.buf(lv.buf);
-        }
-    }
-    if constexpr (GRP && (M & (M - 1)) == 0) {
-        // one unbuilt set N(a) & N(x) with no cut, x a hub: its size is a
-        // function of (a, x) alone, the same for every plan, group and launch
-        // on the graph. It is kept in the launch's shared memo table, in the
-        // word of x chosen by a, tagged a (high bit set, apart from leaf mode
-        // 4's root tags). Bindings that share a and x (roots with the same
-        // hub endpoint reach the same x through many middle vertices, in
-        // every group working on that endpoint) then walk the lists once.
-        // Tag and size share one 64-bit word, written and read whole, so a
-        // word another group overwrote, or one not yet visible, only ever
-        // reads as a miss.
-        constexpr int jj = low_bit(M);
-        const GpLevel& lv = d.lv[F + jj];
-        if (c.memo && lv.last_list >= 0 && lv.pre_buf < 0 && (lv.hi_src | lv.lo_src) == 0) {
-            const int32_t xk = pick<K>(v, lv.last_list);
-            if (xk < c.n_hubs) {
-                const int32_t av = pick<K>(v, lv.pre_list);
-                const uint32_t tag = 0x80000000u | (uint32_t)(av + 1);
-                const Set A0 = X[2 * jj], A1 = X[2 * jj + 1];
-                unsigned long long* const w =
-                    c.memo + ((int64_t)xk << c.memo_log2) + (av & ((int32_t(1) << c.memo_log2) - 1));
-                const unsigned long long e = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if constexpr (MODE == MODE_ACCOUNT) bytes += 8;
-                uint64_t raw;
-                if ((uint32_t)(e >> 32) == tag) {
-                    raw = (uint32_t)e;
-                } else {
-                    const Set Wm = A0.n <= A1.n ? A0 : A1, Om = A0.n <= A1.n ? A1 : A0;
-                    if constexpr (MODE == MODE_ACCOUNT) bytes += (uint64_t)Wm.n * (4 + test_bytes(Om)) + 8;
-                    raw = 0;
-                    for (int32_t base = 0; base < Wm.n; base += G) {
-                        const int32_t i = base + c.g.gl;
-                        const bool ok = i < Wm.n && member(Om, Wm.p[i]);
-                        raw += (uint64_t)__popcll(c.g.ballot(ok));
-                    }
-                    if (c.g.gl == 0)
-                        __hip_atomic_store(w, ((unsigned long long)tag << 32) | raw, __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT);
-                }
-                // outer images in the set (distinct: the binding is injective)
-#pragma unroll
-                for (int o = 0; o < F; ++o)
-                    if ((im >> o) & 1u) {
-                        const int32_t y = v[o];
-                        if constexpr (MODE == MODE_ACCOUNT) bytes += test_bytes(A0) + test_bytes(A1);
-                        if (member(A0, y) && member(A1, y)) --raw;
-                    }
-                return raw;
+            for (int32_t i = c.g.gl; i < an; i += G) {
+                const int32_t y = ap[i];
+                mine += member(W, y) && (ne < 1 || member(E1, y)) && (ne < 2 || member(E2, y));
             }
         }
+        const uint32_t tot = c.g.sum(mine);
+        if (c.g.gl == src) r = tot;
     }
-    // the shortest operand, cut to [L, H), is walked
-    int s = 0;
-    int32_t sn = 0x7fffffff;
-#pragma unroll
-    for (int f = 0; f < 2 * N; ++f)
-        if (((M >> (f / 2)) & 1) && X[f].p && X[f].n < sn) {
-            sn = X[f].n;
-            s = f;
-        }
-    Set W{nullptr, 0, nullptr};
-#pragma unroll
-    for (int f = 0; f < 2 * N; ++f)
-        if (((M >> (f / 2)) & 1) && f == s) W = X[f];
-    if constexpr (MODE == MODE_ACCOUNT) bytes += cut_bytes(W, L, H);
-    if constexpr (GRP) W = trim_u<G>(W, L, H);
-    else W = trim(W, L, H);
-    constexpr bool one = (M & (M - 1)) == 0;
-    if (one && X[2 * __builtin_ctz(M) + 1].p == nullptr) {
-        // one built set: its size, without the outer images in it
-        uint64_t cm = (uint64_t)W.n;
-#pragma unroll
-        for (int o = 0; o < F; ++o) {
-            if ((im >> o) & 1u) {
-                const int32_t y = v[o];
-                if (y >= L && y < H) {
-                    if constexpr (MODE == MODE_ACCOUNT) bytes += test_bytes(W);
-                    if (member(W, y)) --cm;
-                }
-            }
-        }
-        return cm;
+    if (memo) {
+        __hip_atomic_store(memo, ((unsigned long long)tag << 32) | r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if constexpr (MODE == MODE_ACCOUNT) *c.bytes += 8;
     }
-    if constexpr (MODE == MODE_ACCOUNT) {
-        uint64_t per = 4;
-#pragma unroll
-        for (int f = 0; f < 2 * N; ++f)
-            if (((M >> (f / 2)) & 1) && X[f].p && f != s) per += test_bytes(X[f]);
-        bytes += (uint64_t)W.n * per;
-    }
-    uint64_t cm = 0;
-    const int32_t step = GRP ? G : 1;
-    const int32_t first = GRP ? c.g.gl : 0;
-    for (int32_t base = 0; base < W.n; base += step) {
-        const int32_t i = base + first;
-        bool ok = false;
-        if (i < W.n) {
-            const int32_t x = W.p[i];
-            ok = !inj_hit<K>(im, v, x);
-#pragma unroll
-            for (int f = 0; f < 2 * N; ++f)
-                if (((M >> (f / 2)) & 1) && f != s && X[f].p) ok = ok && member(X[f], x);
-        }
-        if constexpr (GRP) cm += (uint64_t)__popcll(c.g.ballot(ok));
-        else cm += ok ? 1u : 0u;
-    }
-    return cm;
+    return r;
 }
 
-template <int K, int G, int MODE, int N, bool GRP, int... Ms>
-__device__ __forceinline__ unsigned __int128 iep_combine(const GpPlanDesc& d, const Ctx<G>& c,
-                                                         const int32_t (&v)[K], uint64_t& bytes,
-                                                         std::integer_sequence<int, Ms...>) {
-    // cnt[M] for every nonempty subset M (cnt[0] unused)
-    const uint64_t cnt[(1 << N)] = {0, iep_subset_count<K, G, MODE, N, GRP, Ms + 1>(d, c, v, bytes)...};
+template <int K, int G>
+__device__ __forceinline__ Set iep_operand(const Ctx<G>& c, const int32_t (&w)[K], int op) {
+    return op >= 0 ? c.nbr(pick<K>(w, op)) : c.buf(-1 - op);
+}
+
+// The outer images among w[0..F-1] that lie in a term's set, of the levels in
+// t.inj: w[o] is in the cut and adjacent to every parent's image (those the
+// pattern makes adjacent are not tested).
+template <int K, int G, int MODE, int F>
+__device__ __forceinline__ uint32_t iep_images(const GpPlanDesc& d, const Ctx<G>& c, const GpIepTerm& t, uint32_t inj,
+                                               const int32_t (&w)[K], int32_t lo, int32_t hi) {
+    uint32_t n = 0;
+#pragma unroll
+    for (int o = 0; o < F; ++o) {
+        if (!((inj >> o) & 1u)) continue;
+        const int32_t y = w[o];
+        bool in = y >= lo && y < hi;
+        uint32_t need = t.pm & ~(uint32_t)d.adj[o];
+        while (need) {
+            const int p = __builtin_ctz(need);
+            need &= need - 1;
+            if (in) in = adjacent<G, MODE>(c, y, pick<K>(w, p));
+        }
+        n += in ? 1u : 0u;
+    }
+    return n;
+}
+
+// The operands of term t for an active lane's binding w.
+template <int K, int G>
+__device__ __forceinline__ void iep_operands(const Ctx<G>& c, const GpIepTerm& t, const int32_t (&w)[K], bool active,
+                                             PairOps& p) {
+    bounds<K>(t.hi_src, t.lo_src, w, p.lo, p.hi);
+    p.cut = (t.hi_src | t.lo_src) != 0;
+    p.ne = t.n_op - 2;
+    p.memo = nullptr;
+    p.tag = 0;
+    p.A = p.B = p.E1 = p.E2 = Set{nullptr, 0, nullptr};
+    if (!active) return;
+    p.A = iep_operand<K, G>(c, w, t.op[0]);
+    if (t.n_op < 2) return;
+    p.B = iep_operand<K, G>(c, w, t.op[t.n_op - 1]);
+    if (t.n_op > 2) p.E1 = iep_operand<K, G>(c, w, t.op[1]);
+    if (t.n_op > 3) p.E2 = iep_operand<K, G>(c, w, t.op[2]);
+    if (t.memo) {
+        const int32_t a = pick<K>(w, t.op[0]);
+        p.memo = iep_memo_word<G>(c, a, pick<K>(w, t.op[1]));
+        p.tag = 0x80000000u | (uint32_t)(a + 1);
+    }
+}
+
+// Terms of the sum over partitions from the sizes cnt[(M - 1) * kBlock].
+template <int N>
+__device__ __forceinline__ unsigned __int128 iep_combine(const uint32_t* cnt) {
     typedef unsigned __int128 u128;
-    auto P = [&](int a) { return (u128)cnt[a]; };
+    auto P = [&](int a) { return (u128)cnt[(a - 1) * kBlock]; };
     if constexpr (N == 2) {
         return P(1) * P(2) - P(3);
     } else if constexpr (N == 3) {
@@ -726,21 +771,26 @@ __device__ __forceinline__ unsigned __int128 iep_combine(const GpPlanDesc& d, co
     }
 }
 
-template <int K, int G, int MODE, int N, bool GRP>
-__device__ __forceinline__ unsigned __int128 iep_value(const GpPlanDesc& d, const Ctx<G>& c,
-                                                       const int32_t (&v)[K]) {
+// The inclusion-exclusion value of every active lane's binding w (outer
+// levels 0 .. K-N-1). Called by all lanes of the group together.
+template <int K, int G, int MODE, int N>
+__device__ __forceinline__ unsigned __int128 iep_value(const GpPlanDesc& d, const Ctx<G>& c, const int32_t (&w)[K],
+                                                       bool active) {
     static_assert(N >= 2 && N <= kIepMaxN && N <= K - 2, "IEP inner levels");
-    uint64_t bytes = 0;
-    const unsigned __int128 r =
-        iep_combine<K, G, MODE, N, GRP>(d, c, v, bytes, std::make_integer_sequence<int, (1 << N) - 1>{});
-    if constexpr (MODE == MODE_ACCOUNT) {
-        if constexpr (GRP) {
-            if (c.g.gl == 0) *c.bytes += bytes;
-        } else {
-            *c.bytes += bytes;
+#pragma unroll 1
+    for (int m = 0; m < (1 << N) - 1; ++m) {
+        const GpIepTerm& t = d.it[m];
+        if (t.alias >= 0) {
+            c.cnt[m * kBlock] = c.cnt[t.alias * kBlock];
+            continue;
         }
+        PairOps p;
+        iep_operands<K, G>(c, t, w, active, p);
+        uint32_t r = pair_count<G, MODE>(c, p, active);
+        if (active && t.inj) r -= iep_images<K, G, MODE, K - N>(d, c, t, t.inj, w, p.lo, p.hi);
+        c.cnt[m * kBlock] = r;
     }
-    return r;
+    return iep_combine<N>(c.cnt);
 }
 
 // The last two enumerated levels flattened into one load-balanced batch
@@ -940,94 +990,152 @@ __device__ bool coop_bits_leaf(const GpPlanDesc& d, const Ctx<G>& c, const int32
 }
 
 // The IEP leaf at the last outer level L (inner levels L+1 .. K-1): every
-// candidate x of level L adds its inclusion-exclusion value. Lanes take
-// different candidates when no build runs after level L is bound; otherwise
-// the group binds one candidate at a time, runs the builds and computes the
-// value together.
-// A lane's walk for the IEP value of its own binding: the longest of its
-// unbuilt inner sets' shorter operands (the single-set counts walk them; the
-// intersections walk no more). Lanes whose walk exceeds kIepLaneWork leave
-// their binding to the whole group (iep_group_pass), so one hub binding does
-// not hold a wavefront's other lanes idle for thousands of steps.
-constexpr int32_t kIepLaneWork = 128;
-
-template <int K, int N, int G>
-__device__ __forceinline__ int64_t iep_lane_work_g(const GpPlanDesc& d, const Ctx<G>& c, const int32_t (&w)[K]) {
-    constexpr int F = K - N;
-    int64_t work = 0;
-#pragma unroll
-    for (int j = 0; j < N; ++j) {
-        const GpLevel& lv = d.lv[F + j];
-        if (lv.last_list < 0) continue;
-        const int32_t a = pick<K>(w, lv.last_list);
-        const int64_t na = c.row_ptr[a + 1] - c.row_ptr[a];
-        int64_t np;
-        if (lv.pre_buf >= 0) {
-            np = c.lens[lv.pre_buf];
-        } else {
-            const int32_t b = pick<K>(w, lv.pre_list);
-            np = c.row_ptr[b + 1] - c.row_ptr[b];
-        }
-        work = max(work, min(na, np));
-    }
-    return work;
-}
-
-// The bindings of the lanes flagged in `m` (a group ballot; x is each lane's
-// level-L vertex), one at a time, each by the whole group.
+// candidate x of level L adds its inclusion-exclusion value, lanes taking
+// different candidates. S: this task's candidates (every st-th), Sf: all of
+// them. No build runs after level L is bound: an inner set whose last parent
+// is level L is left unbuilt.
+//
+// Two inner levels, one of whose sets (term b) does not depend on x while the
+// other's (term a) does (d.iep_sum): the sum over x of Pa(x) Pb(x) - P3(x) is
+// taken apart. Pb is one number less [x in S_b]. P3(x) counts the y of
+// Y = S_b & (S_a's other operands) adjacent to x, so its sum over x is the
+// sum over y in Y of the candidates adjacent to y: |Y| pair sizes, kept in the
+// memo where the candidates are a whole list, in place of a walk of Y or N(x)
+// for each of the far more numerous x. A split task takes its slice of Y as it
+// takes its slice of x: partial totals may be negative, and are exact mod
+// 2^128.
 template <int K, int L, int G, int MODE>
-__device__ __forceinline__ void iep_group_pass(const GpPlanDesc& d, const Ctx<G>& c, const int32_t (&v)[K],
-                                               uint64_t m, int32_t x, uint64_t& acc, uint64_t& carry) {
-    constexpr int N = K - 1 - L;
-    while (m) {
-        const int src = __builtin_ctzll(m);
-        m &= m - 1;
+__device__ __forceinline__ void iep_pair_sum(const GpPlanDesc& d, const Ctx<G>& c, const int32_t (&v)[K], Set S,
+                                             int32_t st, Set Sf, uint32_t inj_l, uint64_t& acc, uint64_t& carry) {
+    const GpIepTerm& ta = d.it[d.iep_sum - 1];
+    const GpIepTerm& tb = d.it[2 - d.iep_sum];
+    const GpIepTerm& t3 = d.it[2];
+    int32_t lo, hi;
+    // Pb but for x
+    bounds<K>(tb.hi_src, tb.lo_src, v, lo, hi);
+    Set Sb = tb.op[0] >= 0 ? c.nbr_u(pick<K>(v, tb.op[0])) : c.buf_u(-1 - tb.op[0]);
+    if constexpr (MODE == MODE_ACCOUNT)
+        if (c.g.gl == 0) *c.bytes += cut_bytes(Sb, lo, hi);
+    Sb = trim_u<G>(Sb, lo, hi);
+    const uint64_t pb = (uint64_t)Sb.n - iep_images<K, G, MODE, L>(d, c, tb, tb.inj, v, lo, hi);
+    // Y: the first of term 3's other operands, tested in the second
+    int32_t ylo, yhi;
+    bounds<K>(t3.hi_src, t3.lo_src, v, ylo, yhi);
+    Set Y = t3.op[0] >= 0 ? c.nbr_u(pick<K>(v, t3.op[0])) : c.buf_u(-1 - t3.op[0]);
+    Set E{nullptr, 0, nullptr};
+    if (t3.n_op > 2) {
+        E = t3.op[1] >= 0 ? c.nbr_u(pick<K>(v, t3.op[1])) : c.buf_u(-1 - t3.op[1]);
+        if (E.n < Y.n) {
+            const Set t = Y;
+            Y = E;
+            E = t;
+        }
+    }
+    if constexpr (MODE == MODE_ACCOUNT)
+        if (c.g.gl == 0) *c.bytes += cut_bytes(Y, ylo, yhi);
+    Y = trim_u<G>(Y, ylo, yhi);
+    if constexpr (L == 2) {
+        if (c.sJ > 1) {
+            Y.n = Y.n > c.sj ? (Y.n - c.sj + c.sJ - 1) / c.sJ : 0;
+            Y.p += c.sj;
+        }
+    }
+    const GpLevel& lv = d.lv[L];
+    const bool whole = lv.list >= 0 && (lv.hi_src | lv.lo_src) == 0;
+    const int32_t a = whole ? pick<K>(v, lv.list) : 0;
+    int32_t slo, shi;
+    bounds<K>(lv.hi_src, lv.lo_src, v, slo, shi);
+    // the candidates x, then the y: one loop, so one copy of the walk
+    const int32_t nx = S.n, ny = Y.n;
+    const int32_t xbatches = (nx + G - 1) / G, batches = xbatches + (ny + G - 1) / G;
+#pragma unroll 1
+    for (int32_t bt = 0; bt < batches; ++bt) {
+        if (c.expired()) break;
+        const bool is_x = bt < xbatches;
+        const int32_t i = (is_x ? bt : bt - xbatches) * G + c.g.gl;
+        int32_t z = 0;
+        bool active = i < (is_x ? nx : ny);
+        if (active) z = (is_x ? S.p : Y.p)[(int64_t)i * st];
         int32_t w[K];
 #pragma unroll
         for (int j = 0; j < K; ++j) w[j] = v[j];
-        w[L] = uni<G>(c.g.bcast(x, src));
-        const unsigned __int128 val = iep_value<K, G, MODE, N, true>(d, c, w);
-        if (c.g.gl == 0) add_count128(acc, carry, (uint64_t)val, (uint64_t)(val >> 64));
+        w[L] = z;
+        PairOps p;
+        if (is_x) {
+            active = active && !inj_hit<K>(inj_l, v, z);
+            iep_operands<K, G>(c, ta, w, active, p);
+        } else {
+            if constexpr (MODE == MODE_ACCOUNT)
+                if (active) *c.bytes += 4 + (t3.n_op > 2 ? test_bytes(E) : 0);
+            active = active && !inj_hit<K>(t3.inj & ((1u << L) - 1), v, z) && (t3.n_op <= 2 || member(E, z));
+            p.A = Sf;
+            p.B = p.E1 = p.E2 = Set{nullptr, 0, nullptr};
+            p.ne = 0;
+            // Sf is cut, but its bitmap is the whole list's: N(z) must be cut too
+            p.cut = (lv.hi_src | lv.lo_src) != 0;
+            p.lo = slo;
+            p.hi = shi;
+            p.memo = nullptr;
+            p.tag = 0x80000000u | (uint32_t)(a + 1);
+            if (active) {
+                p.B = c.nbr(z);
+                if (whole) p.memo = iep_memo_word<G>(c, a, z);
+            }
+        }
+        uint64_t q = pair_count<G, MODE>(c, p, active);
+        if (!active) continue;
+        if (is_x) {
+            if (ta.inj) q -= iep_images<K, G, MODE, L + 1>(d, c, ta, ta.inj, w, p.lo, p.hi);
+            uint64_t b = pb;
+            if ((tb.inj >> L) & 1u) b -= iep_images<K, G, MODE, L + 1>(d, c, tb, 1u << L, w, lo, hi);
+            const unsigned __int128 val = (unsigned __int128)q * b;
+            add_count128(acc, carry, (uint64_t)val, (uint64_t)(val >> 64));
+        } else {
+            // earlier images are no candidates
+            if (inj_l) {
+#pragma unroll
+                for (int o = 0; o < L; ++o) {
+                    if (!((inj_l >> o) & 1u)) continue;
+                    const int32_t u = v[o];
+                    bool in = u >= slo && u < shi && u != z;
+                    uint32_t need = lv.parents & ~(uint32_t)d.adj[o];
+                    while (need) {
+                        const int q2 = __builtin_ctz(need);
+                        need &= need - 1;
+                        if (in) in = adjacent<G, MODE>(c, u, pick<K>(v, q2));
+                    }
+                    if (in) q -= adjacent<G, MODE>(c, u, z) ? 1u : 0u;
+                }
+            }
+            carry -= acc < q ? 1u : 0u;
+            acc -= q;
+        }
     }
 }
 
 template <int K, int L, int G, int MODE>
-__device__ void iep_level(const GpPlanDesc& d, const Ctx<G>& c, int32_t (&v)[K], Set S, int32_t st,
+__device__ void iep_level(const GpPlanDesc& d, const Ctx<G>& c, int32_t (&v)[K], Set S, int32_t st, Set Sf,
                           uint32_t inj_l, uint64_t& acc, uint64_t& carry) {
     constexpr int N = K - 1 - L;
-    if (d.build_begin[L] == d.build_end[L]) {
-        for (int32_t base = 0; base < S.n; base += G) {
-            if (c.expired()) break;
-            const int32_t i = base + c.g.gl;
-            int32_t x = 0;
-            bool longw = false;
-            if (i < S.n) {
-                x = S.p[(int64_t)i * st];
-                if (!inj_hit<K>(inj_l, v, x)) {
-                    int32_t w[K];
+    if constexpr (N == 2) {
+        if (d.iep_sum) {
+            iep_pair_sum<K, L, G, MODE>(d, c, v, S, st, Sf, inj_l, acc, carry);
+            return;
+        }
+    }
+    for (int32_t base = 0; base < S.n; base += G) {
+        if (c.expired()) break;
+        const int32_t i = base + c.g.gl;
+        int32_t w[K];
 #pragma unroll
-                    for (int j = 0; j < K; ++j) w[j] = v[j];
-                    w[L] = x;
-                    if (iep_lane_work_g<K, N, G>(d, c, w) > kIepLaneWork) {
-                        longw = true;
-                    } else {
-                        const unsigned __int128 val = iep_value<K, G, MODE, N, false>(d, c, w);
-                        add_count128(acc, carry, (uint64_t)val, (uint64_t)(val >> 64));
-                    }
-                }
-            }
-            iep_group_pass<K, L, G, MODE>(d, c, v, c.g.ballot(longw), x, acc, carry);
+        for (int j = 0; j < K; ++j) w[j] = v[j];
+        bool active = false;
+        if (i < S.n) {
+            w[L] = S.p[(int64_t)i * st];
+            active = !inj_hit<K>(inj_l, v, w[L]);
         }
-    } else {
-        for (int32_t t = 0; t < S.n; ++t) {
-            if (c.expired()) break;
-            const int32_t x = uni<G>(S.p[(int64_t)t * st]);
-            if (inj_hit<K>(inj_l, v, x)) continue;
-            v[L] = x;
-            run_builds<K, G, MODE>(d, c, L, v);
-            const unsigned __int128 val = iep_value<K, G, MODE, N, true>(d, c, v);
-            if (c.g.gl == 0) add_count128(acc, carry, (uint64_t)val, (uint64_t)(val >> 64));
-        }
+        const unsigned __int128 val = iep_value<K, G, MODE, N>(d, c, w, active);
+        if (active) add_count128(acc, carry, (uint64_t)val, (uint64_t)(val >> 64));
     }
 }
 
@@ -1048,6 +1156,7 @@ __device__ void search(const GpPlanDesc& d, const Ctx<G>& c, int32_t (&v)[K], ui
             if (c.g.gl == 0) *c.bytes += cut_bytes(S, lo, hi);
         S = trim_u<G>(S, lo, hi);
         // a split task binds only its slice of the level-2 candidates
+        const Set Sf = S;
         int32_t st = 1;
         if constexpr (L == 2) {
             if (c.sJ > 1) {
@@ -1060,7 +1169,7 @@ __device__ void search(const GpPlanDesc& d, const Ctx<G>& c, int32_t (&v)[K], ui
             if (c.g.gl == 0) *c.bytes += 4ull * (uint64_t)S.n;
         if constexpr (IEP > 0 && L == K - 1 - IEP) {
             // the last outer level: the inner ones are counted, not enumerated
-            iep_level<K, L, G, MODE>(d, c, v, S, st, lv.inj, acc, carry);
+            iep_level<K, L, G, MODE>(d, c, v, S, st, Sf, lv.inj, acc, carry);
             return;
         }
         if constexpr (L == K - 2) {
@@ -1127,71 +1236,26 @@ __device__ __forceinline__ void run_tasks(const GpPlanDesc& d, Ctx<G>& c, const 
                                           unsigned long long* per_root) {
     constexpr bool PER_ROOT = MODE == MODE_PER_ROOT;
     if constexpr (IEP > 0 && IEP == K - 2) {
-        {
-            // the root is the last outer level
-            if (d.build_begin[1] == d.build_end[1]) {
-                for (int64_t base = t0; base < t1; base += G) {
-                    const int64_t r = base + c.g.gl;
-                    int2 e = make_int2(0, 0);
-                    bool longw = false;
-                    if (r < t1) {
-                        e = ts.roots[ts.offset + r * ts.stride];
-                        if constexpr (MODE == MODE_ACCOUNT) *c.bytes += 8;
-                        int32_t w[K];
+        // the root is the last outer level: lanes take different roots
+        for (int64_t base = t0; base < t1; base += G) {
+            const int64_t r = base + c.g.gl;
+            int32_t w[K];
 #pragma unroll
-                        for (int j = 0; j < K; ++j) w[j] = 0;
-                        w[0] = e.x;
-                        w[1] = e.y;
-                        if (iep_lane_work_g<K, K - 2, G>(d, c, w) > kIepLaneWork) {
-                            longw = true;
-                        } else {
-                            const unsigned __int128 val = iep_value<K, G, MODE, K - 2, false>(d, c, w);
-                            add_count128(acc, carry, (uint64_t)val, (uint64_t)(val >> 64));
-                            if constexpr (PER_ROOT)
-                                per_root[entry_index(c.row_ptr, c.col, e.x, e.y)] = (unsigned long long)val;
-                        }
-                    }
-                    // roots with long inner walks: the whole group, one at a time
-                    uint64_t m = c.g.ballot(longw);
-                    while (m) {
-                        const int src = __builtin_ctzll(m);
-                        m &= m - 1;
-                        int32_t w[K];
-#pragma unroll
-                        for (int j = 0; j < K; ++j) w[j] = 0;
-                        w[0] = uni<G>(c.g.bcast(e.x, src));
-                        w[1] = uni<G>(c.g.bcast(e.y, src));
-                        const unsigned __int128 val = iep_value<K, G, MODE, K - 2, true>(d, c, w);
-                        if (c.g.gl == 0) {
-                            add_count128(acc, carry, (uint64_t)val, (uint64_t)(val >> 64));
-                            if constexpr (PER_ROOT)
-                                per_root[entry_index(c.row_ptr, c.col, w[0], w[1])] = (unsigned long long)val;
-                        }
-                    }
-                }
-            } else {
-                for (int64_t r = t0; r < t1; ++r) {
-                    int2 e = ts.roots[ts.offset + r * ts.stride];
-                    e.x = uni<G>(e.x);
-                    e.y = uni<G>(e.y);
-                    if constexpr (MODE == MODE_ACCOUNT)
-                        if (c.g.gl == 0) *c.bytes += 8;
-                    int32_t v[K];
-#pragma unroll
-                    for (int j = 0; j < K; ++j) v[j] = 0;
-                    v[0] = e.x;
-                    v[1] = e.y;
-                    run_builds<K, G, MODE>(d, c, 1, v);
-                    const unsigned __int128 val = iep_value<K, G, MODE, K - 2, true>(d, c, v);
-                    if (c.g.gl == 0) {
-                        add_count128(acc, carry, (uint64_t)val, (uint64_t)(val >> 64));
-                        if constexpr (PER_ROOT)
-                            per_root[entry_index(c.row_ptr, c.col, e.x, e.y)] = (unsigned long long)val;
-                    }
-                }
+            for (int j = 0; j < K; ++j) w[j] = 0;
+            const bool active = r < t1;
+            if (active) {
+                const int2 e = ts.roots[ts.offset + r * ts.stride];
+                if constexpr (MODE == MODE_ACCOUNT) *c.bytes += 8;
+                w[0] = e.x;
+                w[1] = e.y;
             }
-            return;
+            const unsigned __int128 val = iep_value<K, G, MODE, K - 2>(d, c, w, active);
+            if (active) {
+                add_count128(acc, carry, (uint64_t)val, (uint64_t)(val >> 64));
+                if constexpr (PER_ROOT) per_root[entry_index(c.row_ptr, c.col, w[0], w[1])] = (unsigned long long)val;
+            }
         }
+        return;
     }
     if constexpr (K <= 3 && LEAF != 2) {
         // lanes take different roots
@@ -1349,7 +1413,7 @@ __device__ __forceinline__ bool grab_tasks(const Group<G>& grp, unsigned long lo
 }
 
 constexpr int occupancy_target(int K, int G, int LEAF, int IEP = 0) {
-    return IEP >= 3 ? (IEP == 3 ? 5 : 4)
+    return IEP > 0 ? (IEP == 2 ? 6 : 5)
            : K > 6  ? 1
            : K == 6 ? (G == 64 ? 6 : 5)
                     : (G == 64 && (LEAF == 1 || LEAF == 4) ? 8 : 6);
@@ -1378,6 +1442,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(occupanc
     c.memo = a.memo ? (IEP > 0 ? a.memo : a.memo + group_id * (int64_t)a.n_hubs) : nullptr;
     c.tag = 0;
     c.memo_log2 = a.memo_ways_log2;
+    __shared__ uint32_t s_cnt[IEP > 0 ? ((1 << IEP) - 1) * kBlock : 1];
+    c.cnt = &s_cnt[IEP > 0 ? threadIdx.x : 0];
     const uint64_t t_begin = a.busy ? wall_clock64() : 0;
     c.deadline = a.busy && a.budget_ticks ? t_begin + a.budget_ticks : 0;
     uint64_t chunk_max = 0;

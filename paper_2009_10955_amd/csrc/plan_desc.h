@@ -54,6 +54,21 @@ struct GpLevel {
     int8_t pad[3];
 };
 
+// One nonempty subset M of the IEP inner levels: how |∩_{j in M} S_j| is
+// counted (bit j of M: inner level k - iep + j).
+struct GpIepTerm {
+    int8_t op[4];    // operands: list of outer level l as l, buffer slot s as -1 - s;
+                     // together they cover the parents; the last outer level's list comes last
+    uint8_t n_op;
+    int8_t alias;    // index of an earlier term with the same set (then nothing else is set), or -1
+    uint8_t pm;      // parents (outer levels)
+    uint8_t hi_src;  // cut: values < v_j for j in mask
+    uint8_t lo_src;  // values > v_j
+    uint8_t inj;     // outer levels whose images may lie in the set and are not counted
+    uint8_t memo;    // two lists, no cut: a size that depends on their two vertices alone
+    uint8_t pad;
+};
+
 struct GpPlanDesc {
     int32_t k;
     int32_t root_cut;  // 0: every directed edge, 1: only v1 < v0, 2: only v1 > v0
@@ -67,6 +82,11 @@ struct GpPlanDesc {
     // embedding.
     int32_t iep;
     int32_t iep_div;
+    // iep == 2: 1 or 2 when only the first or only the second inner level's set
+    // depends on the last outer level, and no cut does; else 0
+    int32_t iep_sum;
+    GpIepTerm it[(1 << GP_IEP_MAX_INNER) - 1];  // term M - 1 of subset M
+    uint8_t adj[GP_DESC_MAX_K];                 // levels adjacent in the pattern (bitmask)
     GpLevel lv[GP_DESC_MAX_K];
     GpBuild b[GP_DESC_MAX_BUILDS];
     uint8_t build_begin[GP_DESC_MAX_K];  // builds with h == level are b[begin, end)

@@ -615,6 +615,80 @@ int compile_plan(const Pattern& p, const Perm& order, Rel r, GpPlanDesc* out, Re
     }
     d.iep = iep ? iep_n : 0;
     d.iep_div = iep ? iep_div : 0;
+    for (int i = 0; i < k; ++i)
+        for (int j = 0; j < i; ++j)
+            if (par[i] & (1u << j)) {
+                d.adj[i] |= uint8_t(1u << j);
+                d.adj[j] |= uint8_t(1u << i);
+            }
+    if (iep) {
+        const unsigned outer = (1u << first_inner) - 1;
+        const int last = first_inner - 1;
+        for (int m = 1; m < (1 << iep_n); ++m) {
+            GpIepTerm& t = d.it[m - 1];
+            unsigned pm = 0, h = 0, l = 0;
+            std::vector<std::pair<int, unsigned>> ops;  // operand, the parents it covers
+            auto add = [&](int op, unsigned cover) {
+                for (auto& o : ops)
+                    if (o.first == op) return;
+                ops.push_back({op, cover});
+            };
+            for (int j = 0; j < iep_n; ++j) {
+                if (!((m >> j) & 1)) continue;
+                const GpLevel& L = d.lv[first_inner + j];
+                pm |= L.parents;
+                h |= L.hi_src;
+                l |= L.lo_src;
+                if (L.last_list >= 0) {
+                    if (L.pre_buf >= 0) add(-1 - L.pre_buf, slots[L.pre_buf].first.q);
+                    else add(L.pre_list, 1u << L.pre_list);
+                    add(L.last_list, 1u << L.last_list);
+                } else if (L.list >= 0) {
+                    add(L.list, 1u << L.list);
+                } else {
+                    add(-1 - L.buf, slots[L.buf].first.q);
+                }
+            }
+            t.alias = -1;
+            for (int e = 1; e < m && t.alias < 0; ++e) {
+                const GpIepTerm& u = d.it[e - 1];
+                if (u.alias < 0 && u.pm == pm && u.hi_src == h && u.lo_src == l) t.alias = int8_t(e - 1);
+            }
+            if (t.alias >= 0) continue;
+            // drop operands whose parents the others cover: those that cover
+            // least first (single lists before built sets)
+            std::stable_sort(ops.begin(), ops.end(), [](const auto& a, const auto& b) {
+                return __builtin_popcount(a.second) < __builtin_popcount(b.second);
+            });
+            for (size_t o = 0; o < ops.size();) {
+                unsigned rest = 0;
+                for (size_t q = 0; q < ops.size(); ++q)
+                    if (q != o) rest |= ops[q].second;
+                if ((ops[o].second & ~rest) == 0 && ops.size() > 1) ops.erase(ops.begin() + o);
+                else ++o;
+            }
+            // the last outer level's list last, the others by level
+            std::stable_sort(ops.begin(), ops.end(), [&](const auto& a, const auto& b) {
+                if ((a.first == last) != (b.first == last)) return b.first == last;
+                return a.second < b.second;
+            });
+            if (ops.size() > 4) return GP_ERR_UNSUPPORTED;
+            t.n_op = uint8_t(ops.size());
+            for (size_t o = 0; o < ops.size(); ++o) t.op[o] = int8_t(ops[o].first);
+            t.pm = uint8_t(pm);
+            t.hi_src = uint8_t(h);
+            t.lo_src = uint8_t(l);
+            t.inj = uint8_t(outer & ~pm & ~h & ~l);
+            t.memo = t.n_op == 2 && t.op[0] >= 0 && t.op[1] >= 0 && (h | l) == 0;
+        }
+        if (iep_n == 2 && d.it[2].alias < 0) {
+            const unsigned lb = 1u << last;
+            const bool a0 = (d.it[0].pm & lb) != 0, a1 = d.it[1].alias < 0 && (d.it[1].pm & lb) != 0;
+            const bool cut = ((d.it[2].hi_src | d.it[2].lo_src) & lb) != 0;
+            if (first_inner > 2 && d.it[1].alias < 0 && a0 != a1 && !cut && d.it[2].n_op <= 3)
+                d.iep_sum = a0 ? 1 : 2;
+        }
+    }
     *out = d;
     return 0;
 }
