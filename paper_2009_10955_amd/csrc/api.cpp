@@ -53,6 +53,15 @@ void free_device_graph(gpint::DeviceGraph& g) {
     g = gpint::DeviceGraph{};
 }
 
+// Frees a graph whose device work has finished.
+void delete_graph(gp_graph* g) {
+    const int dev = g->dg.device;
+    const bool pooled = g->pooled;
+    free_device_graph(g->dg);
+    delete g;
+    if (pooled) gpint::pool_drop_graph(dev);
+}
+
 // Triangle plan: schedule (0,1,2), restrictions id(0) > id(1) > id(2).
 gp_status triangle_desc(GpPlanDesc* d) {
     const int32_t e[6] = {0, 1, 1, 2, 2, 0};
@@ -90,10 +99,23 @@ gp::RestrictionSets cached_restriction_sets(const gp::Pattern& pat, const std::v
 gp_status count_to_host(const gp_graph* g, const GpPlanDesc& d, const gpint::LaunchCfg& cfg,
                         hipStream_t s, unsigned long long* per_root, uint64_t* out,
                         uint64_t* alg_bytes = nullptr) {
-    unsigned long long* res = nullptr;
-    GP_HIP_TRY(hipMallocAsync((void**)&res, 3 * sizeof(unsigned long long), s));
-    gp_status st = gpint::launch_count(g->dg, d, cfg, s, res, per_root, alg_bytes != nullptr);
     unsigned long long h[3] = {0, 0, 0};
+    if (unsigned long long* slot = alg_bytes ? nullptr : g->results.acquire()) {
+        slot[0] = slot[1] = 0;
+        gp_status st = gpint::launch_count(g->dg, d, cfg, s, nullptr, per_root, false, nullptr, nullptr, slot);
+        if (hipStreamSynchronize(s) != hipSuccess && st == GP_OK) st = GP_ERR_HIP;
+        h[0] = slot[0];
+        h[1] = slot[1];
+        g->results.release(slot);
+        if (st != GP_OK) return st;
+        if (h[1] & 2) return GP_ERR_INTERNAL;
+        if (h[1]) return GP_ERR_OVERFLOW;
+        *out = h[0];
+        return GP_OK;
+    }
+    unsigned long long* res = nullptr;
+    GP_HIP_TRY(gpint::pool_malloc((void**)&res, 3 * sizeof(unsigned long long), s));
+    gp_status st = gpint::launch_count(g->dg, d, cfg, s, res, per_root, alg_bytes != nullptr);
     if (st == GP_OK) {
         if (hipMemcpyAsync(h, res, sizeof h, hipMemcpyDeviceToHost, s) != hipSuccess) st = GP_ERR_HIP;
     }
@@ -164,9 +186,11 @@ gp_status gp_load_graph_opts(const int64_t* row_ptr, const int32_t* col, int64_t
         return GP_ERR_HIP;
     }
     g->dg.device = dev;
+    gpint::pool_add_graph(dev);
+    g->pooled = true;
     int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
-        delete g;
+        delete_graph(g);
         return GP_ERR_HIP;
     }
     g->dg.num_cus = cus;
@@ -230,8 +254,7 @@ gp_status gp_load_graph_opts(const int64_t* row_ptr, const int32_t* col, int64_t
     }
     if (st != GP_OK) {
         (void)hipStreamSynchronize(s);
-        free_device_graph(g->dg);
-        delete g;
+        delete_graph(g);
         return st;
     }
     g->dg.stats.load_seconds = now_seconds() - t0;
@@ -266,8 +289,7 @@ void gp_free_graph(gp_graph* g) {
     if (!g) return;
     DeviceGuard dgd(g->dg.device);
     (void)hipDeviceSynchronize();
-    free_device_graph(g->dg);
-    delete g;
+    delete_graph(g);
 }
 
 void gp_plan_opts_default(gp_plan_opts* o) {
@@ -618,7 +640,7 @@ gp_status gp_list(const gp_graph* g, const gp_plan* p, const gp_launch* launch, 
     int32_t order[GP_MAX_K] = {};
     for (int i = 0; i < k; ++i) order[i] = p->order[i];
     unsigned long long* res = nullptr;
-    GP_HIP_TRY(hipMallocAsync((void**)&res, 2 * sizeof(unsigned long long), s));
+    GP_HIP_TRY(gpint::pool_malloc((void**)&res, 2 * sizeof(unsigned long long), s));
     gp_status st = gpint::launch_list(g->dg, p->desc, order, cfg, s, res, out, (int64_t)capacity);
     unsigned long long h[2] = {0, 0};
     if (st == GP_OK && hipMemcpyAsync(h, res, sizeof h, hipMemcpyDeviceToHost, s) != hipSuccess) st = GP_ERR_HIP;

@@ -1,13 +1,45 @@
 // Handle types behind the C ABI, shared by the API and tuner units.
 #pragma once
+#include <mutex>
 #include <vector>
 
 #include "gp.h"
 #include "internal.hpp"
 #include "planner.hpp"
 
+// Pinned words that blocking calls on a graph receive their results in: the
+// last kernel writes them, so no copy is enqueued. One page, allocated on the
+// first call, a slot per call in flight; a call that finds none copies instead.
+struct ResultSlots {
+    static constexpr int kSlots = 64, kWords = 8;
+    std::mutex mu;
+    unsigned long long* page = nullptr;
+    uint64_t used = 0;
+    bool failed = false;
+    unsigned long long* acquire() {
+        std::lock_guard<std::mutex> lk(mu);
+        if (!page && !failed)
+            failed = hipHostMalloc((void**)&page, sizeof(unsigned long long) * kSlots * kWords, hipHostMallocDefault) !=
+                     hipSuccess;
+        if (!page || ~used == 0) return nullptr;
+        const int i = __builtin_ctzll(~used);
+        used |= uint64_t(1) << i;
+        return page + i * kWords;
+    }
+    void release(unsigned long long* p) {
+        if (!p) return;
+        std::lock_guard<std::mutex> lk(mu);
+        used &= ~(uint64_t(1) << ((p - page) / kWords));
+    }
+    ~ResultSlots() {
+        if (page) (void)hipHostFree(page);
+    }
+};
+
 struct gp_graph {
     gpint::DeviceGraph dg;
+    mutable ResultSlots results;
+    bool pooled = false;  // counted by pool_add_graph
 };
 
 struct gp_plan {

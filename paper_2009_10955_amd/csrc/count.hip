@@ -123,7 +123,7 @@ bool memo_eligible(const GpPlanDesc& d) {
 // set only if the quotient does not fit in 64 bits; check: flag a remainder (a
 // whole count must divide exactly).
 __global__ void finish_count(unsigned long long* result, const unsigned long long* queue, unsigned long long div,
-                             int check) {
+                             int check, unsigned long long* host) {
     uint64_t lo, hi;
     slot_sum128(queue, lo, hi);
     if (threadIdx.x == 0) {
@@ -131,6 +131,10 @@ __global__ void finish_count(unsigned long long* result, const unsigned long lon
         result[0] = lo;
         finish128(&result[0], &result[1], hi, div);
         if (!check) result[1] = (result[1] & ~2ull) | (flags & 2ull);
+        if (host) {
+            host[0] = result[0];
+            host[1] = result[1];
+        }
     }
 }
 
@@ -155,6 +159,62 @@ __global__ void sum_check_kernel(const unsigned long long* vals, int64_t n, unsi
 using namespace gpcount;
 
 namespace gpint {
+
+namespace {
+constexpr int kMaxDevices = 64;
+std::mutex g_pool_mu;
+hipMemPool_t g_pool[kMaxDevices] = {};
+bool g_pool_failed[kMaxDevices] = {};
+int g_pool_graphs[kMaxDevices] = {};
+
+// The device's pool, made on first use; null if it cannot be made.
+hipMemPool_t device_pool(int device) {
+    if (device < 0 || device >= kMaxDevices) return nullptr;
+    std::lock_guard<std::mutex> lk(g_pool_mu);
+    if (!g_pool[device] && !g_pool_failed[device]) {
+        hipMemPoolProps props;
+        std::memset(&props, 0, sizeof props);
+        props.allocType = hipMemAllocationTypePinned;
+        props.location.type = hipMemLocationTypeDevice;
+        props.location.id = device;
+        hipMemPool_t p = nullptr;
+        uint64_t keep = kPoolKeepBytes;
+        if (hipMemPoolCreate(&p, &props) != hipSuccess) p = nullptr;
+        else if (hipMemPoolSetAttribute(p, hipMemPoolAttrReleaseThreshold, &keep) != hipSuccess) {
+            (void)hipMemPoolDestroy(p);
+            p = nullptr;
+        }
+        g_pool[device] = p;
+        g_pool_failed[device] = p == nullptr;
+        if (!p) (void)hipGetLastError();
+    }
+    return g_pool[device];
+}
+}  // namespace
+
+hipError_t pool_malloc(void** p, size_t bytes, hipStream_t stream) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    int dev = -1;
+    hipMemPool_t pool = nullptr;
+    if (hipStreamIsCapturing(stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone &&
+        hipGetDevice(&dev) == hipSuccess)
+        pool = device_pool(dev);
+    if (pool && hipMallocFromPoolAsync(p, bytes, pool, stream) == hipSuccess) return hipSuccess;
+    (void)hipGetLastError();  // the default pool decides
+    return hipMallocAsync(p, bytes, stream);
+}
+
+void pool_add_graph(int device) {
+    if (device < 0 || device >= kMaxDevices) return;
+    std::lock_guard<std::mutex> lk(g_pool_mu);
+    ++g_pool_graphs[device];
+}
+
+void pool_drop_graph(int device) {
+    if (device < 0 || device >= kMaxDevices) return;
+    std::lock_guard<std::mutex> lk(g_pool_mu);
+    if (--g_pool_graphs[device] == 0 && g_pool[device]) (void)hipMemPoolTrimTo(g_pool[device], 0);
+}
 
 LaunchCfg default_launch(const GpPlanDesc& d) {
     LaunchCfg cfg;
@@ -258,7 +318,7 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCfg& cfg,
                        hipStream_t stream, unsigned long long* result_dev,
                        unsigned long long* per_root, bool account, unsigned long long* busy,
-                       const Workspace* ws) {
+                       const Workspace* ws, unsigned long long* result_host) {
     if (cfg.group != 64 && cfg.group != 32 && cfg.group != 16 && cfg.group != 8) return GP_ERR_ARG;
     if (cfg.leaf < 1 || cfg.leaf > 4) return GP_ERR_ARG;
     if (cfg.waves_per_cu < 1 || cfg.waves_per_cu > 32 || cfg.chunk < 1) return GP_ERR_ARG;
@@ -317,27 +377,18 @@ gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCf
     int32_t* scratch = nullptr;
     unsigned long long* queue = nullptr;
     unsigned long long* memo = nullptr;
-    if (ws) {
-        char* base = (char*)ws->base;
-        queue = (unsigned long long*)base;
-        if (scratch_bytes) scratch = (int32_t*)(base + kQueueBytes);
-        if (use_memo) memo = (unsigned long long*)(base + kQueueBytes + align_up(scratch_bytes));
-    } else {
-        GP_HIP_TRY(hipMallocAsync((void**)&queue, kQueueBytes, stream));
-        if (scratch_bytes) {
-            if (hipMallocAsync((void**)&scratch, scratch_bytes, stream) != hipSuccess) {
-                (void)hipFreeAsync(queue, stream);
-                return GP_ERR_NOMEM;
-            }
-        }
-        if (use_memo) {
-            if (hipMallocAsync((void**)&memo, (size_t)memo_words * 8, stream) != hipSuccess) {
-                if (scratch) (void)hipFreeAsync(scratch, stream);
-                (void)hipFreeAsync(queue, stream);
-                return GP_ERR_NOMEM;
-            }
-        }
-    }
+    // one region: the queue, (without result_dev) the result words, the
+    // candidate buffers, the memo
+    if (!result_dev && (ws || !result_host)) return GP_ERR_ARG;
+    const size_t head = kQueueBytes + (result_dev ? 0 : kAlign);
+    char* base = ws ? (char*)ws->base : nullptr;
+    if (!ws && pool_malloc((void**)&base, head + align_up(scratch_bytes) + (use_memo ? (size_t)memo_words * 8 : 0),
+                           stream) != hipSuccess)
+        return GP_ERR_NOMEM;
+    queue = (unsigned long long*)base;
+    if (!result_dev) result_dev = (unsigned long long*)(base + kQueueBytes);
+    if (scratch_bytes) scratch = (int32_t*)(base + head);
+    if (use_memo) memo = (unsigned long long*)(base + head + align_up(scratch_bytes));
     if (use_memo)
         hipLaunchKernelGGL(zero_u64, dim3((unsigned)std::min<int64_t>(4096, (memo_words + 255) / 256)), dim3(256), 0,
                            stream, memo, memo_words);
@@ -375,13 +426,9 @@ gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCf
     // is an estimate, not checked
     const bool whole = cfg.root_stride == 1 && cfg.root_offset == 0 && !(busy && cfg.budget_ms > 0);
     hipLaunchKernelGGL(finish_count, dim3(1), dim3(64), 0, stream, result_dev, queue,
-                       (unsigned long long)(iep ? d.iep_div : 1), whole ? 1 : 0);
+                       (unsigned long long)(iep ? d.iep_div : 1), whole ? 1 : 0, result_host);
     hipError_t le = hipGetLastError();
-    if (!ws) {
-        if (scratch) (void)hipFreeAsync(scratch, stream);
-        if (memo) (void)hipFreeAsync(memo, stream);
-        (void)hipFreeAsync(queue, stream);
-    }
+    if (!ws) (void)hipFreeAsync(base, stream);
     if (le != hipSuccess) return GP_ERR_HIP;
     return GP_OK;
 }
@@ -390,7 +437,7 @@ gp_status check_sum(const uint64_t* values, int64_t n, uint64_t div, hipStream_t
                     uint32_t* flags) {
     if (n < 0 || (n > 0 && !values) || div < 1) return GP_ERR_ARG;
     unsigned long long* w = nullptr;  // the queue's slots, {low word, flags}, then the values
-    GP_HIP_TRY(hipMallocAsync((void**)&w, kQueueBytes + sizeof(unsigned long long) * (2 + (size_t)n), stream));
+    GP_HIP_TRY(pool_malloc((void**)&w, kQueueBytes + sizeof(unsigned long long) * (2 + (size_t)n), stream));
     unsigned long long* res = w + kQueueWords;
     unsigned long long h[2] = {0, 0};
     hipError_t e = hipSuccess;
@@ -400,7 +447,8 @@ gp_status check_sum(const uint64_t* values, int64_t n, uint64_t div, hipStream_t
         e = hipMemcpyAsync(res + 2, values, sizeof(unsigned long long) * (size_t)n, hipMemcpyHostToDevice, stream);
     if (e == hipSuccess) {
         hipLaunchKernelGGL(sum_check_kernel, dim3(4), dim3(kBlock), 0, stream, res + 2, n, w);
-        hipLaunchKernelGGL(finish_count, dim3(1), dim3(64), 0, stream, res, w, (unsigned long long)div, 1);
+        hipLaunchKernelGGL(finish_count, dim3(1), dim3(64), 0, stream, res, w, (unsigned long long)div, 1,
+                           (unsigned long long*)nullptr);
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipMemcpyAsync(h, res, sizeof h, hipMemcpyDeviceToHost, stream);

@@ -71,10 +71,13 @@ int resident_waves_per_cu(const DeviceGraph& g, const GpPlanDesc& d, const Launc
 // flags} (plus bytes when `account`), zeroed by this call on the stream.
 // per_root may be null. Scratch is allocated stream-ordered and released
 // after the kernel, or carved from ws when given (then nothing is allocated).
+// result_host (may be null): host memory the device can write, which also
+// receives {count, flags}; result_dev may then be null.
 gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCfg& cfg,
                        hipStream_t stream, unsigned long long* result_dev,
                        unsigned long long* per_root, bool account = false,
-                       unsigned long long* busy = nullptr, const Workspace* ws = nullptr);
+                       unsigned long long* busy = nullptr, const Workspace* ws = nullptr,
+                       unsigned long long* result_host = nullptr);
 
 // launch_count without allocating: the queue (kNoallocQueueBytes), candidate
 // buffers and memo (kNoallocWorkspaceBytes) come from one static device array per GPU
@@ -181,6 +184,17 @@ gp_status batch_result(const GpPlanDesc& d, const unsigned long long* r4, uint64
 // quotient does not fit in 64 bits, bit 1 if div does not divide the sum.
 gp_status check_sum(const uint64_t* values, int64_t n, uint64_t div, hipStream_t stream, uint64_t* out,
                     uint32_t* flags);
+// Stream-ordered device memory of a call (hipFreeAsync returns it). It comes
+// from a pool of the library's own per GPU that keeps up to kPoolKeepBytes
+// between calls (the default pool keeps nothing: it unmaps at every
+// synchronisation, 0.06 ms a call for small launches and 0.3 ms from 256 MiB
+// on), and gives everything back when the last graph on the GPU is freed.
+// Under stream capture the allocation is hipMallocAsync's graph node.
+constexpr uint64_t kPoolKeepBytes = uint64_t(1) << 30;
+hipError_t pool_malloc(void** p, size_t bytes, hipStream_t stream);
+void pool_add_graph(int device);   // a graph now lives on the device
+void pool_drop_graph(int device);  // it is gone (its work has finished)
+
 // Number of root tasks of a descriptor (its cut picks the root array).
 int64_t root_task_count(const DeviceGraph& g, const GpPlanDesc& d);
 // Tasks of plan d over g with cfg's root splitting (no sampling).

@@ -405,7 +405,7 @@ gp_status launch_list(const DeviceGraph& g, const GpPlanDesc& d, const int32_t* 
     // stream-ordered allocations, all released after the kernels
     std::vector<void*> owned;
     auto get = [&](void** p, size_t bytes) {
-        if (hipMallocAsync(p, std::max<size_t>(bytes, 8), stream) != hipSuccess) return false;
+        if (pool_malloc(p, std::max<size_t>(bytes, 8), stream) != hipSuccess) return false;
         owned.push_back(*p);
         return true;
     };
