@@ -227,8 +227,9 @@ __device__ __forceinline__ int64_t uni64(int64_t x) {
 // Cut a group-uniform set to [lo, hi) (lo, hi group-uniform).
 template <int G>
 __device__ __forceinline__ Set trim_u(Set s, int32_t lo, int32_t hi) {
-    int32_t b = lo > 0 ? uni<G>(lower_bound(s.p, s.n, lo)) : 0;
-    int32_t e = hi < 0x7fffffff ? uni<G>(lower_bound(s.p, s.n, hi)) : s.n;
+    const Group<G> g;
+    int32_t b = lo > 0 ? uni<G>(lower_bound_group<G>(g, s.p, s.n, lo)) : 0;
+    int32_t e = hi < 0x7fffffff ? uni<G>(lower_bound_group<G>(g, s.p, s.n, hi)) : s.n;
     if (e < b) e = b;
     return Set{s.p + b, e - b, s.bits};
 }

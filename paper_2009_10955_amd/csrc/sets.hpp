@@ -180,6 +180,27 @@ struct Group {
     }
 };
 
+// lower_bound by a whole group (the same arguments in every lane): each step
+// loads G elements at once and keeps the G-th part that holds the answer, so a
+// list of n takes log n / log G dependent loads instead of log2 n (two instead
+// of twelve for 4,096 elements and 64 lanes).
+template <int G>
+__device__ __forceinline__ int32_t lower_bound_group(const Group<G>& g, const int32_t* a, int32_t n, int32_t x) {
+    int32_t base = 0;
+    while (n > 0) {
+        // lane i looks at the last element of the i-th part
+        const int32_t step = (n + G - 1) / G;
+        const int32_t i = (g.gl + 1) * step - 1;
+        const bool below = g.gl * step < n && a[base + min(i, n - 1)] < x;
+        const int32_t c = (int32_t)__popcll(g.ballot(below));  // parts that lie wholly below x
+        base += min(c * step, n);
+        if (c * step >= n) break;
+        // the part's last element is not below x
+        n = min(step, n - c * step) - 1;
+    }
+    return base;
+}
+
 // Group-cooperative dst = A ∩ B (both already cut to the wanted range).
 // Returns the number of elements written (the same in every lane).
 template <int G>
