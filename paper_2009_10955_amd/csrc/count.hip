@@ -16,6 +16,7 @@ KernelFn pick_kernel_k5(int group, int leaf, int mode, int iep);
 KernelFn pick_kernel_k6(int group, int leaf, int mode, int iep);
 KernelFn pick_kernel_k7(int group, int leaf, int mode, int iep);
 KernelFn pick_kernel_k8(int group, int leaf, int mode, int iep);
+KernelFn pick_table_kernel(int k, int mode);
 BatchFn batch_kernel_k2_2(int group, int leaf, int iep);
 BatchFn batch_kernel_k3_3(int group, int leaf, int iep);
 BatchFn batch_kernel_k4_4(int group, int leaf, int iep);
@@ -84,10 +85,6 @@ __global__ void zero_u64(unsigned long long* p, int64_t n) {
         p[i] = 0;
 }
 
-// Whether leaf mode 4 may keep its last-level counts per root: the last
-// level is pre & N(v[k-2]) with pre the list of a root level, its cut comes
-// from the root levels only, and every earlier image it must avoid is a
-// parent of level k-2.
 // IEP plans: some inner set is left unbuilt as N(a) & N(x) with a an outer
 // vertex's list and no cut, so its size depends on (a, x) alone and the
 // kernel keeps it in a table shared by the launch's groups
@@ -110,12 +107,36 @@ int iep_memo_log2(int64_t n_hubs, int64_t words_cap) {
     return l;
 }
 
+// Whether leaf mode 4 may keep its last-level counts per root: the last
+// level is pre & N(v[k-2]) with pre the list of a root level, its cut comes
+// from the root levels only, and every earlier image it must avoid is a
+// parent of level k-2.
 bool memo_eligible(const GpPlanDesc& d) {
     if (d.k < 4 || d.iep) return false;
     const GpLevel& ll = d.lv[d.k - 1];
     if (ll.last_list != d.k - 2 || ll.pre_buf >= 0 || ll.pre_list < 0 || ll.pre_list > 1) return false;
     if ((ll.hi_src | ll.lo_src) & ~3u) return false;
     return (ll.inj & ~(uint32_t)d.lv[d.k - 2].parents) == 0;
+}
+
+// Whether a count of d over g runs on the table kernel (count_table.hip):
+// every plan whose last level is such a table, whole counts and samples alike,
+// while its sizes fit 16 bits. Not with builds at the root level, which each of
+// the block's 16 wavefronts would repeat, and not per root. R-MAT 17 5-cycle
+// (64 lanes, split 4 ways): 477 ms in leaf mode 4 with a memo, 35 with the
+// table; 4-cycle on G(1000, 0.01), a whole call: 109 us without, 76 with it.
+bool table_rule(const gpint::DeviceGraph& g, const GpPlanDesc& d, int mode) {
+    return mode != MODE_PER_ROOT && memo_eligible(d) && d.build_begin[1] == d.build_end[1] && g.max_deg < 65536;
+}
+
+// Its launch: two blocks of 16 wavefronts per CU (64 KB of LDS each), and up to
+// 16 roots per grab, which share a hub endpoint and so a table.
+int64_t table_blocks(const gpint::DeviceGraph& g, int waves_per_cu, int64_t n_roots) {
+    const int64_t most = (int64_t)g.num_cus * (waves_per_cu >= 2 * (kTabBlock / 64) ? 2 : 1);
+    return std::max<int64_t>(1, std::min(most, n_roots));
+}
+int32_t table_chunk(int64_t blocks, int64_t n_roots) {
+    return (int32_t)std::max<int64_t>(1, std::min<int64_t>(16, n_roots / (blocks * 8)));
 }
 
 // The count's last step (one wavefront): the sum of the queue's 128-bit totals
@@ -231,6 +252,7 @@ LaunchCfg default_launch(const GpPlanDesc& d) {
 }
 
 int resident_waves_per_cu(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCfg& cfg) {
+    if (table_rule(g, d, MODE_PLAIN)) return cfg.waves_per_cu >= 2 * (kTabBlock / 64) ? 2 * (kTabBlock / 64) : kTabBlock / 64;
     const bool iep = d.iep != 0;
     const int group = iep ? (cfg.group >= 64 ? 64 : 32) : cfg.group;
     KernelFn fn = pick_kernel(d.k, group, cfg.leaf, MODE_PLAIN, d.iep);
@@ -325,7 +347,8 @@ gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCf
     const int mode = account ? MODE_ACCOUNT : (per_root ? MODE_PER_ROOT : MODE_PLAIN);
     const bool iep = d.iep != 0;
     const int group = iep ? (cfg.group >= 64 ? 64 : 32) : cfg.group;  // IEP kernels: 64 or 32 lanes
-    KernelFn fn = pick_kernel(d.k, group, cfg.leaf, mode, d.iep);
+    const bool table = table_rule(g, d, mode);
+    KernelFn fn = table ? pick_table_kernel(d.k, mode) : pick_kernel(d.k, group, cfg.leaf, mode, d.iep);
     if (!fn) return GP_ERR_UNSUPPORTED;
 
     int64_t all_roots = 0;
@@ -345,7 +368,13 @@ gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCf
 
     const int waves_per_block = kBlock / 64;
     int64_t blocks = std::max<int64_t>(1, (int64_t)g.num_cus * cfg.waves_per_cu / waves_per_block);
-    const int64_t groups_per_block = kBlock / group;
+    int64_t groups_per_block = kBlock / group;
+    int32_t chunk = cfg.chunk;
+    if (table) {
+        groups_per_block = kTabBlock / 64;
+        blocks = table_blocks(g, cfg.waves_per_cu, n_roots);
+        chunk = table_chunk(blocks, n_roots);
+    }
     const int64_t cap = std::max<int64_t>(1, g.deg2);
     const int64_t per_block = d.nbuf > 0 ? groups_per_block * d.nbuf * cap * 4 : 0;
     // keep scratch within a fixed budget (or the caller's workspace): fewer
@@ -357,9 +386,9 @@ gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCf
         blocks = std::min(blocks, std::max<int64_t>(1, budget / per_block));
     }
     // a grid larger than the number of root tasks only adds idle groups
-    int64_t need = (n_tasks + cfg.chunk - 1) / cfg.chunk;
+    int64_t need = (n_tasks + chunk - 1) / chunk;
     int64_t need_blocks = std::max<int64_t>(1, (need + groups_per_block - 1) / groups_per_block);
-    blocks = std::min(blocks, need_blocks);
+    if (!table) blocks = std::min(blocks, need_blocks);
 
     const size_t scratch_bytes = (size_t)(blocks * per_block);
     // leaf mode 4's per-task memo: one word per hub per group, within 4 GiB
@@ -370,7 +399,7 @@ gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCf
         iep && iep_memo_eligible(d) ? iep_memo_log2(g.n_hubs, std::min(memo_cap, kIepMemoBytes) / 8) : -1;
     const int64_t memo_words = iep ? (iep_log2 >= 0 ? (int64_t)g.n_hubs << iep_log2 : 0)
                                    : blocks * groups_per_block * (int64_t)g.n_hubs;
-    const bool leaf4_memo = cfg.leaf == 4 && mode != MODE_PER_ROOT && !iep && memo_eligible(d) &&
+    const bool leaf4_memo = cfg.leaf == 4 && !table && mode != MODE_PER_ROOT && !iep && memo_eligible(d) &&
                             n_tasks < (int64_t(1) << 31);
     const bool use_memo = (leaf4_memo || iep_log2 >= 0) && g.n_hubs > 0 && memo_words * 8 <= memo_cap;
 
@@ -401,7 +430,8 @@ gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCf
     a.roots = roots;
     a.n_roots = n_roots;
     a.n_tasks = n_tasks;
-    a.n_chunks = (n_tasks + cfg.chunk - 1) / cfg.chunk;
+    a.n_chunks = table ? (n_roots + chunk - 1) / chunk : need;
+    a.tab_n = (int32_t)std::min<int64_t>(g.n, kTabMax);
     a.split_roots = split_roots;
     a.split_ways = split_ways;
     a.budget_ticks = busy && cfg.budget_ms > 0 ? (uint64_t)(cfg.budget_ms * g.wall_khz) : 0;
@@ -417,11 +447,11 @@ gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCf
     a.per_root = per_root;
     a.busy = busy;
     a.memo = memo;
-    a.chunk = cfg.chunk;
+    a.chunk = chunk;
     a.memo_ways_log2 = std::max(iep_log2, 0);
     a.xcd_block = xcd_block_tasks(g, cfg, group);
     if (n_tasks > 0)
-        hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(kBlock), 0, stream, d, a);
+        hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(table ? kTabBlock : kBlock), 0, stream, d, a);
     // a sample's total need not be a multiple of the over-count: its quotient
     // is an estimate, not checked
     const bool whole = cfg.root_stride == 1 && cfg.root_offset == 0 && !(busy && cfg.budget_ms > 0);
@@ -577,7 +607,8 @@ static gp_status batch_layout(const DeviceGraph& g, const GpPlanDesc* descs, con
         // their descriptors are its kernel arguments)
         const int iep_depth = descs[i].iep;
         const int ksize = std::min((int)descs[i].k, 7);  // sizes 7 and 8 share a kernel
-        if (b->runs.empty() || b->runs.back().group != bp.group || b->runs.back().leaf != bp.leaf ||
+        const bool table = whole[i] && table_rule(g, descs[i], MODE_PLAIN);
+        if (b->runs.empty() || table || b->runs.back().table || b->runs.back().group != bp.group || b->runs.back().leaf != bp.leaf ||
             b->runs.back().iep != iep_depth || std::min(b->runs.back().kmin, 7) != ksize ||
             b->runs.back().p1 - b->runs.back().p0 >= kRunMaxPlans || cfgs[i].batch_runs == 2) {
             BatchRun r;
@@ -586,6 +617,7 @@ static gp_status batch_layout(const DeviceGraph& g, const GpPlanDesc* descs, con
             r.leaf = bp.leaf;
             r.iep = iep_depth;
             r.kmin = r.kmax = descs[i].k;
+            r.table = table;
             b->runs.push_back(r);
         }
         b->runs.back().p1 = i + 1;
@@ -593,7 +625,7 @@ static gp_status batch_layout(const DeviceGraph& g, const GpPlanDesc* descs, con
         b->runs.back().kmax = std::max(b->runs.back().kmax, (int)descs[i].k);
         b->runs.back().waves_per_cu = std::max(b->runs.back().waves_per_cu, cfgs[i].waves_per_cu);
         bp.tag_base = 0;
-        if (bp.leaf == 4 && !descs[i].iep && g.n_hubs > 0 && memo_eligible(descs[i]) &&
+        if (bp.leaf == 4 && !table && !descs[i].iep && g.n_hubs > 0 && memo_eligible(descs[i]) &&
             tag_next + n_all < (int64_t(1) << 31) - 1) {  // below the IEP memo's tags
             bp.tag_base = (uint32_t)tag_next - 1;  // tags tag_base + root + 1 >= tag_next
             tag_next += n_all;
@@ -644,7 +676,9 @@ static int64_t batch_blocks(const DeviceGraph& g, int waves_per_cu, int slots_pe
 }
 
 // Group slots (scratch and memo tables) a run's launch addresses.
-static int64_t run_group_slots(const BatchRun& r) { return r.blocks * (kBlock / 64) * (64 / r.group); }
+static int64_t run_group_slots(const BatchRun& r) {
+    return r.table ? r.blocks * (kTabBlock / 64) : r.blocks * (kBlock / 64) * (64 / r.group);
+}
 
 gp_status batch_prepare(const DeviceGraph& g, const GpPlanDesc* descs, const LaunchCfg* cfgs,
                         const int64_t* offsets, const int64_t* counts, int np, int waves_per_cu,
@@ -659,6 +693,13 @@ gp_status batch_prepare(const DeviceGraph& g, const GpPlanDesc* descs, const Lau
     int64_t slots = 0;
     for (BatchRun& r : b.runs) {
         r.blocks = batch_blocks(g, std::min(waves_per_cu, r.waves_per_cu), 64 / r.group, b.nbuf, b.cap, b.use_memo);
+        if (r.table) {
+            // within the scratch budget, as batch_blocks keeps the others
+            r.blocks = table_blocks(g, std::min(waves_per_cu, r.waves_per_cu), std::max<int64_t>(1, r.n_roots));
+            if (b.nbuf > 0)
+                r.blocks = std::max<int64_t>(
+                    1, std::min(r.blocks, (int64_t(16) << 30) / ((kTabBlock / 64) * b.nbuf * b.cap * 4)));
+        }
         slots = std::max(slots, run_group_slots(r));
     }
     b.memo_words = b.use_memo ? slots * (int64_t)g.n_hubs : 0;
@@ -722,15 +763,17 @@ gp_status batch_enqueue(const DeviceGraph& g, const BatchState& st, hipStream_t 
             // the plain counting kernel over the plan's whole task space
             const int p = r.p0;
             const GpPlanDesc& d = st.h_descs[p];
-            KernelFn fn = pick_kernel(d.k, r.group, r.leaf, MODE_PLAIN, d.iep);
+            KernelFn fn = r.table ? pick_table_kernel(d.k, MODE_PLAIN) : pick_kernel(d.k, r.group, r.leaf, MODE_PLAIN, d.iep);
             if (!fn) return GP_ERR_UNSUPPORTED;
+            const int32_t chunk = r.table ? table_chunk(r.blocks, r.n_roots) : r.chunk;
             CountArgs a;
             a.row_ptr = g.row_ptr;
             a.col = g.col;
             a.roots = r.roots;
             a.n_roots = r.n_roots;
             a.n_tasks = r.n_tasks;
-            a.n_chunks = (r.n_tasks + r.chunk - 1) / r.chunk;
+            a.n_chunks = ((r.table ? r.n_roots : r.n_tasks) + chunk - 1) / chunk;
+            a.tab_n = (int32_t)std::min<int64_t>(g.n, kTabMax);
             a.split_roots = r.split_roots;
             a.split_ways = r.split_ways;
             a.budget_ticks = 0;
@@ -752,10 +795,10 @@ gp_status batch_enqueue(const DeviceGraph& g, const BatchState& st, hipStream_t 
                                      : -1;
             a.memo = iep_log2 >= 0 ? st.memo : nullptr;
             a.memo_ways_log2 = std::max(iep_log2, 0);
-            a.chunk = r.chunk;
+            a.chunk = chunk;
             a.xcd_block = 0;
             if (r.n_tasks > 0)
-                hipLaunchKernelGGL(fn, dim3((unsigned)r.blocks), dim3(kBlock), 0, stream, d, a);
+                hipLaunchKernelGGL(fn, dim3((unsigned)r.blocks), dim3(r.table ? kTabBlock : kBlock), 0, stream, d, a);
             continue;
         }
         BatchArgs a;
@@ -827,9 +870,10 @@ gp_status arena_launch(const DeviceGraph& g, BatchArena* ar, const GpPlanDesc* d
     if (b.use_memo) room = std::min(room, ar->slots_cap);
     int64_t slots = 0;
     for (BatchRun& r : b.runs) {
-        const int64_t per_block = (kBlock / 64) * (64 / r.group);
-        r.blocks = batch_blocks(g, std::min(ar->waves_per_cu, r.waves_per_cu), 64 / r.group, b.nbuf, b.cap,
-                                b.use_memo);
+        const int64_t per_block = r.table ? kTabBlock / 64 : (kBlock / 64) * (64 / r.group);
+        r.blocks = r.table ? table_blocks(g, std::min(ar->waves_per_cu, r.waves_per_cu), std::max<int64_t>(1, r.n_roots))
+                           : batch_blocks(g, std::min(ar->waves_per_cu, r.waves_per_cu), 64 / r.group, b.nbuf, b.cap,
+                                          b.use_memo);
         r.blocks = std::max<int64_t>(1, std::min(r.blocks, room / per_block));
         slots = std::max(slots, run_group_slots(r));
     }

@@ -56,6 +56,8 @@ __device__ void run_piece(const BatchArgs& a, const GpPlanDesc& d, const BatchPl
                      : ((a.memo && bp.tag_base) ? a.memo + slot * (int64_t)a.n_hubs : nullptr);
     c.tag = 0;
     c.memo_log2 = max(a.iep_memo_log2, 0);
+    c.tab = nullptr;
+    c.tab_n = 0;
     __shared__ uint32_t s_cnt[IEP > 0 ? ((1 << IEP) - 1) * kBlock : 1];
     c.cnt = &s_cnt[IEP > 0 ? threadIdx.x : 0];
     TaskSpace ts;

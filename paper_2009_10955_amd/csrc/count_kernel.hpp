@@ -56,6 +56,11 @@ using namespace gpdev;
 
 constexpr int kBlock = 256;
 
+// The table kernel's block, and the most vertices its table covers (16-bit
+// counts, 64 KB of LDS: two blocks per CU).
+constexpr int kTabBlock = 1024;
+constexpr int kTabMax = 32768;
+
 // Kernel modes: plain count, per-root counts, or accounting of the bytes the
 // search reads and writes (never timed).
 enum { MODE_PLAIN = 0, MODE_PER_ROOT = 1, MODE_ACCOUNT = 2 };
@@ -127,6 +132,7 @@ struct CountArgs {
     // its blocks in order from its own cursor and then helps the others; 0:
     // one cursor for the device
     int64_t xcd_block;
+    int32_t tab_n;  // table kernel: vertices its table covers
 };
 
 typedef void (*KernelFn)(GpPlanDesc, CountArgs);
@@ -251,6 +257,8 @@ struct Ctx {
     uint32_t tag;              // memo validity tag of the current root
     int32_t memo_log2;         // IEP memo: log2 of its rows
     uint32_t* cnt;             // IEP: this lane's subset sizes in LDS, kBlock words apart
+    const uint16_t* tab;       // leaf mode 5: the block's path table in LDS, of vertices [0, tab_n)
+    int32_t tab_n;
     Group<G> g;
 
     __device__ __forceinline__ bool expired() const {
@@ -260,6 +268,14 @@ struct Ctx {
     __device__ __forceinline__ Set nbr(int32_t v) const {
         int64_t b = row_ptr[v], e = row_ptr[v + 1];
         return Set{col + b, (int32_t)(e - b), v < n_hubs ? hub_bits + (int64_t)v * hub_words : nullptr};
+    }
+    // whether u and v are adjacent: a bit of the higher-degree one's bitmap, else
+    // a search in the shorter list
+    __device__ __forceinline__ bool edge(int32_t u, int32_t v) const {
+        const int32_t h = min(u, v), o = max(u, v);
+        if (h < n_hubs) return (hub_bits[(int64_t)h * hub_words + (o >> 5)] >> (o & 31)) & 1u;
+        const Set s = nbr(o);
+        return contains(s.p, s.n, h);
     }
     __device__ __forceinline__ Set buf(int slot) const {
         return Set{bufs + (int64_t)slot * cap, lens[slot], nullptr};
@@ -580,18 +596,13 @@ __device__ __forceinline__ unsigned long long* iep_memo_word(const Ctx<G>& c, in
     return c.memo + (int64_t)(a & ((int32_t(1) << c.memo_log2) - 1)) * c.n_hubs + x;
 }
 
-// Whether data vertices u and v are adjacent: a bit of the higher-degree one's
-// bitmap, else a search in the shorter list.
 template <int G, int MODE>
 __device__ __forceinline__ bool adjacent(const Ctx<G>& c, int32_t u, int32_t v) {
-    const int32_t h = min(u, v), o = max(u, v);
-    if (h < c.n_hubs) {
-        if constexpr (MODE == MODE_ACCOUNT) *c.bytes += 4;
-        return (c.hub_bits[(int64_t)h * c.hub_words + (o >> 5)] >> (o & 31)) & 1u;
+    if constexpr (MODE == MODE_ACCOUNT) {
+        const int32_t o = max(u, v);
+        *c.bytes += min(u, v) < c.n_hubs ? 4 : probe_bytes((int32_t)(c.row_ptr[o + 1] - c.row_ptr[o]));
     }
-    const Set s = c.nbr(o);
-    if constexpr (MODE == MODE_ACCOUNT) *c.bytes += probe_bytes(s.n);
-    return contains(s.p, s.n, h);
+    return c.edge(u, v);
 }
 
 // What one pair_count call counts: |A & B & E1 & E2 & [lo, hi)|, A and B per
@@ -990,6 +1001,58 @@ __device__ bool coop_bits_leaf(const GpPlanDesc& d, const Ctx<G>& c, const int32
     return true;
 }
 
+// Leaf mode 5 (table_kernel): the last level is N(x) & N(p) cut by root levels,
+// p a root endpoint, so its size is a function of x alone while the root edge
+// stays: the block's table holds it for every vertex below tab_n. The images
+// it must avoid are parents of x, so whether they are in the set depends on
+// the levels above only: one number per call. A lane's element costs one
+// coalesced list load and one LDS load; vertices past the table, the ones of
+// lowest degree, have their lists walked.
+template <int K, int G, int MODE>
+__device__ __forceinline__ void table_leaf(const GpPlanDesc& d, const Ctx<G>& c, const int32_t (&v)[K], Set S,
+                                           int32_t slo, int32_t shi, uint32_t inj_l, uint64_t& acc, uint64_t& carry) {
+    const GpLevel& ll = d.lv[K - 1];
+    const int32_t p = ll.pre_list == 0 ? v[0] : v[1];
+    int32_t lo, hi;
+    bounds<K>(ll.hi_src, ll.lo_src, v, lo, hi);
+    uint32_t corr = 0;
+#pragma unroll
+    for (int j = 0; j < K - 2; ++j)
+        if ((ll.inj >> j) & 1u) {
+            const int32_t y = v[j];
+            if (y >= lo && y < hi) corr += c.edge(y, p) ? 1u : 0u;
+        }
+    corr = (uint32_t)uni<G>((int32_t)corr);
+    // K = 4: level 2 itself, dealt to the block's waves in batches of G
+    const int32_t first = K == 4 ? c.sj * G : 0, step = K == 4 ? c.sJ * G : G;
+    if (S.n > 4 * G || K == 4) {
+        if (slo > 0 || shi < 0x7fffffff) S = trim_u<G>(S, slo, shi);
+        slo = 0;
+        shi = 0x7fffffff;
+    }
+    uint32_t sum = 0, taken = 0;
+    const Set P = c.nbr_u(p);
+    for (int32_t base = first; base < S.n; base += step) {
+        const int32_t i = base + c.g.gl;
+        const int32_t x = i < S.n ? S.p[i] : -1;
+        if constexpr (MODE == MODE_ACCOUNT) *c.bytes += i < S.n ? 4 : 0;
+        if (x >= slo && x < shi && !inj_hit<K>(inj_l, v, x)) {
+            ++taken;
+            if (x < c.tab_n) {
+                sum += c.tab[x];
+            } else {
+                const Set N = c.nbr(x);
+                if constexpr (MODE == MODE_ACCOUNT) *c.bytes += (uint64_t)N.n * (4 + test_bytes(P));
+                auto none = [](int32_t) { return false; };
+                if (P.bits) sum += count_bits_range(N, lo, hi, P.bits, none);
+                else sum += intersect_count_serial(trim(N, lo, hi), trim(P, lo, hi));
+            }
+        }
+    }
+    // |N(x) & N(p)| < 2^16 and a lane takes fewer than 2^16 elements
+    add_count(acc, (uint64_t)sum - (uint64_t)corr * taken, carry);
+}
+
 // The IEP leaf at the last outer level L (inner levels L+1 .. K-1): every
 // candidate x of level L adds its inclusion-exclusion value, lanes taking
 // different candidates. S: this task's candidates (every st-th), Sf: all of
@@ -1153,6 +1216,10 @@ __device__ void search(const GpPlanDesc& d, const Ctx<G>& c, int32_t (&v)[K], ui
         int32_t lo, hi;
         bounds<K>(lv.hi_src, lv.lo_src, v, lo, hi);
         Set S = lv.list >= 0 ? c.nbr_u(pick<K>(v, lv.list)) : c.buf_u(lv.buf);
+        if constexpr (LEAF == 5 && L == K - 2) {
+            table_leaf<K, G, MODE>(d, c, v, S, lo, hi, lv.inj, acc, carry);
+            return;
+        }
         if constexpr (MODE == MODE_ACCOUNT)
             if (c.g.gl == 0) *c.bytes += cut_bytes(S, lo, hi);
         S = trim_u<G>(S, lo, hi);
@@ -1443,6 +1510,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(occupanc
     c.memo = a.memo ? (IEP > 0 ? a.memo : a.memo + group_id * (int64_t)a.n_hubs) : nullptr;
     c.tag = 0;
     c.memo_log2 = a.memo_ways_log2;
+    c.tab = nullptr;
+    c.tab_n = 0;
     __shared__ uint32_t s_cnt[IEP > 0 ? ((1 << IEP) - 1) * kBlock : 1];
     c.cnt = &s_cnt[IEP > 0 ? threadIdx.x : 0];
     const uint64_t t_begin = a.busy ? wall_clock64() : 0;

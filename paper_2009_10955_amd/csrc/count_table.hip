@@ -1,0 +1,173 @@
+// Counting kernel for plans whose last level depends on the root edge and one
+// more vertex only: the last level is N(x) & N(p), x the vertex bound before
+// it and p a root endpoint, cut by root levels (the cycles, and what ends in
+// a cycle through a root endpoint). Its size for every x is then one table
+// per root edge: T[x] = |{y in N(p), lo <= y < hi : x in N(y)}|, the number
+// of two-paths from p to x, filled by walking the lists of N(p).
+//
+// How it maps to the machine:
+//   * a block of 16 wavefronts works on one root edge with the table in its
+//     LDS: 16-bit counts of the kTabMax vertices of highest degree (64 KB, so
+//     two blocks and 32 wavefronts per CU). In the degree-sorted layout these
+//     hold nearly every list entry (95% on R-MAT 17);
+//   * roots come in order of their hub endpoint, the other one ascending. While
+//     p, the hub, stays and the cut only grows with the other endpoint, a root
+//     adds the lists of the y that come in; else the table is filled anew,
+//     which walks N(p)'s lists once where the search walks N(x)'s for every x;
+//   * the wavefronts take different level-2 candidates (k = 4: different
+//     batches of one list) and search on as 64-lane groups (leaf mode 5).
+// The search reads lists in order and looks counts up in LDS: neither the
+// lists of x nor a table of 8-byte words per group in HBM are touched. What bounds
+// it now is reading the lists of the level-2 candidates, from L2: 5-cycle on
+// R-MAT 17 (971,517 edges) 35 ms, against 477 ms in leaf mode 4.
+#include "count_kernel.hpp"
+
+namespace gpcount {
+
+namespace {
+
+// Adds 1 to T[x] for every x < tab_n of the lists of N(p)[b, e), the block's
+// wavefronts taking different lists.
+template <int MODE>
+__device__ __forceinline__ void add_lists(const Ctx<64>& c, const Set& P, int32_t b, int32_t e, int wave, int waves,
+                                          uint32_t* tab) {
+    for (int32_t t = b + wave; t < e; t += waves) {
+        const Set N = c.nbr_u(uni<64>(P.p[t]));
+        if constexpr (MODE == MODE_ACCOUNT)
+            if (c.g.gl == 0) *c.bytes += 4;
+        for (int32_t base = 0; base < N.n; base += 64) {
+            const int32_t i = base + c.g.gl;
+            const int32_t x = i < N.n ? N.p[i] : 0x7fffffff;
+            if constexpr (MODE == MODE_ACCOUNT) *c.bytes += i < N.n ? 4 : 0;
+            // no carry into the neighbouring count: at most max_deg < 2^16 per vertex
+            if (x < c.tab_n) atomicAdd(&tab[x >> 1], 1u << ((x & 1) * 16));
+            if (uni<64>(x) >= c.tab_n) break;  // the lane holding the smallest is past the table
+        }
+    }
+}
+
+template <int K, int MODE>
+__global__ __launch_bounds__(kTabBlock) __attribute__((amdgpu_waves_per_eu(8))) void table_kernel(GpPlanDesc d,
+                                                                                                  CountArgs a) {
+    constexpr int kWaves = kTabBlock / 64;
+    __shared__ __attribute__((aligned(16))) uint32_t s_tab[kTabMax / 2];
+    __shared__ int32_t s_len[kWaves][GP_DESC_MAX_BUILDS];
+    __shared__ int64_t s_chunk;
+    __shared__ int32_t s_cur;
+    Ctx<64> c;
+    const int wave = uni<64>((int)(threadIdx.x / 64));
+    c.row_ptr = a.row_ptr;
+    c.col = a.col;
+    c.cap = a.buf_cap;
+    c.hub_bits = a.hub_bits;
+    c.hub_words = a.hub_words;
+    c.n_hubs = a.n_hubs;
+    c.bufs = a.scratch ? a.scratch + ((int64_t)blockIdx.x * kWaves + wave) * (int64_t)d.nbuf * a.buf_cap : nullptr;
+    c.lens = s_len[wave];
+    uint64_t bytes = 0;
+    c.bytes = &bytes;
+    c.sj = wave;
+    c.sJ = kWaves;
+    c.memo = nullptr;
+    c.tag = 0;
+    c.memo_log2 = 0;
+    c.cnt = nullptr;
+    c.tab = (const uint16_t*)s_tab;
+    c.tab_n = a.tab_n;
+    const uint64_t t_begin = a.busy ? wall_clock64() : 0;
+    c.deadline = a.busy && a.budget_ticks ? t_begin + a.budget_ticks : 0;
+    uint64_t chunk_max = 0;
+    bool stopped = false;
+    uint64_t acc = 0, carry = 0;
+
+    const GpLevel& ll = d.lv[K - 1];
+    int32_t cur_p = -1, cur_lo = 0, cur_hi = 0, cur_pos = 0;
+    if (threadIdx.x == 0) s_cur = (int)(blockIdx.x & (kCursors - 1));
+    __syncthreads();
+    for (;;) {
+        if (wave == 0) {
+            const int64_t q = next_chunk<64>(c.g, a.queue, a.n_chunks, &s_cur);
+            if (c.g.gl == 0) s_chunk = q;
+        }
+        __syncthreads();
+        const int64_t q = uni64<64>(s_chunk);
+        __syncthreads();
+        if (q < 0) break;
+        const uint64_t t_chunk = a.busy ? wall_clock64() : 0;
+        const int64_t r1 = min((q + 1) * a.chunk, a.n_roots);
+        for (int64_t r = q * a.chunk; r < r1; ++r) {
+            const int2 e = a.roots[a.root_offset + r * a.root_stride];
+            if constexpr (MODE == MODE_ACCOUNT) bytes += threadIdx.x == 0 ? 8 : 0;
+            int32_t v[K];
+#pragma unroll
+            for (int j = 0; j < K; ++j) v[j] = 0;
+            v[0] = uni<64>(e.x);
+            v[1] = uni<64>(e.y);
+            const int32_t p = ll.pre_list == 0 ? v[0] : v[1];
+            int32_t lo, hi;
+            bounds<K>(ll.hi_src, ll.lo_src, v, lo, hi);
+            const Set P = c.nbr_u(p);
+            // every wavefront of the block takes the same way here
+            if (p != cur_p || lo != cur_lo || hi < cur_hi) {
+                for (int i = threadIdx.x; i < (a.tab_n + 7) / 8; i += kTabBlock)
+                    reinterpret_cast<uint4*>(s_tab)[i] = make_uint4(0, 0, 0, 0);
+                cur_pos = lo > 0 ? uni<64>(lower_bound_group<64>(c.g, P.p, P.n, lo)) : 0;
+                __syncthreads();
+            }
+            const int32_t end = hi < 0x7fffffff
+                                    ? cur_pos + uni<64>(lower_bound_group<64>(c.g, P.p + cur_pos, P.n - cur_pos, hi))
+                                    : P.n;
+            if (end > cur_pos) add_lists<MODE>(c, P, cur_pos, end, wave, kWaves, s_tab);
+            cur_pos = max(cur_pos, end);
+            cur_p = p;
+            cur_lo = lo;
+            cur_hi = hi;
+            __syncthreads();
+            search<K, 2, 64, 5, MODE, 0>(d, c, v, acc, carry);
+            __syncthreads();
+        }
+        if (a.busy) {
+            const uint64_t now = wall_clock64();
+            chunk_max = max(chunk_max, now - t_chunk);
+            // the whole block stops together
+            const bool late = c.deadline && now > c.deadline;
+            if (__syncthreads_or(late)) {
+                stopped = true;
+                break;
+            }
+        }
+    }
+    uint64_t s = acc, s_hi = carry;
+    wave_sum128(s, s_hi);
+    if constexpr (MODE == MODE_ACCOUNT) bytes = c.g.sum(bytes);
+    if (__lane_id() == 0) {
+        if constexpr (MODE == MODE_ACCOUNT) atomicAdd(&a.result[2], (unsigned long long)bytes);
+        unsigned long long* slot = a.queue + (blockIdx.x & (kSlots - 1)) * kSlotWords;
+        publish128(&slot[SLOT_LO], &slot[SLOT_HI], s, s_hi);
+        if (stopped) atomicOr(&a.result[1], 4ull);
+        if (a.busy) {
+            atomicAdd(&a.busy[0], (unsigned long long)(wall_clock64() - t_begin));
+            atomicAdd(&a.busy[1], 1ull);
+            atomicMax(&a.busy[2], (unsigned long long)chunk_max);
+        }
+    }
+}
+
+}  // namespace
+
+KernelFn pick_table_kernel(int k, int mode) {
+    if (mode != MODE_PLAIN && mode != MODE_ACCOUNT) return nullptr;
+#define GP_TABLE_CASE(KK) \
+    case KK: return mode == MODE_PLAIN ? table_kernel<KK, MODE_PLAIN> : table_kernel<KK, MODE_ACCOUNT>;
+    switch (k) {
+        GP_TABLE_CASE(4)
+        GP_TABLE_CASE(5)
+        GP_TABLE_CASE(6)
+        GP_TABLE_CASE(7)
+        GP_TABLE_CASE(8)
+        default: return nullptr;
+    }
+#undef GP_TABLE_CASE
+}
+
+}  // namespace gpcount

@@ -108,6 +108,7 @@ struct BatchRun {
     // per-plan machinery of the batched kernel only slows down; its task
     // space as that kernel takes it
     bool solo = false;
+    bool table = false;  // solo, by the table kernel
     const int2* roots = nullptr;
     int64_t n_roots = 0, root_offset = 0, root_stride = 1, n_tasks = 0, split_roots = 0;
     int32_t split_ways = 1, chunk = 1;
