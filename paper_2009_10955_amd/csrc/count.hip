@@ -328,6 +328,13 @@ static SplitPlan split_plan(const DeviceGraph& g, const GpPlanDesc& d, const Lau
     const int64_t sampled = pref > offset ? (pref - offset + stride - 1) / stride : 0;
     sp.roots = std::min(n_roots, sampled);
     sp.ways = cfg.split_ways;
+    // where lanes take the level-2 candidates, a way of fewer than a group's
+    // width leaves lanes idle: the 5-vertex patterns with IEP on Chung-Lu (3,000
+    // vertices, 30K edges, largest degree 281) take 1.5-2.2 ms each split 16
+    // ways, 0.3-0.6 split 4 ways
+    if (d.k - (d.iep ? d.iep + 1 : 2) == 2)
+        sp.ways = (int)std::min<int64_t>(sp.ways, std::max<int64_t>(1, g.max_deg / std::max(cfg.group, 1)));
+    if (sp.ways <= 1) sp = SplitPlan{};
     return sp;
 }
 

@@ -130,6 +130,11 @@ void finish(gp_server* S, Query* q, gp_status st) {
     S->cv_done.notify_all();
 }
 
+// Grabs a slice is cut into at least, while its tasks allow (four per resident
+// wavefront): heavy roots come first, and a slice of 8,192 of their tasks taken
+// four at a time keeps a quarter of the wavefronts busy.
+constexpr int64_t kSliceGrabs = 32768;
+
 // Launch shape of every batched launch of the server (its kernels, its task space).
 gpint::LaunchCfg server_launch(const gp_server* S) {
     gpint::LaunchCfg cfg;
@@ -418,6 +423,8 @@ void worker_main(gp_server* S) {
                 cfgs.push_back(lcfg);
                 // lanes take different root edges: a grab fills them
                 if (q->plan->desc.k <= 3 || q->plan->desc.iep == q->plan->desc.k - 2) cfgs.back().chunk = 64;
+                // a slice of fewer tasks than fill the device at the usual grab
+                else cfgs.back().chunk = (int)std::max<int64_t>(1, std::min<int64_t>(lcfg.chunk, c / kSliceGrabs));
                 offs.push_back(q->launched);
                 L.qs.push_back(q);
                 L.slices.push_back(c);
@@ -489,7 +496,8 @@ void worker_main(gp_server* S) {
             const double t_q = std::max(1e-7, (double)r[4 * i + 2] * tick_s / groups);
             const double rate = (double)L.slices[i] / t_q;
             double next = rate * fair;
-            next = std::min(next, 4.0 * (double)L.slices[i] + 1);
+            // the first tasks are the heaviest, so the rate errs low: let it grow fast
+            next = std::min(next, 32.0 * (double)L.slices[i] + 1);
             next = std::max(next, 64.0);
             q->slice = (int64_t)std::min(next, 1e12);
         }
