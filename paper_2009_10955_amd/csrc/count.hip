@@ -119,14 +119,21 @@ bool memo_eligible(const GpPlanDesc& d) {
     return (ll.inj & ~(uint32_t)d.lv[d.k - 2].parents) == 0;
 }
 
-// Whether a count of d over g runs on the table kernel (count_table.hip):
-// every plan whose last level is such a table, whole counts and samples alike,
-// while its sizes fit 16 bits. Not with builds at the root level, which each of
-// the block's 16 wavefronts would repeat, and not per root. R-MAT 17 5-cycle
-// (64 lanes, split 4 ways): 477 ms in leaf mode 4 with a memo, 35 with the
-// table; 4-cycle on G(1000, 0.01), a whole call: 109 us without, 76 with it.
+// Whether a count of d over g runs on the table kernel (count_table.hip): every
+// plan whose last level is N(x) & N(root endpoint) cut by root levels, whole
+// counts and samples alike, while its sizes fit 16 bits. Not with builds at the
+// root level, which each of the block's 16 wavefronts would repeat, and not
+// per root. Without and with the table: R-MAT 17 5-cycle (64 lanes, split 4
+// ways, leaf mode 4 with a memo) 477 and 31 ms; 5-cycle of the cost model's plan on
+// R-MAT (20,000 vertices, 160K edges) 100 and 11.5 ms; 6-cycle on Chung-Lu (3,000
+// vertices, 30K edges) 199 and 24 ms; 4-cycle on G(1000, 0.01), a whole call,
+// 109 and 76 us.
 bool table_rule(const gpint::DeviceGraph& g, const GpPlanDesc& d, int mode) {
-    return mode != MODE_PER_ROOT && memo_eligible(d) && d.build_begin[1] == d.build_end[1] && g.max_deg < 65536;
+    if (mode == MODE_PER_ROOT || d.k < 4 || d.iep || d.build_begin[1] != d.build_end[1] || g.max_deg >= 65536)
+        return false;
+    const GpLevel& ll = d.lv[d.k - 1];
+    return ll.last_list == d.k - 2 && ll.pre_buf < 0 && (ll.pre_list == 0 || ll.pre_list == 1) &&
+           ((ll.hi_src | ll.lo_src) & ~3u) == 0;
 }
 
 // Its launch: two blocks of 16 wavefronts per CU (64 KB of LDS each), and up to

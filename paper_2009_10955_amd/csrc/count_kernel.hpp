@@ -259,6 +259,7 @@ struct Ctx {
     uint32_t* cnt;             // IEP: this lane's subset sizes in LDS, kBlock words apart
     const uint16_t* tab;       // leaf mode 5: the block's path table in LDS, of vertices [0, tab_n)
     int32_t tab_n;
+    int32_t out;               // leaf mode 5: the root endpoint left out of the table, a neighbor of p (-1: none)
     Group<G> g;
 
     __device__ __forceinline__ bool expired() const {
@@ -1003,26 +1004,38 @@ __device__ bool coop_bits_leaf(const GpPlanDesc& d, const Ctx<G>& c, const int32
 
 // Leaf mode 5 (table_kernel): the last level is N(x) & N(p) cut by root levels,
 // p a root endpoint, so its size is a function of x alone while the root edge
-// stays: the block's table holds it for every vertex below tab_n. The images
-// it must avoid are parents of x, so whether they are in the set depends on
-// the levels above only: one number per call. A lane's element costs one
-// coalesced list load and one LDS load; vertices past the table, the ones of
-// lowest degree, have their lists walked.
+// stays: the block's table holds it for every vertex below tab_n. A lane's
+// element costs one coalesced list load and one LDS load; vertices past the
+// table, the ones of lowest degree, have their lists walked. Of the images the
+// last level must avoid, the other root endpoint is left out of the table;
+// those that are parents of x lie in the set or not whatever x is, one
+// number per call (corr); the rest (mask ex) are in the set only of the x
+// adjacent to them, and only if they are in N(p) and the cut at all.
+// Of levels [2, F), the images that the last level must avoid and that lie in
+// N(p) and the cut: as a mask (the root endpoints are not among them).
+template <int K, int G, int F>
+__device__ __forceinline__ uint32_t table_images(const GpLevel& ll, const Ctx<G>& c, const int32_t (&v)[K], int32_t p,
+                                                 int32_t lo, int32_t hi) {
+    uint32_t m = 0;
+#pragma unroll
+    for (int j = 2; j < F; ++j)
+        if ((ll.inj >> j) & 1u) {
+            const int32_t y = v[j];
+            if (y >= lo && y < hi && c.edge(y, p)) m |= 1u << j;
+        }
+    return (uint32_t)uni<G>((int32_t)m);
+}
+
 template <int K, int G, int MODE>
 __device__ __forceinline__ void table_leaf(const GpPlanDesc& d, const Ctx<G>& c, const int32_t (&v)[K], Set S,
-                                           int32_t slo, int32_t shi, uint32_t inj_l, uint64_t& acc, uint64_t& carry) {
+                                           int32_t slo, int32_t shi, uint32_t inj_l, uint32_t images, uint64_t& acc,
+                                           uint64_t& carry) {
+    const uint32_t corr = (uint32_t)__popc(images & d.lv[K - 2].parents);
+    const uint32_t ex = images & ~(uint32_t)d.lv[K - 2].parents;
     const GpLevel& ll = d.lv[K - 1];
     const int32_t p = ll.pre_list == 0 ? v[0] : v[1];
     int32_t lo, hi;
     bounds<K>(ll.hi_src, ll.lo_src, v, lo, hi);
-    uint32_t corr = 0;
-#pragma unroll
-    for (int j = 0; j < K - 2; ++j)
-        if ((ll.inj >> j) & 1u) {
-            const int32_t y = v[j];
-            if (y >= lo && y < hi) corr += c.edge(y, p) ? 1u : 0u;
-        }
-    corr = (uint32_t)uni<G>((int32_t)corr);
     // K = 4: level 2 itself, dealt to the block's waves in batches of G
     const int32_t first = K == 4 ? c.sj * G : 0, step = K == 4 ? c.sJ * G : G;
     if (S.n > 4 * G || K == 4) {
@@ -1031,7 +1044,6 @@ __device__ __forceinline__ void table_leaf(const GpPlanDesc& d, const Ctx<G>& c,
         shi = 0x7fffffff;
     }
     uint32_t sum = 0, taken = 0;
-    const Set P = c.nbr_u(p);
     for (int32_t base = first; base < S.n; base += step) {
         const int32_t i = base + c.g.gl;
         const int32_t x = i < S.n ? S.p[i] : -1;
@@ -1041,16 +1053,61 @@ __device__ __forceinline__ void table_leaf(const GpPlanDesc& d, const Ctx<G>& c,
             if (x < c.tab_n) {
                 sum += c.tab[x];
             } else {
-                const Set N = c.nbr(x);
+                const Set N = c.nbr(x), P = c.nbr(p);
                 if constexpr (MODE == MODE_ACCOUNT) *c.bytes += (uint64_t)N.n * (4 + test_bytes(P));
                 auto none = [](int32_t) { return false; };
                 if (P.bits) sum += count_bits_range(N, lo, hi, P.bits, none);
                 else sum += intersect_count_serial(trim(N, lo, hi), trim(P, lo, hi));
+                if (c.out >= lo && c.out < hi && c.edge(c.out, x)) --sum;
             }
+            for (uint32_t m = ex; m; m &= m - 1) sum -= c.edge(pick<K>(v, __builtin_ctz(m)), x) ? 1u : 0u;
         }
     }
     // |N(x) & N(p)| < 2^16 and a lane takes fewer than 2^16 elements
     add_count(acc, (uint64_t)sum - (uint64_t)corr * taken, carry);
+}
+
+// Level K-3 above a table_leaf over the list of its vertex: the lanes look up
+// 64 candidates' list bounds (and whether the last level must avoid them) at
+// once, so that a candidate costs its list's loads alone.
+template <int K, int G, int MODE>
+__device__ __forceinline__ void table_lists(const GpPlanDesc& d, const Ctx<G>& c, int32_t (&v)[K], Set S, int32_t st,
+                                            uint32_t inj_l, uint64_t& acc, uint64_t& carry) {
+    constexpr int L = K - 3;
+    const GpLevel& l2 = d.lv[K - 2];
+    const GpLevel& ll = d.lv[K - 1];
+    const int32_t p = ll.pre_list == 0 ? v[0] : v[1];
+    int32_t lo, hi;
+    bounds<K>(ll.hi_src, ll.lo_src, v, lo, hi);
+    const uint32_t images = table_images<K, G, L>(ll, c, v, p, lo, hi);
+    const bool avoid = L >= 2 && ((ll.inj >> L) & 1u);
+    for (int32_t base = 0; base < S.n; base += G) {
+        if (c.expired()) break;
+        const int32_t i = base + c.g.gl;
+        int32_t x = 0, n = 0;
+        long long q = 0;
+        uint32_t own = 0;
+        if (i < S.n) {
+            x = S.p[(int64_t)i * st];
+            if (!inj_hit<K>(inj_l, v, x)) {
+                const int64_t b = c.row_ptr[x], e = c.row_ptr[x + 1];
+                q = (long long)(c.col + b);
+                n = (int32_t)(e - b);
+                if (avoid && x >= lo && x < hi) own = c.edge(x, p) ? 1u : 0u;
+            }
+        }
+        uint64_t m = c.g.ballot(n > 0);
+        while (m) {
+            const int src = __builtin_ctzll(m);
+            m &= m - 1;
+            v[L] = uni<G>(c.g.bcast(x, src));
+            const Set N{(const int32_t*)uni64<G>(c.g.bcast(q, src)), uni<G>(c.g.bcast(n, src)), nullptr};
+            int32_t slo, shi;
+            bounds<K>(l2.hi_src, l2.lo_src, v, slo, shi);
+            const uint32_t mine = (uint32_t)uni<G>((int32_t)c.g.bcast(own, src)) << L;
+            table_leaf<K, G, MODE>(d, c, v, N, slo, shi, l2.inj, images | mine, acc, carry);
+        }
+    }
 }
 
 // The IEP leaf at the last outer level L (inner levels L+1 .. K-1): every
@@ -1217,7 +1274,11 @@ __device__ void search(const GpPlanDesc& d, const Ctx<G>& c, int32_t (&v)[K], ui
         bounds<K>(lv.hi_src, lv.lo_src, v, lo, hi);
         Set S = lv.list >= 0 ? c.nbr_u(pick<K>(v, lv.list)) : c.buf_u(lv.buf);
         if constexpr (LEAF == 5 && L == K - 2) {
-            table_leaf<K, G, MODE>(d, c, v, S, lo, hi, lv.inj, acc, carry);
+            const GpLevel& ll = d.lv[K - 1];
+            int32_t llo, lhi;
+            bounds<K>(ll.hi_src, ll.lo_src, v, llo, lhi);
+            const uint32_t images = table_images<K, G, K - 2>(ll, c, v, ll.pre_list == 0 ? v[0] : v[1], llo, lhi);
+            table_leaf<K, G, MODE>(d, c, v, S, lo, hi, lv.inj, images, acc, carry);
             return;
         }
         if constexpr (MODE == MODE_ACCOUNT)
@@ -1269,6 +1330,12 @@ __device__ void search(const GpPlanDesc& d, const Ctx<G>& c, int32_t (&v)[K], ui
                 }
             }
         } else {
+            if constexpr (LEAF == 5 && L == K - 3) {
+                if (d.build_begin[L] == d.build_end[L] && d.lv[K - 2].list == L) {
+                    table_lists<K, G, MODE>(d, c, v, S, st, lv.inj, acc, carry);
+                    return;
+                }
+            }
             if constexpr (LEAF == 3 && L == K - 3 && IEP == 0) {
                 if (d.build_begin[L] == d.build_end[L]) {
                     flat_leaf<K, G, MODE>(d, c, v, S, st, lv.inj, acc, carry);

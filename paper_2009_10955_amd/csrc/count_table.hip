@@ -12,8 +12,10 @@
 //     hold nearly every list entry (95% on R-MAT 17);
 //   * roots come in order of their hub endpoint, the other one ascending. While
 //     p, the hub, stays and the cut only grows with the other endpoint, a root
-//     adds the lists of the y that come in; else the table is filled anew,
-//     which walks N(p)'s lists once where the search walks N(x)'s for every x;
+//     adds the lists of the y that come in; else (p the other endpoint, or the
+//     endpoint that the last level must avoid left out) the table is filled
+//     anew, which walks N(p)'s lists once where the search walks N(x)'s for
+//     every x;
 //   * the wavefronts take different level-2 candidates (k = 4: different
 //     batches of one list) and search on as 64-lane groups (leaf mode 5).
 // The search reads lists in order and looks counts up in LDS: neither the
@@ -31,17 +33,31 @@ namespace {
 template <int MODE>
 __device__ __forceinline__ void add_lists(const Ctx<64>& c, const Set& P, int32_t b, int32_t e, int wave, int waves,
                                           uint32_t* tab) {
-    for (int32_t t = b + wave; t < e; t += waves) {
-        const Set N = c.nbr_u(uni<64>(P.p[t]));
-        if constexpr (MODE == MODE_ACCOUNT)
-            if (c.g.gl == 0) *c.bytes += 4;
-        for (int32_t base = 0; base < N.n; base += 64) {
-            const int32_t i = base + c.g.gl;
-            const int32_t x = i < N.n ? N.p[i] : 0x7fffffff;
-            if constexpr (MODE == MODE_ACCOUNT) *c.bytes += i < N.n ? 4 : 0;
-            // no carry into the neighbouring count: at most max_deg < 2^16 per vertex
-            if (x < c.tab_n) atomicAdd(&tab[x >> 1], 1u << ((x & 1) * 16));
-            if (uni<64>(x) >= c.tab_n) break;  // the lane holding the smallest is past the table
+    for (int32_t t0 = b + wave; t0 < e; t0 += 64 * waves) {
+        // the lanes look up 64 lists' bounds at once
+        const int32_t t = t0 + c.g.gl * waves;
+        long long q = 0;
+        int32_t n = 0;
+        int32_t y = c.out;
+        if (t < e) y = P.p[t];
+        if (y != c.out) {
+            const int64_t rb = c.row_ptr[y], re = c.row_ptr[y + 1];
+            q = (long long)(c.col + rb);
+            n = (int32_t)(re - rb);
+            if constexpr (MODE == MODE_ACCOUNT) *c.bytes += 4;
+        }
+        const int lists = (int)__popcll(c.g.ballot(t < e));
+        for (int j = 0; j < lists; ++j) {
+            const int32_t* np = (const int32_t*)uni64<64>(c.g.bcast(q, j));
+            const int32_t nn = uni<64>(c.g.bcast(n, j));
+            for (int32_t base = 0; base < nn; base += 64) {
+                const int32_t i = base + c.g.gl;
+                const int32_t x = i < nn ? np[i] : 0x7fffffff;
+                if constexpr (MODE == MODE_ACCOUNT) *c.bytes += i < nn ? 4 : 0;
+                // no carry into the neighbouring count: at most max_deg < 2^16 per vertex
+                if (x < c.tab_n) atomicAdd(&tab[x >> 1], 1u << ((x & 1) * 16));
+                if (uni<64>(x) >= c.tab_n) break;  // the lane holding the smallest is past the table
+            }
         }
     }
 }
@@ -82,6 +98,7 @@ __global__ __launch_bounds__(kTabBlock) __attribute__((amdgpu_waves_per_eu(8))) 
 
     const GpLevel& ll = d.lv[K - 1];
     int32_t cur_p = -1, cur_lo = 0, cur_hi = 0, cur_pos = 0;
+    c.out = -1;
     if (threadIdx.x == 0) s_cur = (int)(blockIdx.x & (kCursors - 1));
     __syncthreads();
     for (;;) {
@@ -107,8 +124,10 @@ __global__ __launch_bounds__(kTabBlock) __attribute__((amdgpu_waves_per_eu(8))) 
             int32_t lo, hi;
             bounds<K>(ll.hi_src, ll.lo_src, v, lo, hi);
             const Set P = c.nbr_u(p);
+            const int q = 1 - ll.pre_list;
+            const int32_t out = (ll.inj >> q) & 1u ? v[q] : -1;
             // every wavefront of the block takes the same way here
-            if (p != cur_p || lo != cur_lo || hi < cur_hi) {
+            if (p != cur_p || lo != cur_lo || hi < cur_hi || out != c.out) {
                 for (int i = threadIdx.x; i < (a.tab_n + 7) / 8; i += kTabBlock)
                     reinterpret_cast<uint4*>(s_tab)[i] = make_uint4(0, 0, 0, 0);
                 cur_pos = lo > 0 ? uni<64>(lower_bound_group<64>(c.g, P.p, P.n, lo)) : 0;
@@ -117,6 +136,7 @@ __global__ __launch_bounds__(kTabBlock) __attribute__((amdgpu_waves_per_eu(8))) 
             const int32_t end = hi < 0x7fffffff
                                     ? cur_pos + uni<64>(lower_bound_group<64>(c.g, P.p + cur_pos, P.n - cur_pos, hi))
                                     : P.n;
+            c.out = out;
             if (end > cur_pos) add_lists<MODE>(c, P, cur_pos, end, wave, kWaves, s_tab);
             cur_pos = max(cur_pos, end);
             cur_p = p;
