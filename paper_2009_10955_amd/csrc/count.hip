@@ -16,7 +16,7 @@ KernelFn pick_kernel_k5(int group, int leaf, int mode, int iep);
 KernelFn pick_kernel_k6(int group, int leaf, int mode, int iep);
 KernelFn pick_kernel_k7(int group, int leaf, int mode, int iep);
 KernelFn pick_kernel_k8(int group, int leaf, int mode, int iep);
-KernelFn pick_table_kernel(int k, int mode);
+KernelFn pick_table_kernel(int k, int mode, int waves);
 BatchFn batch_kernel_k2_2(int group, int leaf, int iep);
 BatchFn batch_kernel_k3_3(int group, int leaf, int iep);
 BatchFn batch_kernel_k4_4(int group, int leaf, int iep);
@@ -136,10 +136,16 @@ bool table_rule(const gpint::DeviceGraph& g, const GpPlanDesc& d, int mode) {
            ((ll.hi_src | ll.lo_src) & ~3u) == 0;
 }
 
-// Its launch: two blocks of 16 wavefronts per CU (64 KB of LDS each), and up to
-// 16 roots per grab, which share a hub endpoint and so a table.
-int64_t table_blocks(const gpint::DeviceGraph& g, int waves_per_cu, int64_t n_roots) {
-    const int64_t most = (int64_t)g.num_cus * (waves_per_cu >= 2 * (kTabBlock / 64) ? 2 : 1);
+// Its blocks: 4 wavefronts where a root edge has little work (one level of lanes,
+// k = 4) or the small table covers the graph, else 16: 4-cycle on G(1000, 0.01), a
+// whole call, 76 us with 16 and 54 with 4; 5-cycle on G(5000, 0.004) 0.74 and 0.31 ms.
+int table_waves(const gpint::DeviceGraph& g, const GpPlanDesc& d) { return d.k == 4 || g.n <= table_max(4) ? 4 : 16; }
+
+// Its launch: blocks that keep waves_per_cu wavefronts (a multiple of the
+// block's, at least one block) per CU, and up to 16 roots per grab, which share
+// a hub endpoint and so a table.
+int64_t table_blocks(const gpint::DeviceGraph& g, const GpPlanDesc& d, int waves_per_cu, int64_t n_roots) {
+    const int64_t most = (int64_t)g.num_cus * std::max(1, waves_per_cu / table_waves(g, d));
     return std::max<int64_t>(1, std::min(most, n_roots));
 }
 int32_t table_chunk(int64_t blocks, int64_t n_roots) {
@@ -259,7 +265,10 @@ LaunchCfg default_launch(const GpPlanDesc& d) {
 }
 
 int resident_waves_per_cu(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCfg& cfg) {
-    if (table_rule(g, d, MODE_PLAIN)) return cfg.waves_per_cu >= 2 * (kTabBlock / 64) ? 2 * (kTabBlock / 64) : kTabBlock / 64;
+    if (table_rule(g, d, MODE_PLAIN)) {
+        const int w = table_waves(g, d);
+        return std::max(1, cfg.waves_per_cu / w) * w;
+    }
     const bool iep = d.iep != 0;
     const int group = iep ? (cfg.group >= 64 ? 64 : 32) : cfg.group;
     KernelFn fn = pick_kernel(d.k, group, cfg.leaf, MODE_PLAIN, d.iep);
@@ -369,7 +378,8 @@ gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCf
     const bool iep = d.iep != 0;
     const int group = iep ? (cfg.group >= 64 ? 64 : 32) : cfg.group;  // IEP kernels: 64 or 32 lanes
     const bool table = table_rule(g, d, mode);
-    KernelFn fn = table ? pick_table_kernel(d.k, mode) : pick_kernel(d.k, group, cfg.leaf, mode, d.iep);
+    const int tab_waves = table_waves(g, d);
+    KernelFn fn = table ? pick_table_kernel(d.k, mode, tab_waves) : pick_kernel(d.k, group, cfg.leaf, mode, d.iep);
     if (!fn) return GP_ERR_UNSUPPORTED;
 
     int64_t all_roots = 0;
@@ -392,8 +402,8 @@ gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCf
     int64_t groups_per_block = kBlock / group;
     int32_t chunk = cfg.chunk;
     if (table) {
-        groups_per_block = kTabBlock / 64;
-        blocks = table_blocks(g, cfg.waves_per_cu, n_roots);
+        groups_per_block = tab_waves;
+        blocks = table_blocks(g, d, cfg.waves_per_cu, n_roots);
         chunk = table_chunk(blocks, n_roots);
     }
     const int64_t cap = std::max<int64_t>(1, g.deg2);
@@ -452,7 +462,7 @@ gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCf
     a.n_roots = n_roots;
     a.n_tasks = n_tasks;
     a.n_chunks = table ? (n_roots + chunk - 1) / chunk : need;
-    a.tab_n = (int32_t)std::min<int64_t>(g.n, kTabMax);
+    a.tab_n = (int32_t)std::min<int64_t>(g.n, table_max(tab_waves));
     a.split_roots = split_roots;
     a.split_ways = split_ways;
     a.budget_ticks = busy && cfg.budget_ms > 0 ? (uint64_t)(cfg.budget_ms * g.wall_khz) : 0;
@@ -472,7 +482,7 @@ gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCf
     a.memo_ways_log2 = std::max(iep_log2, 0);
     a.xcd_block = xcd_block_tasks(g, cfg, group);
     if (n_tasks > 0)
-        hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(table ? kTabBlock : kBlock), 0, stream, d, a);
+        hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(table ? tab_waves * 64 : kBlock), 0, stream, d, a);
     // a sample's total need not be a multiple of the over-count: its quotient
     // is an estimate, not checked
     const bool whole = cfg.root_stride == 1 && cfg.root_offset == 0 && !(busy && cfg.budget_ms > 0);
@@ -639,6 +649,7 @@ static gp_status batch_layout(const DeviceGraph& g, const GpPlanDesc* descs, con
             r.iep = iep_depth;
             r.kmin = r.kmax = descs[i].k;
             r.table = table;
+            r.tab_waves = table_waves(g, descs[i]);
             b->runs.push_back(r);
         }
         b->runs.back().p1 = i + 1;
@@ -698,7 +709,7 @@ static int64_t batch_blocks(const DeviceGraph& g, int waves_per_cu, int slots_pe
 
 // Group slots (scratch and memo tables) a run's launch addresses.
 static int64_t run_group_slots(const BatchRun& r) {
-    return r.table ? r.blocks * (kTabBlock / 64) : r.blocks * (kBlock / 64) * (64 / r.group);
+    return r.table ? r.blocks * r.tab_waves : r.blocks * (kBlock / 64) * (64 / r.group);
 }
 
 gp_status batch_prepare(const DeviceGraph& g, const GpPlanDesc* descs, const LaunchCfg* cfgs,
@@ -716,10 +727,11 @@ gp_status batch_prepare(const DeviceGraph& g, const GpPlanDesc* descs, const Lau
         r.blocks = batch_blocks(g, std::min(waves_per_cu, r.waves_per_cu), 64 / r.group, b.nbuf, b.cap, b.use_memo);
         if (r.table) {
             // within the scratch budget, as batch_blocks keeps the others
-            r.blocks = table_blocks(g, std::min(waves_per_cu, r.waves_per_cu), std::max<int64_t>(1, r.n_roots));
+            r.blocks = table_blocks(g, descs[r.p0], std::min(waves_per_cu, r.waves_per_cu),
+                                    std::max<int64_t>(1, r.n_roots));
             if (b.nbuf > 0)
                 r.blocks = std::max<int64_t>(
-                    1, std::min(r.blocks, (int64_t(16) << 30) / ((kTabBlock / 64) * b.nbuf * b.cap * 4)));
+                    1, std::min(r.blocks, (int64_t(16) << 30) / (r.tab_waves * b.nbuf * b.cap * 4)));
         }
         slots = std::max(slots, run_group_slots(r));
     }
@@ -784,7 +796,7 @@ gp_status batch_enqueue(const DeviceGraph& g, const BatchState& st, hipStream_t 
             // the plain counting kernel over the plan's whole task space
             const int p = r.p0;
             const GpPlanDesc& d = st.h_descs[p];
-            KernelFn fn = r.table ? pick_table_kernel(d.k, MODE_PLAIN) : pick_kernel(d.k, r.group, r.leaf, MODE_PLAIN, d.iep);
+            KernelFn fn = r.table ? pick_table_kernel(d.k, MODE_PLAIN, r.tab_waves) : pick_kernel(d.k, r.group, r.leaf, MODE_PLAIN, d.iep);
             if (!fn) return GP_ERR_UNSUPPORTED;
             const int32_t chunk = r.table ? table_chunk(r.blocks, r.n_roots) : r.chunk;
             CountArgs a;
@@ -794,7 +806,7 @@ gp_status batch_enqueue(const DeviceGraph& g, const BatchState& st, hipStream_t 
             a.n_roots = r.n_roots;
             a.n_tasks = r.n_tasks;
             a.n_chunks = ((r.table ? r.n_roots : r.n_tasks) + chunk - 1) / chunk;
-            a.tab_n = (int32_t)std::min<int64_t>(g.n, kTabMax);
+            a.tab_n = (int32_t)std::min<int64_t>(g.n, table_max(r.tab_waves));
             a.split_roots = r.split_roots;
             a.split_ways = r.split_ways;
             a.budget_ticks = 0;
@@ -819,7 +831,7 @@ gp_status batch_enqueue(const DeviceGraph& g, const BatchState& st, hipStream_t 
             a.chunk = chunk;
             a.xcd_block = 0;
             if (r.n_tasks > 0)
-                hipLaunchKernelGGL(fn, dim3((unsigned)r.blocks), dim3(r.table ? kTabBlock : kBlock), 0, stream, d, a);
+                hipLaunchKernelGGL(fn, dim3((unsigned)r.blocks), dim3(r.table ? r.tab_waves * 64 : kBlock), 0, stream, d, a);
             continue;
         }
         BatchArgs a;
@@ -891,8 +903,9 @@ gp_status arena_launch(const DeviceGraph& g, BatchArena* ar, const GpPlanDesc* d
     if (b.use_memo) room = std::min(room, ar->slots_cap);
     int64_t slots = 0;
     for (BatchRun& r : b.runs) {
-        const int64_t per_block = r.table ? kTabBlock / 64 : (kBlock / 64) * (64 / r.group);
-        r.blocks = r.table ? table_blocks(g, std::min(ar->waves_per_cu, r.waves_per_cu), std::max<int64_t>(1, r.n_roots))
+        const int64_t per_block = r.table ? r.tab_waves : (kBlock / 64) * (64 / r.group);
+        r.blocks = r.table ? table_blocks(g, descs[r.p0], std::min(ar->waves_per_cu, r.waves_per_cu),
+                                          std::max<int64_t>(1, r.n_roots))
                            : batch_blocks(g, std::min(ar->waves_per_cu, r.waves_per_cu), 64 / r.group, b.nbuf, b.cap,
                                           b.use_memo);
         r.blocks = std::max<int64_t>(1, std::min(r.blocks, room / per_block));

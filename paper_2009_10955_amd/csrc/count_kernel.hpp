@@ -56,10 +56,9 @@ using namespace gpdev;
 
 constexpr int kBlock = 256;
 
-// The table kernel's block, and the most vertices its table covers (16-bit
-// counts, 64 KB of LDS: two blocks per CU).
-constexpr int kTabBlock = 1024;
-constexpr int kTabMax = 32768;
+// The table kernel's blocks: 16 wavefronts with a table of 32,768 vertices, or
+// 4 with one of 8,192 (16-bit counts, 64 or 16 KB of LDS: 32 wavefronts per CU).
+constexpr int table_max(int waves) { return waves * 2048; }
 
 // Kernel modes: plain count, per-root counts, or accounting of the bytes the
 // search reads and writes (never timed).
@@ -435,9 +434,12 @@ __device__ __forceinline__ void group_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
-// Builds scheduled right after level h is bound.
+// Builds scheduled right after level h is bound. False once one comes out empty:
+// every buffer holds a superset of some level's candidates, so nothing below
+// this binding is an embedding (with inclusion-exclusion, no tuple either), and
+// the remaining builds and levels are skipped.
 template <int K, int G, int MODE>
-__device__ __forceinline__ void run_builds(const GpPlanDesc& d, const Ctx<G>& c, int h,
+__device__ __forceinline__ bool run_builds(const GpPlanDesc& d, const Ctx<G>& c, int h,
                                            const int32_t (&v)[K]) {
     const int b0 = d.build_begin[h], b1 = d.build_end[h];
     for (int t = b0; t < b1; ++t) {
@@ -453,10 +455,12 @@ __device__ __forceinline__ void run_builds(const GpPlanDesc& d, const Ctx<G>& c,
         int32_t n = uni<G>(intersect_into<G>(c.g, A, B, c.bufs + (int64_t)b.dst * c.cap));
         if constexpr (MODE == MODE_ACCOUNT)
             if (c.g.gl == 0) *c.bytes += cb + probe_isect_bytes(A, B) + 4ull * (uint64_t)n;
+        if (n == 0) return false;
         group_fence();
         c.lens[b.dst] = n;
         group_fence();
     }
+    return true;
 }
 
 // Count of the last level for bound values v[0..K-2], by one lane.
@@ -1347,8 +1351,7 @@ __device__ void search(const GpPlanDesc& d, const Ctx<G>& c, int32_t (&v)[K], ui
                 const int32_t x = uni<G>(S.p[(int64_t)t * st]);
                 if (inj_hit<K>(lv.inj, v, x)) continue;
                 v[L] = x;
-                run_builds<K, G, MODE>(d, c, L, v);
-                search<K, L + 1, G, LEAF, MODE, IEP>(d, c, v, acc, carry);
+                if (run_builds<K, G, MODE>(d, c, L, v)) search<K, L + 1, G, LEAF, MODE, IEP>(d, c, v, acc, carry);
             }
         }
     }
@@ -1431,8 +1434,7 @@ __device__ __forceinline__ void run_tasks(const GpPlanDesc& d, Ctx<G>& c, const 
                 for (int j = 0; j < K; ++j) v[j] = 0;
                 v[0] = e.x;
                 v[1] = e.y;
-                run_builds<K, G, MODE>(d, c, 1, v);
-                search<K, 2, G, LEAF, MODE, IEP>(d, c, v, acc, carry);
+                if (run_builds<K, G, MODE>(d, c, 1, v)) search<K, 2, G, LEAF, MODE, IEP>(d, c, v, acc, carry);
             }
             if constexpr (PER_ROOT) {
                 uint64_t mine = c.g.sum(acc - before);

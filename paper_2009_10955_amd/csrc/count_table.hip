@@ -6,10 +6,10 @@
 // of two-paths from p to x, filled by walking the lists of N(p).
 //
 // How it maps to the machine:
-//   * a block of 16 wavefronts works on one root edge with the table in its
-//     LDS: 16-bit counts of the kTabMax vertices of highest degree (64 KB, so
-//     two blocks and 32 wavefronts per CU). In the degree-sorted layout these
-//     hold nearly every list entry (95% on R-MAT 17);
+//   * a block of 16 or 4 wavefronts works on one root edge with the table in
+//     its LDS: 16-bit counts of the 32,768 or 8,192 vertices of highest degree
+//     (64 or 16 KB, so 32 wavefronts per CU). In the degree-sorted layout the
+//     first 32,768 hold nearly every list entry (95% on R-MAT 17);
 //   * roots come in order of their hub endpoint, the other one ascending. While
 //     p, the hub, stays and the cut only grows with the other endpoint, a root
 //     adds the lists of the y that come in; else (p the other endpoint, or the
@@ -62,11 +62,11 @@ __device__ __forceinline__ void add_lists(const Ctx<64>& c, const Set& P, int32_
     }
 }
 
-template <int K, int MODE>
-__global__ __launch_bounds__(kTabBlock) __attribute__((amdgpu_waves_per_eu(8))) void table_kernel(GpPlanDesc d,
-                                                                                                  CountArgs a) {
-    constexpr int kWaves = kTabBlock / 64;
-    __shared__ __attribute__((aligned(16))) uint32_t s_tab[kTabMax / 2];
+template <int K, int MODE, int kWaves>
+__global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(8))) void table_kernel(GpPlanDesc d,
+                                                                                                    CountArgs a) {
+    constexpr int kTabBlock = kWaves * 64;
+    __shared__ __attribute__((aligned(16))) uint32_t s_tab[table_max(kWaves) / 2];
     __shared__ int32_t s_len[kWaves][GP_DESC_MAX_BUILDS];
     __shared__ int64_t s_chunk;
     __shared__ int32_t s_cur;
@@ -175,10 +175,12 @@ __global__ __launch_bounds__(kTabBlock) __attribute__((amdgpu_waves_per_eu(8))) 
 
 }  // namespace
 
-KernelFn pick_table_kernel(int k, int mode) {
-    if (mode != MODE_PLAIN && mode != MODE_ACCOUNT) return nullptr;
-#define GP_TABLE_CASE(KK) \
-    case KK: return mode == MODE_PLAIN ? table_kernel<KK, MODE_PLAIN> : table_kernel<KK, MODE_ACCOUNT>;
+KernelFn pick_table_kernel(int k, int mode, int waves) {
+    if ((mode != MODE_PLAIN && mode != MODE_ACCOUNT) || (waves != 4 && waves != 16)) return nullptr;
+#define GP_TABLE_CASE(KK)                                                                                \
+    case KK:                                                                                             \
+        if (waves == 4) return mode == MODE_PLAIN ? table_kernel<KK, MODE_PLAIN, 4> : table_kernel<KK, MODE_ACCOUNT, 4>; \
+        return mode == MODE_PLAIN ? table_kernel<KK, MODE_PLAIN, 16> : table_kernel<KK, MODE_ACCOUNT, 16>;
     switch (k) {
         GP_TABLE_CASE(4)
         GP_TABLE_CASE(5)

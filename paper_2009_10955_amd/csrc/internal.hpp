@@ -109,6 +109,7 @@ struct BatchRun {
     // space as that kernel takes it
     bool solo = false;
     bool table = false;  // solo, by the table kernel
+    int tab_waves = 16;  // wavefronts of its blocks
     const int2* roots = nullptr;
     int64_t n_roots = 0, root_offset = 0, root_stride = 1, n_tasks = 0, split_roots = 0;
     int32_t split_ways = 1, chunk = 1;

@@ -251,8 +251,8 @@ __device__ void list_search(const GpPlanDesc& d, const gpcount::Ctx<G>& c, const
             const int32_t x = gpcount::uni<G>(S.p[t]);
             if (gpcount::inj_hit<K>(lv.inj, v, x)) continue;
             v[L] = x;
-            gpcount::run_builds<K, G, gpcount::MODE_PLAIN>(d, c, L, v);
-            list_search<K, L + 1, WRITE>(d, c, a, v, pos, st);
+            if (gpcount::run_builds<K, G, gpcount::MODE_PLAIN>(d, c, L, v))
+                list_search<K, L + 1, WRITE>(d, c, a, v, pos, st);
         }
     }
 }
@@ -315,8 +315,8 @@ __global__ __launch_bounds__(kBlock) void list_kernel(GpPlanDesc d, ListArgs a) 
                 v[1] = gpcount::uni<G>(e.y);
                 uint64_t pos = WRITE ? (uint64_t)gpcount::uni64<G>((int64_t)a.task_rows[t]) : 0;
                 Stage st{WRITE ? &s_stage[grp][0] : nullptr, pos, 0};
-                gpcount::run_builds<K, G, gpcount::MODE_PLAIN>(d, c, 1, v);
-                list_search<K, 2, WRITE>(d, c, a, v, pos, st);
+                if (gpcount::run_builds<K, G, gpcount::MODE_PLAIN>(d, c, 1, v))
+                    list_search<K, 2, WRITE>(d, c, a, v, pos, st);
                 if constexpr (WRITE) flush<K>(c.g, a, st);
                 if constexpr (!WRITE)
                     if (c.g.gl == 0) a.task_rows[t] = pos;
