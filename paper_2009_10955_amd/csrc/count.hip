@@ -17,6 +17,7 @@ KernelFn pick_kernel_k6(int group, int leaf, int mode, int iep);
 KernelFn pick_kernel_k7(int group, int leaf, int mode, int iep);
 KernelFn pick_kernel_k8(int group, int leaf, int mode, int iep);
 KernelFn pick_table_kernel(int k, int mode, int waves);
+KernelFn pick_table_iep_kernel(int k, int mode);
 BatchFn batch_kernel_k2_2(int group, int leaf, int iep);
 BatchFn batch_kernel_k3_3(int group, int leaf, int iep);
 BatchFn batch_kernel_k4_4(int group, int leaf, int iep);
@@ -123,14 +124,22 @@ bool memo_eligible(const GpPlanDesc& d) {
 // plan whose last level is N(x) & N(root endpoint) cut by root levels, whole
 // counts and samples alike, while its sizes fit 16 bits. Not with builds at the
 // root level, which each of the block's 16 wavefronts would repeat, and not
-// per root. Without and with the table: R-MAT 17 5-cycle (64 lanes, split 4
+// per root. With inclusion-exclusion: plans whose set of the last outer vertex x is
+// N(root endpoint) & N(x). Without and with the table: R-MAT 17 5-cycle (64 lanes, split 4
 // ways, leaf mode 4 with a memo) 477 and 31 ms; 5-cycle of the cost model's plan on
 // R-MAT (20,000 vertices, 160K edges) 100 and 11.5 ms; 6-cycle on Chung-Lu (3,000
 // vertices, 30K edges) 199 and 24 ms; 4-cycle on G(1000, 0.01), a whole call,
 // 109 and 76 us.
 bool table_rule(const gpint::DeviceGraph& g, const GpPlanDesc& d, int mode) {
-    if (mode == MODE_PER_ROOT || d.k < 4 || d.iep || d.build_begin[1] != d.build_end[1] || g.max_deg >= 65536)
-        return false;
+    if (mode == MODE_PER_ROOT || d.k < 4 || g.deg2 >= 65536) return false;
+    if (d.iep) {
+        // the set of the last outer vertex: N(p) & N(x), uncut, p the endpoint
+        // that the root array is ordered by
+        if (d.iep != 2 || !d.iep_sum || d.root_cut == 0) return false;
+        const GpIepTerm& t = d.it[d.iep_sum - 1];
+        return t.n_op == 2 && t.memo && t.op[0] == (d.root_cut == 2 ? 0 : 1) && t.op[1] == d.k - 3;
+    }
+    if (d.build_begin[1] != d.build_end[1]) return false;
     const GpLevel& ll = d.lv[d.k - 1];
     return ll.last_list == d.k - 2 && ll.pre_buf < 0 && (ll.pre_list == 0 || ll.pre_list == 1) &&
            ((ll.hi_src | ll.lo_src) & ~3u) == 0;
@@ -139,17 +148,24 @@ bool table_rule(const gpint::DeviceGraph& g, const GpPlanDesc& d, int mode) {
 // Its blocks: 4 wavefronts where a root edge has little work (one level of lanes,
 // k = 4) or the small table covers the graph, else 16: 4-cycle on G(1000, 0.01), a
 // whole call, 76 us with 16 and 54 with 4; 5-cycle on G(5000, 0.004) 0.74 and 0.31 ms.
-int table_waves(const gpint::DeviceGraph& g, const GpPlanDesc& d) { return d.k == 4 || g.n <= table_max(4) ? 4 : 16; }
+int table_waves(const gpint::DeviceGraph& g, const GpPlanDesc& d) {
+    if (d.iep) return kIepTableWaves;
+    return d.k == 4 || g.n <= table_max(4) ? 4 : 16;
+}
 
 // Its launch: blocks that keep waves_per_cu wavefronts (a multiple of the
-// block's, at least one block) per CU, and up to 16 roots per grab, which share
-// a hub endpoint and so a table.
+// block's, at least one block) per CU, and up to 16 roots (IEP: 64) per grab,
+// which share a hub endpoint and so a table.
 int64_t table_blocks(const gpint::DeviceGraph& g, const GpPlanDesc& d, int waves_per_cu, int64_t n_roots) {
-    const int64_t most = (int64_t)g.num_cus * std::max(1, waves_per_cu / table_waves(g, d));
+    const int w = table_waves(g, d);
+    const int64_t most = (int64_t)g.num_cus * std::max(1, std::min(waves_per_cu, d.iep ? 3 * w : 32) / w);
     return std::max<int64_t>(1, std::min(most, n_roots));
 }
-int32_t table_chunk(int64_t blocks, int64_t n_roots) {
-    return (int32_t)std::max<int64_t>(1, std::min<int64_t>(16, n_roots / (blocks * 8)));
+int32_t table_chunk(const GpPlanDesc& d, int64_t blocks, int64_t n_roots) {
+    return (int32_t)std::max<int64_t>(1, std::min<int64_t>(d.iep ? 64 : 16, n_roots / (blocks * 8)));
+}
+KernelFn pick_table(const GpPlanDesc& d, int mode, int waves) {
+    return d.iep ? pick_table_iep_kernel(d.k, mode) : pick_table_kernel(d.k, mode, waves);
 }
 
 // The count's last step (one wavefront): the sum of the queue's 128-bit totals
@@ -267,7 +283,7 @@ LaunchCfg default_launch(const GpPlanDesc& d) {
 int resident_waves_per_cu(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCfg& cfg) {
     if (table_rule(g, d, MODE_PLAIN)) {
         const int w = table_waves(g, d);
-        return std::max(1, cfg.waves_per_cu / w) * w;
+        return std::max(1, std::min(cfg.waves_per_cu, d.iep ? 3 * w : 32) / w) * w;
     }
     const bool iep = d.iep != 0;
     const int group = iep ? (cfg.group >= 64 ? 64 : 32) : cfg.group;
@@ -379,7 +395,7 @@ gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCf
     const int group = iep ? (cfg.group >= 64 ? 64 : 32) : cfg.group;  // IEP kernels: 64 or 32 lanes
     const bool table = table_rule(g, d, mode);
     const int tab_waves = table_waves(g, d);
-    KernelFn fn = table ? pick_table_kernel(d.k, mode, tab_waves) : pick_kernel(d.k, group, cfg.leaf, mode, d.iep);
+    KernelFn fn = table ? pick_table(d, mode, tab_waves) : pick_kernel(d.k, group, cfg.leaf, mode, d.iep);
     if (!fn) return GP_ERR_UNSUPPORTED;
 
     int64_t all_roots = 0;
@@ -404,7 +420,7 @@ gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCf
     if (table) {
         groups_per_block = tab_waves;
         blocks = table_blocks(g, d, cfg.waves_per_cu, n_roots);
-        chunk = table_chunk(blocks, n_roots);
+        chunk = table_chunk(d, blocks, n_roots);
     }
     const int64_t cap = std::max<int64_t>(1, g.deg2);
     const int64_t per_block = d.nbuf > 0 ? groups_per_block * d.nbuf * cap * 4 : 0;
@@ -796,9 +812,9 @@ gp_status batch_enqueue(const DeviceGraph& g, const BatchState& st, hipStream_t 
             // the plain counting kernel over the plan's whole task space
             const int p = r.p0;
             const GpPlanDesc& d = st.h_descs[p];
-            KernelFn fn = r.table ? pick_table_kernel(d.k, MODE_PLAIN, r.tab_waves) : pick_kernel(d.k, r.group, r.leaf, MODE_PLAIN, d.iep);
+            KernelFn fn = r.table ? pick_table(d, MODE_PLAIN, r.tab_waves) : pick_kernel(d.k, r.group, r.leaf, MODE_PLAIN, d.iep);
             if (!fn) return GP_ERR_UNSUPPORTED;
-            const int32_t chunk = r.table ? table_chunk(r.blocks, r.n_roots) : r.chunk;
+            const int32_t chunk = r.table ? table_chunk(d, r.blocks, r.n_roots) : r.chunk;
             CountArgs a;
             a.row_ptr = g.row_ptr;
             a.col = g.col;

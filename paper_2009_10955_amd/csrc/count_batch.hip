@@ -58,6 +58,7 @@ __device__ void run_piece(const BatchArgs& a, const GpPlanDesc& d, const BatchPl
     c.memo_log2 = max(a.iep_memo_log2, 0);
     c.tab = nullptr;
     c.tab_n = 0;
+    c.filt = nullptr;
     __shared__ uint32_t s_cnt[IEP > 0 ? ((1 << IEP) - 1) * kBlock : 1];
     c.cnt = &s_cnt[IEP > 0 ? threadIdx.x : 0];
     TaskSpace ts;

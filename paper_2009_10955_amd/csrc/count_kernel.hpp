@@ -59,6 +59,10 @@ constexpr int kBlock = 256;
 // The table kernel's blocks: 16 wavefronts with a table of 32,768 vertices, or
 // 4 with one of 8,192 (16-bit counts, 64 or 16 KB of LDS: 32 wavefronts per CU).
 constexpr int table_max(int waves) { return waves * 2048; }
+// Words of the filter of N(p) that the table kernel for IEP keeps: bit y mod
+// 32 * kFiltWords is set for every y in N(p).
+constexpr int kFiltWords = 2048;
+constexpr int kIepTableWaves = 8;  // its blocks: 32 KB of table, 8 of filter, three blocks per CU
 
 // Kernel modes: plain count, per-root counts, or accounting of the bytes the
 // search reads and writes (never timed).
@@ -259,6 +263,7 @@ struct Ctx {
     const uint16_t* tab;       // leaf mode 5: the block's path table in LDS, of vertices [0, tab_n)
     int32_t tab_n;
     int32_t out;               // leaf mode 5: the root endpoint left out of the table, a neighbor of p (-1: none)
+    const uint32_t* filt;      // IEP with the table: N(p) hashed to kFiltWords words of bits in LDS
     Group<G> g;
 
     __device__ __forceinline__ bool expired() const {
@@ -1129,7 +1134,61 @@ __device__ __forceinline__ void table_lists(const GpPlanDesc& d, const Ctx<G>& c
 // for each of the far more numerous x. A split task takes its slice of Y as it
 // takes its slice of x: partial totals may be negative, and are exact mod
 // 2^128.
-template <int K, int L, int G, int MODE>
+//
+// TAB: |N(p) & N(x)| of the x below tab_n comes from the block's table, p the
+// root endpoint whose roots the block's wavefronts are working on; other x, of low
+// degree, have their lists walked against the filter of N(p).
+
+// Whether y (which passed the filter) is a neighbor of p, P = N(p).
+template <int G>
+__device__ __forceinline__ bool filt_hit(const Ctx<G>& c, const Set& P, int32_t y) {
+    const uint32_t b = (uint32_t)y & (32u * kFiltWords - 1);
+    return ((c.filt[b >> 5] >> (b & 31)) & 1u) && member(P, y);
+}
+
+// |N(p) & N(x)| of every active lane's x. Called by all lanes of the group.
+template <int G, int MODE>
+__device__ __forceinline__ uint32_t filt_count(const Ctx<G>& c, const Set& P, int32_t x, bool active) {
+    uint32_t r = 0;
+    bool longw = false;
+    Set N{nullptr, 0, nullptr};
+    if (active) {
+        N = c.nbr(x);
+        if constexpr (MODE == MODE_ACCOUNT) *c.bytes += 4ull * (uint64_t)min(N.n, P.n);
+        if (P.n * 8 < N.n) {
+            // a search in N(x) for each of p's few neighbors
+            if (P.n <= kIepLaneWork) {
+                for (int32_t i = 0; i < P.n; ++i) r += contains(N.p, N.n, P.p[i]) ? 1u : 0u;
+            } else {
+                longw = true;
+            }
+        } else if (N.n > kIepLaneWork) {
+            longw = true;
+        } else {
+            int32_t i = 0;
+            for (; i + 4 <= N.n; i += 4) {
+                const int32_t y0 = N.p[i], y1 = N.p[i + 1], y2 = N.p[i + 2], y3 = N.p[i + 3];
+                r += (filt_hit<G>(c, P, y0) ? 1u : 0u) + (filt_hit<G>(c, P, y1) ? 1u : 0u) +
+                     (filt_hit<G>(c, P, y2) ? 1u : 0u) + (filt_hit<G>(c, P, y3) ? 1u : 0u);
+            }
+            for (; i < N.n; ++i) r += filt_hit<G>(c, P, N.p[i]) ? 1u : 0u;
+        }
+    }
+    uint64_t m = c.g.ballot(longw);
+    while (m) {
+        const int src = __builtin_ctzll(m);
+        m &= m - 1;
+        const int32_t* np = (const int32_t*)uni64<G>(c.g.bcast((long long)N.p, src));
+        const int32_t nn = uni<G>(c.g.bcast(N.n, src));
+        uint32_t mine = 0;
+        for (int32_t i = c.g.gl; i < nn; i += G) mine += filt_hit<G>(c, P, np[i]) ? 1u : 0u;
+        const uint32_t tot = c.g.sum(mine);
+        if (c.g.gl == src) r = tot;
+    }
+    return r;
+}
+
+template <int K, int L, int G, int MODE, bool TAB>
 __device__ __forceinline__ void iep_pair_sum(const GpPlanDesc& d, const Ctx<G>& c, const int32_t (&v)[K], Set S,
                                              int32_t st, Set Sf, uint32_t inj_l, uint64_t& acc, uint64_t& carry) {
     const GpIepTerm& ta = d.it[d.iep_sum - 1];
@@ -1170,8 +1229,32 @@ __device__ __forceinline__ void iep_pair_sum(const GpPlanDesc& d, const Ctx<G>& 
     const int32_t a = whole ? pick<K>(v, lv.list) : 0;
     int32_t slo, shi;
     bounds<K>(lv.hi_src, lv.lo_src, v, slo, shi);
+    if constexpr (TAB) {
+        const Set N = c.nbr_u(pick<K>(v, ta.op[0]));
+        for (int32_t base = 0; base < S.n; base += G) {
+            if (c.expired()) break;
+            const int32_t i = base + c.g.gl;
+            int32_t x = 0;
+            bool active = i < S.n;
+            if (active) x = S.p[(int64_t)i * st];
+            active = active && !inj_hit<K>(inj_l, v, x);
+            const bool far = active && x >= c.tab_n;
+            uint64_t q = far || !active ? 0 : c.tab[x];
+            if (c.g.ballot(far)) q += filt_count<G, MODE>(c, N, x, far);
+            if (!active) continue;
+            int32_t w[K];
+#pragma unroll
+            for (int j = 0; j < K; ++j) w[j] = v[j];
+            w[L] = x;
+            if (ta.inj) q -= iep_images<K, G, MODE, L + 1>(d, c, ta, ta.inj, w, 0, 0x7fffffff);
+            uint64_t b = pb;
+            if ((tb.inj >> L) & 1u) b -= iep_images<K, G, MODE, L + 1>(d, c, tb, 1u << L, w, lo, hi);
+            const unsigned __int128 val = (unsigned __int128)q * b;
+            add_count128(acc, carry, (uint64_t)val, (uint64_t)(val >> 64));
+        }
+    }
     // the candidates x, then the y: one loop, so one copy of the walk
-    const int32_t nx = S.n, ny = Y.n;
+    const int32_t nx = TAB ? 0 : S.n, ny = Y.n;
     const int32_t xbatches = (nx + G - 1) / G, batches = xbatches + (ny + G - 1) / G;
 #pragma unroll 1
     for (int32_t bt = 0; bt < batches; ++bt) {
@@ -1238,16 +1321,17 @@ __device__ __forceinline__ void iep_pair_sum(const GpPlanDesc& d, const Ctx<G>& 
     }
 }
 
-template <int K, int L, int G, int MODE>
+template <int K, int L, int G, int MODE, bool TAB>
 __device__ void iep_level(const GpPlanDesc& d, const Ctx<G>& c, int32_t (&v)[K], Set S, int32_t st, Set Sf,
                           uint32_t inj_l, uint64_t& acc, uint64_t& carry) {
     constexpr int N = K - 1 - L;
     if constexpr (N == 2) {
         if (d.iep_sum) {
-            iep_pair_sum<K, L, G, MODE>(d, c, v, S, st, Sf, inj_l, acc, carry);
+            iep_pair_sum<K, L, G, MODE, TAB>(d, c, v, S, st, Sf, inj_l, acc, carry);
             return;
         }
     }
+    if constexpr (TAB) return;  // the table kernel takes only such plans
     for (int32_t base = 0; base < S.n; base += G) {
         if (c.expired()) break;
         const int32_t i = base + c.g.gl;
@@ -1277,7 +1361,7 @@ __device__ void search(const GpPlanDesc& d, const Ctx<G>& c, int32_t (&v)[K], ui
         int32_t lo, hi;
         bounds<K>(lv.hi_src, lv.lo_src, v, lo, hi);
         Set S = lv.list >= 0 ? c.nbr_u(pick<K>(v, lv.list)) : c.buf_u(lv.buf);
-        if constexpr (LEAF == 5 && L == K - 2) {
+        if constexpr (LEAF == 5 && IEP == 0 && L == K - 2) {
             const GpLevel& ll = d.lv[K - 1];
             int32_t llo, lhi;
             bounds<K>(ll.hi_src, ll.lo_src, v, llo, lhi);
@@ -1302,7 +1386,7 @@ __device__ void search(const GpPlanDesc& d, const Ctx<G>& c, int32_t (&v)[K], ui
             if (c.g.gl == 0) *c.bytes += 4ull * (uint64_t)S.n;
         if constexpr (IEP > 0 && L == K - 1 - IEP) {
             // the last outer level: the inner ones are counted, not enumerated
-            iep_level<K, L, G, MODE>(d, c, v, S, st, Sf, lv.inj, acc, carry);
+            iep_level<K, L, G, MODE, LEAF == 5>(d, c, v, S, st, Sf, lv.inj, acc, carry);
             return;
         }
         if constexpr (L == K - 2) {
@@ -1334,7 +1418,7 @@ __device__ void search(const GpPlanDesc& d, const Ctx<G>& c, int32_t (&v)[K], ui
                 }
             }
         } else {
-            if constexpr (LEAF == 5 && L == K - 3) {
+            if constexpr (LEAF == 5 && IEP == 0 && L == K - 3) {
                 if (d.build_begin[L] == d.build_end[L] && d.lv[K - 2].list == L) {
                     table_lists<K, G, MODE>(d, c, v, S, st, lv.inj, acc, carry);
                     return;
@@ -1581,6 +1665,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(occupanc
     c.memo_log2 = a.memo_ways_log2;
     c.tab = nullptr;
     c.tab_n = 0;
+    c.filt = nullptr;
     __shared__ uint32_t s_cnt[IEP > 0 ? ((1 << IEP) - 1) * kBlock : 1];
     c.cnt = &s_cnt[IEP > 0 ? threadIdx.x : 0];
     const uint64_t t_begin = a.busy ? wall_clock64() : 0;

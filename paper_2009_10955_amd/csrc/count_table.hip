@@ -28,11 +28,11 @@ namespace gpcount {
 
 namespace {
 
-// Adds 1 to T[x] for every x < tab_n of the lists of N(p)[b, e), the block's
-// wavefronts taking different lists.
+// Adds 1 to T[x] for every x < tab_n other than p of the lists of N(p)[b, e),
+// the block's wavefronts taking different lists.
 template <int MODE>
-__device__ __forceinline__ void add_lists(const Ctx<64>& c, const Set& P, int32_t b, int32_t e, int wave, int waves,
-                                          uint32_t* tab) {
+__device__ __forceinline__ void add_lists(const Ctx<64>& c, int32_t p, const Set& P, int32_t b, int32_t e, int wave,
+                                          int waves, uint32_t* tab) {
     for (int32_t t0 = b + wave; t0 < e; t0 += 64 * waves) {
         // the lanes look up 64 lists' bounds at once
         const int32_t t = t0 + c.g.gl * waves;
@@ -54,8 +54,9 @@ __device__ __forceinline__ void add_lists(const Ctx<64>& c, const Set& P, int32_
                 const int32_t i = base + c.g.gl;
                 const int32_t x = i < nn ? np[i] : 0x7fffffff;
                 if constexpr (MODE == MODE_ACCOUNT) *c.bytes += i < nn ? 4 : 0;
-                // no carry into the neighbouring count: at most max_deg < 2^16 per vertex
-                if (x < c.tab_n) atomicAdd(&tab[x >> 1], 1u << ((x & 1) * 16));
+                // no carry into the neighbouring count: two different vertices
+                // share at most deg2 < 2^16 neighbors
+                if (x < c.tab_n && x != p) atomicAdd(&tab[x >> 1], 1u << ((x & 1) * 16));
                 if (uni<64>(x) >= c.tab_n) break;  // the lane holding the smallest is past the table
             }
         }
@@ -90,6 +91,7 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(8))
     c.cnt = nullptr;
     c.tab = (const uint16_t*)s_tab;
     c.tab_n = a.tab_n;
+    c.filt = nullptr;
     const uint64_t t_begin = a.busy ? wall_clock64() : 0;
     c.deadline = a.busy && a.budget_ticks ? t_begin + a.budget_ticks : 0;
     uint64_t chunk_max = 0;
@@ -137,7 +139,7 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(8))
                                     ? cur_pos + uni<64>(lower_bound_group<64>(c.g, P.p + cur_pos, P.n - cur_pos, hi))
                                     : P.n;
             c.out = out;
-            if (end > cur_pos) add_lists<MODE>(c, P, cur_pos, end, wave, kWaves, s_tab);
+            if (end > cur_pos) add_lists<MODE>(c, p, P, cur_pos, end, wave, kWaves, s_tab);
             cur_pos = max(cur_pos, end);
             cur_p = p;
             cur_lo = lo;
@@ -173,7 +175,155 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(8))
     }
 }
 
+// The table with inclusion-exclusion: plans with two inner levels whose set of
+// the last outer vertex x is N(p) & N(x), uncut, p the endpoint that the
+// root array is ordered by. The table then holds for all roots of p: a block
+// fills it once for a run of roots of one p (and hashes N(p) into the filter),
+// and its wavefronts take the run's roots one by one, each searching on its
+// own. What it replaces: a walk of N(p) or N(x) per (p, x), random words of
+// hub bitmaps, which bounded the house count by memory lines (a 60th of
+// R-MAT 22: 3.9 TB of lines fetched in 507 ms; now 1.06 TB in 223 ms, most of
+// them for the pairs of term 3 that the memo does not hold yet. R-MAT 17 whole:
+// 16.3 ms, now 10.5).
+constexpr int kIepWaves = kIepTableWaves;
+
+template <int K, int MODE>
+__global__ __launch_bounds__(kIepWaves * 64) __attribute__((amdgpu_waves_per_eu(6))) void table_iep_kernel(GpPlanDesc d,
+                                                                                                           CountArgs a) {
+    __shared__ __attribute__((aligned(16))) uint32_t s_tab[table_max(kIepWaves) / 2];
+    __shared__ __attribute__((aligned(16))) uint32_t s_filt[kFiltWords];
+    __shared__ int32_t s_len[kIepWaves][GP_DESC_MAX_BUILDS];
+    __shared__ int64_t s_chunk;
+    __shared__ int32_t s_cur, s_next;
+    Ctx<64> c;
+    const int wave = uni<64>((int)(threadIdx.x / 64));
+    c.row_ptr = a.row_ptr;
+    c.col = a.col;
+    c.cap = a.buf_cap;
+    c.hub_bits = a.hub_bits;
+    c.hub_words = a.hub_words;
+    c.n_hubs = a.n_hubs;
+    c.bufs = a.scratch ? a.scratch + ((int64_t)blockIdx.x * kIepWaves + wave) * (int64_t)d.nbuf * a.buf_cap : nullptr;
+    c.lens = s_len[wave];
+    uint64_t bytes = 0;
+    c.bytes = &bytes;
+    c.sj = 0;
+    c.sJ = 1;
+    c.memo = a.memo;
+    c.tag = 0;
+    c.memo_log2 = a.memo_ways_log2;
+    c.cnt = nullptr;
+    c.tab = (const uint16_t*)s_tab;
+    c.tab_n = a.tab_n;
+    c.out = -1;
+    c.filt = s_filt;
+    const uint64_t t_begin = a.busy ? wall_clock64() : 0;
+    c.deadline = a.busy && a.budget_ticks ? t_begin + a.budget_ticks : 0;
+    uint64_t chunk_max = 0;
+    bool stopped = false;
+    uint64_t acc = 0, carry = 0;
+    const bool second = d.it[d.iep_sum - 1].op[0] == 1;
+    int32_t cur_p = -1;
+    if (threadIdx.x == 0) s_cur = (int)(blockIdx.x & (kCursors - 1));
+    __syncthreads();
+    for (;;) {
+        if (wave == 0) {
+            const int64_t q = next_chunk<64>(c.g, a.queue, a.n_chunks, &s_cur);
+            if (c.g.gl == 0) s_chunk = q;
+        }
+        __syncthreads();
+        const int64_t q = uni64<64>(s_chunk);
+        if (q < 0) break;
+        const uint64_t t_chunk = a.busy ? wall_clock64() : 0;
+        const int64_t r1 = min((q + 1) * a.chunk, a.n_roots);
+        for (int64_t r = q * a.chunk; r < r1;) {
+            // the chunk's next run of roots of one p (a chunk has at most 64)
+            const int lanes = (int)(r1 - r);
+            int32_t own = -1;
+            if (c.g.gl < lanes) {
+                const int2 e = a.roots[a.root_offset + (r + c.g.gl) * a.root_stride];
+                own = second ? e.y : e.x;
+            }
+            const int32_t p = uni<64>(own);
+            const uint64_t other = c.g.ballot(own != p);
+            const int run = other ? __builtin_ctzll(other) : 64;
+            __syncthreads();  // the last run's readers are done
+            if (threadIdx.x == 0) s_next = 0;
+            if (p != cur_p) {
+                const Set P = c.nbr_u(p);
+                for (int i = threadIdx.x; i < (a.tab_n + 7) / 8; i += kIepWaves * 64)
+                    reinterpret_cast<uint4*>(s_tab)[i] = make_uint4(0, 0, 0, 0);
+                reinterpret_cast<uint4*>(s_filt)[threadIdx.x] = make_uint4(0, 0, 0, 0);
+                static_assert(kFiltWords == kIepWaves * 64 * 4, "one store per thread clears the filter");
+                __syncthreads();
+                for (int32_t i = threadIdx.x; i < P.n; i += kIepWaves * 64) {
+                    const uint32_t b = (uint32_t)P.p[i] & (32u * kFiltWords - 1);
+                    atomicOr(&s_filt[b >> 5], 1u << (b & 31));
+                }
+                add_lists<MODE>(c, p, P, 0, P.n, wave, kIepWaves, s_tab);
+                cur_p = p;
+            }
+            __syncthreads();
+            for (;;) {
+                int t = 0;
+                if (c.g.gl == 0) t = atomicAdd(&s_next, 1);
+                t = uni<64>(t);
+                if (t >= run) break;
+                const int2 e = a.roots[a.root_offset + (r + t) * a.root_stride];
+                if constexpr (MODE == MODE_ACCOUNT) bytes += c.g.gl == 0 ? 8 : 0;
+                int32_t v[K];
+#pragma unroll
+                for (int j = 0; j < K; ++j) v[j] = 0;
+                v[0] = uni<64>(e.x);
+                v[1] = uni<64>(e.y);
+                if (run_builds<K, 64, MODE>(d, c, 1, v)) search<K, 2, 64, 5, MODE, 2>(d, c, v, acc, carry);
+            }
+            r += run;
+        }
+        if (a.busy) {
+            const uint64_t now = wall_clock64();
+            chunk_max = max(chunk_max, now - t_chunk);
+            if (__syncthreads_or(c.deadline && now > c.deadline)) {
+                stopped = true;
+                break;
+            }
+        } else {
+            __syncthreads();  // s_chunk has been read
+        }
+    }
+    uint64_t s = acc, s_hi = carry;
+    wave_sum128(s, s_hi);
+    if constexpr (MODE == MODE_ACCOUNT) bytes = c.g.sum(bytes);
+    if (__lane_id() == 0) {
+        if constexpr (MODE == MODE_ACCOUNT) atomicAdd(&a.result[2], (unsigned long long)bytes);
+        unsigned long long* slot = a.queue + (blockIdx.x & (kSlots - 1)) * kSlotWords;
+        publish128(&slot[SLOT_LO], &slot[SLOT_HI], s, s_hi);
+        if (stopped) atomicOr(&a.result[1], 4ull);
+        if (a.busy) {
+            atomicAdd(&a.busy[0], (unsigned long long)(wall_clock64() - t_begin));
+            atomicAdd(&a.busy[1], 1ull);
+            atomicMax(&a.busy[2], (unsigned long long)chunk_max);
+        }
+    }
+}
+
 }  // namespace
+
+// The kernel for IEP plans: k from 5 on (two inner levels below one more outer
+// level than the root edge).
+KernelFn pick_table_iep_kernel(int k, int mode) {
+    if (mode != MODE_PLAIN && mode != MODE_ACCOUNT) return nullptr;
+#define GP_TABLE_CASE(KK) \
+    case KK: return mode == MODE_PLAIN ? table_iep_kernel<KK, MODE_PLAIN> : table_iep_kernel<KK, MODE_ACCOUNT>;
+    switch (k) {
+        GP_TABLE_CASE(5)
+        GP_TABLE_CASE(6)
+        GP_TABLE_CASE(7)
+        GP_TABLE_CASE(8)
+        default: return nullptr;
+    }
+#undef GP_TABLE_CASE
+}
 
 KernelFn pick_table_kernel(int k, int mode, int waves) {
     if ((mode != MODE_PLAIN && mode != MODE_ACCOUNT) || (waves != 4 && waves != 16)) return nullptr;

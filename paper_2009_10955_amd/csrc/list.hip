@@ -284,6 +284,7 @@ __global__ __launch_bounds__(kBlock) void list_kernel(GpPlanDesc d, ListArgs a) 
     c.cnt = nullptr;
     c.tab = nullptr;
     c.tab_n = 0;
+    c.filt = nullptr;
     const int64_t chunk = a.chunk;
     __shared__ int s_cur[kBlock / G];
     s_cur[grp] = (int)(group_id & (gpcount::kCursors - 1));
