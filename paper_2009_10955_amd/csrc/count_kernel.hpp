@@ -453,13 +453,23 @@ __device__ __forceinline__ bool run_builds(const GpPlanDesc& d, const Ctx<G>& c,
         bounds<K>(b.hi_src, b.lo_src, v, lo, hi);
         Set A = b.src_buf >= 0 ? c.buf_u(b.src_buf) : c.nbr_u(pick<K>(v, b.src_list));
         Set B = c.nbr_u(pick<K>(v, b.with_list));
-        uint64_t cb = 0;
-        if constexpr (MODE == MODE_ACCOUNT) cb = cut_bytes(A, lo, hi) + cut_bytes(B, lo, hi);
-        A = trim_u<G>(A, lo, hi);
-        B = trim_u<G>(B, lo, hi);
-        int32_t n = uni<G>(intersect_into<G>(c.g, A, B, c.bufs + (int64_t)b.dst * c.cap));
+        // The shorter operand is walked and the other tested whole. Only the
+        // walk is cut, and a walk of a few steps not even that: its elements are
+        // compared with the bounds. Each cut left out is two or more dependent
+        // loads less before the first element.
+        if (B.n < A.n) {
+            const Set t = A;
+            A = B;
+            B = t;
+        }
+        if (A.n > 4 * G && (b.hi_src | b.lo_src)) {
+            if constexpr (MODE == MODE_ACCOUNT)
+                if (c.g.gl == 0) *c.bytes += cut_bytes(A, lo, hi);
+            A = trim_u<G>(A, lo, hi);
+        }
+        int32_t n = uni<G>(intersect_into<G>(c.g, A, B, lo, hi, c.bufs + (int64_t)b.dst * c.cap));
         if constexpr (MODE == MODE_ACCOUNT)
-            if (c.g.gl == 0) *c.bytes += cb + probe_isect_bytes(A, B) + 4ull * (uint64_t)n;
+            if (c.g.gl == 0) *c.bytes += (uint64_t)A.n * (4 + test_bytes(B)) + 4ull * (uint64_t)n;
         if (n == 0) return false;
         group_fence();
         c.lens[b.dst] = n;
@@ -1369,9 +1379,11 @@ __device__ void search(const GpPlanDesc& d, const Ctx<G>& c, int32_t (&v)[K], ui
             table_leaf<K, G, MODE>(d, c, v, S, lo, hi, lv.inj, images, acc, carry);
             return;
         }
-        if constexpr (MODE == MODE_ACCOUNT)
-            if (c.g.gl == 0) *c.bytes += cut_bytes(S, lo, hi);
-        S = trim_u<G>(S, lo, hi);
+        if (!lv.cut_done) {
+            if constexpr (MODE == MODE_ACCOUNT)
+                if (c.g.gl == 0) *c.bytes += cut_bytes(S, lo, hi);
+            S = trim_u<G>(S, lo, hi);
+        }
         // a split task binds only its slice of the level-2 candidates
         const Set Sf = S;
         int32_t st = 1;

@@ -51,7 +51,8 @@ struct GpLevel {
     int8_t pre_buf;    // prefix operand: buffer slot, or -1 for N(v[pre_list])
     int8_t pre_list;
     int8_t last_list;  // -1 when the last level reads `list` or `buf`
-    int8_t pad[3];
+    int8_t cut_done;   // `buf` was built with all of this level's cuts
+    int8_t pad[2];
 };
 
 // One nonempty subset M of the IEP inner levels: how |∩_{j in M} S_j| is

@@ -599,6 +599,10 @@ int compile_plan(const Pattern& p, const Perm& order, Rel r, GpPlanDesc* out, Re
             L.last_list = int8_t(h);
         }
     }
+    for (int i = 1; i < k; ++i) {
+        GpLevel& L = d.lv[i];
+        L.cut_done = L.buf >= 0 && slots[L.buf].first.h == hi[i] && slots[L.buf].first.l == lo[i];
+    }
     if (builds.size() > GP_DESC_MAX_BUILDS) return GP_ERR_UNSUPPORTED;
     std::stable_sort(builds.begin(), builds.end(),
                      [](const GpBuild& a, const GpBuild& b) { return a.h < b.h; });

@@ -201,15 +201,11 @@ __device__ __forceinline__ int32_t lower_bound_group(const Group<G>& g, const in
     return base;
 }
 
-// Group-cooperative dst = A ∩ B (both already cut to the wanted range).
+// Group-cooperative dst = A ∩ B ∩ [lo, hi), walking a and testing in b.
 // Returns the number of elements written (the same in every lane).
 template <int G>
-__device__ __forceinline__ int32_t intersect_into(const Group<G>& g, Set a, Set b, int32_t* dst) {
-    if (a.n > b.n) {
-        Set t = a;
-        a = b;
-        b = t;
-    }
+__device__ __forceinline__ int32_t intersect_into(const Group<G>& g, Set a, Set b, int32_t lo, int32_t hi,
+                                                  int32_t* dst) {
     int32_t out = 0;
     for (int32_t base = 0; base < a.n; base += G) {
         int32_t i = base + g.gl;
@@ -217,7 +213,7 @@ __device__ __forceinline__ int32_t intersect_into(const Group<G>& g, Set a, Set 
         int32_t x = 0;
         if (i < a.n) {
             x = a.p[i];
-            found = member(b, x);
+            found = x >= lo && x < hi && member(b, x);
         }
         uint64_t m = g.ballot(found);
         if (found) dst[out + (int32_t)g.below_mask_count(m)] = x;
