@@ -243,9 +243,9 @@ gp_status gp_load_graph_opts(const int64_t* row_ptr, const int32_t* col, int64_t
         st = triangle_desc(&tri);
         if (st == GP_OK) {
             gpint::LaunchCfg cfg;
-            cfg.group = 16;
-            cfg.waves_per_cu = 16;
-            cfg.chunk = 256;
+            cfg.group = 64;
+            cfg.waves_per_cu = 32;
+            cfg.chunk = 64;
             cfg.leaf = 1;
             uint64_t t = 0;
             st = count_to_host(g, tri, cfg, s, nullptr, &t);

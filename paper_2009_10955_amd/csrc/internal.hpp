@@ -27,7 +27,7 @@ struct DeviceGraph {
     int64_t upper_pref[32] = {};  // roots_upper entries with v0 < 2^i
     int32_t* new_id = nullptr;    // original id -> layout id
     uint32_t* hub_bits = nullptr; // dense neighbor bitmaps of vertices [0, n_hubs)
-    int64_t hub_words = 0;        // uint32 words per bitmap = ceil(n / 32)
+    int64_t hub_words = 0;        // uint32 words per bitmap: up to the last vertex with a neighbor
     int32_t n_hubs = 0;
     int64_t max_deg = 0;          // largest degree
     int64_t deg2 = 0;             // second largest degree (bound on any |N(a) & N(b)|, a != b)
