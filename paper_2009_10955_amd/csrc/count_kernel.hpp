@@ -478,10 +478,11 @@ __device__ __forceinline__ bool run_builds(const GpPlanDesc& d, const Ctx<G>& c,
     return true;
 }
 
-// Count of the last level for bound values v[0..K-2], by one lane.
+// Count of the last level for bound values v[0..K-2], by one lane. at: index of
+// v[K-2] in its level's whole candidate set (used where GpLevel::pre_below).
 template <int K, int G, int MODE>
 __device__ __forceinline__ uint32_t leaf_serial(const GpPlanDesc& d, const Ctx<G>& c,
-                                                const int32_t (&v)[K]) {
+                                                const int32_t (&v)[K], int32_t at = 0) {
     const GpLevel& lv = d.lv[K - 1];
     int32_t lo, hi;
     bounds<K>(lv.hi_src, lv.lo_src, v, lo, hi);
@@ -508,6 +509,18 @@ __device__ __forceinline__ uint32_t leaf_serial(const GpPlanDesc& d, const Ctx<G
     // image are not counted
     const uint32_t inj = lv.inj;
     auto skip = [&](int32_t x) { return inj_hit<K>(inj, v, x); };
+    if (lv.pre_below) {
+        // the cliques: the part of A below v[K-2], with no search for where it
+        // ends, tested in N(v[K-2]); B is cut by being tested
+        A.n = at;
+        if (B.bits) {
+            if constexpr (MODE == MODE_ACCOUNT) *c.bytes += 8ull * (uint64_t)A.n;
+            return count_bits(A, B.bits, skip);
+        }
+        if (B.n <= A.n) B = trim(B, lo, hi);
+        if constexpr (MODE == MODE_ACCOUNT) *c.bytes += serial_isect_bytes(A, B);
+        return intersect_count_serial(A, B, skip);
+    }
     // a hub operand is tested by bits, so only the other operand is cut; a
     // short list is range-tested element by element instead of cut
     if (B.bits && A.n <= kShortList && A.n * 4 <= B.n) {
@@ -888,7 +901,8 @@ __device__ void flat_leaf(const GpPlanDesc& d, const Ctx<G>& c, const int32_t (&
                 w[L] = ox;
                 if (!inj_hit<K>(l2.inj, w, y)) {
                     w[K - 2] = y;
-                    add_count(acc, leaf_serial<K, G, MODE>(d, c, w), carry);
+                    // pre_below sets are cut at their build: op is the whole buffer
+                    add_count(acc, leaf_serial<K, G, MODE>(d, c, w, item - oex), carry);
                 }
             }
         }
@@ -1415,7 +1429,9 @@ __device__ void search(const GpPlanDesc& d, const Ctx<G>& c, int32_t (&v)[K], ui
 #pragma unroll
                             for (int j = 0; j < K; ++j) w[j] = v[j];
                             w[K - 2] = x;
-                            add_count(acc, leaf_serial<K, G, MODE>(d, c, w), carry);
+                            // in a split task's slice the index steps by its ways
+                            const int32_t at = L == 2 && c.sJ > 1 ? c.sj + i * st : i;
+                            add_count(acc, leaf_serial<K, G, MODE>(d, c, w, at), carry);
                         }
                     }
                 }

@@ -145,38 +145,7 @@ __device__ void list_last(const GpPlanDesc& d, const gpcount::Ctx<G>& c, const L
     }
 }
 
-// The last level for one lane's own bound values w[0..K-2], by that lane
-// alone: the number of embeddings (count pass).
-template <int K>
-__device__ uint32_t last_count(const GpPlanDesc& d, const gpcount::Ctx<G>& c, const int32_t (&w)[K]) {
-    const GpLevel& lv = d.lv[K - 1];
-    int32_t lo, hi;
-    gpcount::bounds<K>(lv.hi_src, lv.lo_src, w, lo, hi);
-    uint32_t n = 0;
-    if (lv.last_list < 0) {
-        const Set S = trim(lv.list >= 0 ? c.nbr(gpcount::pick<K>(w, lv.list)) : c.buf(lv.buf), lo, hi);
-        for (int32_t i = 0; i < S.n; ++i) {
-            const int32_t x = S.p[i];
-            n += !gpcount::inj_hit<K>(lv.inj, w, x);
-        }
-    } else {
-        Set A = trim(lv.pre_buf >= 0 ? c.buf(lv.pre_buf) : c.nbr(gpcount::pick<K>(w, lv.pre_list)), lo, hi);
-        Set B = trim(c.nbr(gpcount::pick<K>(w, lv.last_list)), lo, hi);
-        if (A.n > B.n) {
-            const Set t = A;
-            A = B;
-            B = t;
-        }
-        for (int32_t i = 0; i < A.n; ++i) {
-            const int32_t x = A.p[i];
-            n += member(B, x) && !gpcount::inj_hit<K>(lv.inj, w, x);
-        }
-    }
-    return n;
-}
-
-// Write pass of last_count: every lane walks its own last level one candidate
-// per step, and a ballot per step places the step's embeddings at rows pos,
+// Write pass: every lane walks its own last level one candidate per step, and a ballot per step places the step's embeddings at rows pos,
 // pos + 1, ... in lane order (one walk, no count first). Lanes without a
 // binding (have false) only join the ballots.
 template <int K>
@@ -223,7 +192,7 @@ __device__ void list_search(const GpPlanDesc& d, const gpcount::Ctx<G>& c, const
         int32_t lo, hi;
         gpcount::bounds<K>(lv.hi_src, lv.lo_src, v, lo, hi);
         Set S = lv.list >= 0 ? c.nbr_u(gpcount::pick<K>(v, lv.list)) : c.buf_u(lv.buf);
-        S = gpcount::trim_u<G>(S, lo, hi);
+        if (!lv.cut_done) S = gpcount::trim_u<G>(S, lo, hi);
         for (int32_t base = 0; base < S.n; base += G) {
             const int32_t i = base + c.g.gl;
             int32_t w[K];
@@ -237,7 +206,7 @@ __device__ void list_search(const GpPlanDesc& d, const gpcount::Ctx<G>& c, const
             if constexpr (WRITE) {
                 last_lockstep<K>(d, c, a, w, have, pos, st);
             } else {
-                const uint32_t mine = have ? last_count<K>(d, c, w) : 0u;
+                const uint32_t mine = have ? gpcount::leaf_serial<K, G, gpcount::MODE_PLAIN>(d, c, w, i) : 0u;
                 pos += c.g.sum(mine);
             }
         }
@@ -246,7 +215,7 @@ __device__ void list_search(const GpPlanDesc& d, const gpcount::Ctx<G>& c, const
         int32_t lo, hi;
         gpcount::bounds<K>(lv.hi_src, lv.lo_src, v, lo, hi);
         Set S = lv.list >= 0 ? c.nbr_u(gpcount::pick<K>(v, lv.list)) : c.buf_u(lv.buf);
-        S = gpcount::trim_u<G>(S, lo, hi);
+        if (!lv.cut_done) S = gpcount::trim_u<G>(S, lo, hi);
         for (int32_t t = 0; t < S.n; ++t) {
             const int32_t x = gpcount::uni<G>(S.p[t]);
             if (gpcount::inj_hit<K>(lv.inj, v, x)) continue;

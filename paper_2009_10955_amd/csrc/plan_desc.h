@@ -52,7 +52,11 @@ struct GpLevel {
     int8_t pre_list;
     int8_t last_list;  // -1 when the last level reads `list` or `buf`
     int8_t cut_done;   // `buf` was built with all of this level's cuts
-    int8_t pad[2];
+    // the last level: `pre_buf` is the previous level's `buf`, built with every
+    // cut but "below the previous vertex", so what is left of it below the
+    // buffer's i-th element are its first i elements
+    int8_t pre_below;
+    int8_t pad;
 };
 
 // One nonempty subset M of the IEP inner levels: how |∩_{j in M} S_j| is

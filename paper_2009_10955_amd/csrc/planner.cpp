@@ -603,6 +603,12 @@ int compile_plan(const Pattern& p, const Perm& order, Rel r, GpPlanDesc* out, Re
         GpLevel& L = d.lv[i];
         L.cut_done = L.buf >= 0 && slots[L.buf].first.h == hi[i] && slots[L.buf].first.l == lo[i];
     }
+    if (k >= 4 && d.lv[k - 1].pre_buf >= 0 && d.lv[k - 1].last_list == k - 2 && !iep) {
+        const int b = d.lv[k - 1].pre_buf;
+        const unsigned prev = 1u << (k - 2);
+        d.lv[k - 1].pre_below = d.lv[k - 2].buf == b && d.lv[k - 2].cut_done && (hi[k - 1] & prev) && lo[k - 1] == 0 &&
+                                slots[b].first.l == 0 && slots[b].first.h == (hi[k - 1] & ~prev);
+    }
     if (builds.size() > GP_DESC_MAX_BUILDS) return GP_ERR_UNSUPPORTED;
     std::stable_sort(builds.begin(), builds.end(),
                      [](const GpBuild& a, const GpBuild& b) { return a.h < b.h; });
