@@ -784,12 +784,13 @@ __device__ __forceinline__ void iep_operands(const Ctx<G>& c, const GpIepTerm& t
     p.memo = nullptr;
     p.tag = 0;
     p.A = p.B = p.E1 = p.E2 = Set{nullptr, 0, nullptr};
+    // in every lane, active or not: the group's walks test their elements in them
+    if (t.n_op > 2) p.E1 = iep_operand<K, G>(c, w, t.op[1]);
+    if (t.n_op > 3) p.E2 = iep_operand<K, G>(c, w, t.op[2]);
     if (!active) return;
     p.A = iep_operand<K, G>(c, w, t.op[0]);
     if (t.n_op < 2) return;
     p.B = iep_operand<K, G>(c, w, t.op[t.n_op - 1]);
-    if (t.n_op > 2) p.E1 = iep_operand<K, G>(c, w, t.op[1]);
-    if (t.n_op > 3) p.E2 = iep_operand<K, G>(c, w, t.op[2]);
     if (t.memo) {
         const int32_t a = pick<K>(w, t.op[0]);
         p.memo = iep_memo_word<G>(c, a, pick<K>(w, t.op[1]));
