@@ -266,14 +266,28 @@ void pool_drop_graph(int device) {
     if (--g_pool_graphs[device] == 0 && g_pool[device]) (void)hipMemPoolTrimTo(g_pool[device], 0);
 }
 
+// Plans whose search ends at the root edge: lanes take different root edges.
+static bool lanes_take_roots(const GpPlanDesc& d) { return d.k <= 3 || d.iep == d.k - 2; }
+
+// Tasks per grab of a launch: at least one per lane where lanes take root edges.
+static int32_t grab_tasks_of(const GpPlanDesc& d, const LaunchCfg& cfg, int group) {
+    return lanes_take_roots(d) ? std::max(cfg.chunk, group) : cfg.chunk;
+}
+
 LaunchCfg default_launch(const GpPlanDesc& d) {
     LaunchCfg cfg;
-    cfg.group = 64;
+    // Plain searches run widest on 16 lanes: their sets are short, and four paths
+    // per wavefront hide each other's loads. 64 and 16 lanes: R-MAT 19 4-clique 3.0
+    // and 2.2 ms, R-MAT 17 diamond 4.8 and 2.8, 5-clique (model plan) 10.2 and 6.3,
+    // Chung-Lu 7000 prism 268 and 121, 5-wheel 74 and 36, house 13.3 and 7.1.
+    // Where lanes take root edges, and with inclusion-exclusion (lanes take the
+    // last outer level), the width of a wavefront.
+    cfg.group = d.k >= 4 && !d.iep ? 16 : 64;
     cfg.waves_per_cu = 32;
     // where lanes take different root edges (k <= 3, or IEP over every level
     // after the root) a grab fills the lanes of a group: the 4-star with IEP on
     // R-MAT (91K vertices, 907K edges) takes 116 ms at 4 per grab, 0.13 at 64
-    cfg.chunk = d.k <= 3 || d.iep == d.k - 2 ? 64 : 4;
+    cfg.chunk = lanes_take_roots(d) ? 64 : 4;
     cfg.leaf = 1;
     cfg.split_ways = 16;
     cfg.split_vertices = 256;
@@ -298,7 +312,7 @@ int resident_waves_per_cu(const DeviceGraph& g, const GpPlanDesc& d, const Launc
 int64_t xcd_block_tasks(const DeviceGraph& g, const LaunchCfg& cfg, int group) {
     (void)g;
     (void)group;
-    if (cfg.xcd <= 0) return 0;  // the default: one cursor (measured faster)
+    if (cfg.xcd <= 0) return 0;  // the default: one task order for the device (measured faster)
     const int64_t chunk = std::max(1, cfg.chunk);
     return (cfg.xcd + chunk - 1) / chunk * chunk;
 }
@@ -416,7 +430,7 @@ gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCf
     const int waves_per_block = kBlock / 64;
     int64_t blocks = std::max<int64_t>(1, (int64_t)g.num_cus * cfg.waves_per_cu / waves_per_block);
     int64_t groups_per_block = kBlock / group;
-    int32_t chunk = cfg.chunk;
+    int32_t chunk = grab_tasks_of(d, cfg, group);
     if (table) {
         groups_per_block = tab_waves;
         blocks = table_blocks(g, d, cfg.waves_per_cu, n_roots);
@@ -431,6 +445,10 @@ gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCf
     if (per_block > 0) {
         if (ws && per_block > budget) return GP_ERR_NOMEM;  // not even one block's buffers fit
         blocks = std::min(blocks, std::max<int64_t>(1, budget / per_block));
+        // within what the pool keeps, if that leaves half the grid: memory beyond
+        // it is freed after the call, and the driver clears it at 24 GB/s
+        const int64_t kept = std::max<int64_t>(1, (int64_t)kPoolKeepBytes * 7 / 8 / per_block);
+        if (!ws && 2 * kept >= blocks) blocks = std::min(blocks, kept);
     }
     // a grid larger than the number of root tasks only adds idle groups
     int64_t need = (n_tasks + chunk - 1) / chunk;
@@ -496,7 +514,9 @@ gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCf
     a.memo = memo;
     a.chunk = chunk;
     a.memo_ways_log2 = std::max(iep_log2, 0);
-    a.xcd_block = xcd_block_tasks(g, cfg, group);
+    LaunchCfg grab = cfg;
+    grab.chunk = chunk;
+    a.xcd_block = xcd_block_tasks(g, grab, group);
     if (n_tasks > 0)
         hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(table ? tab_waves * 64 : kBlock), 0, stream, d, a);
     // a sample's total need not be a multiple of the over-count: its quotient
@@ -595,7 +615,7 @@ static void batch_shape(const GpPlanDesc& d, const LaunchCfg& c, int min_group, 
     if (d.iep) bp->group = want >= 64 ? 64 : 32;
     else bp->group = want >= 64 ? 64 : (want >= 32 ? 32 : (want >= 16 ? 16 : 8));
     bp->leaf = d.iep ? 1 : (c.leaf == 3 || c.leaf == 4 ? c.leaf : 1);
-    bp->chunk = std::max(1, c.chunk);
+    bp->chunk = std::max(1, grab_tasks_of(d, c, bp->group));
 }
 
 int batch_shape_key(const GpPlanDesc& d, const LaunchCfg& c, int min_group) {

@@ -192,7 +192,7 @@ gp_status check_sum(const uint64_t* values, int64_t n, uint64_t div, hipStream_t
 // synchronisation, 0.06 ms a call for small launches and 0.3 ms from 256 MiB
 // on), and gives everything back when the last graph on the GPU is freed.
 // Under stream capture the allocation is hipMallocAsync's graph node.
-constexpr uint64_t kPoolKeepBytes = uint64_t(1) << 30;
+constexpr uint64_t kPoolKeepBytes = uint64_t(4) << 30;
 hipError_t pool_malloc(void** p, size_t bytes, hipStream_t stream);
 void pool_add_graph(int device);   // a graph now lives on the device
 void pool_drop_graph(int device);  // it is gone (its work has finished)

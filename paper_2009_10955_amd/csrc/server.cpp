@@ -421,10 +421,8 @@ void worker_main(gp_server* S) {
                 const int64_t c = std::min(q->slice, q->n_tasks - q->launched);
                 descs.push_back(q->plan->desc);
                 cfgs.push_back(lcfg);
-                // lanes take different root edges: a grab fills them
-                if (q->plan->desc.k <= 3 || q->plan->desc.iep == q->plan->desc.k - 2) cfgs.back().chunk = 64;
                 // a slice of fewer tasks than fill the device at the usual grab
-                else cfgs.back().chunk = (int)std::max<int64_t>(1, std::min<int64_t>(lcfg.chunk, c / kSliceGrabs));
+                cfgs.back().chunk = (int)std::max<int64_t>(1, std::min<int64_t>(lcfg.chunk, c / kSliceGrabs));
                 offs.push_back(q->launched);
                 L.qs.push_back(q);
                 L.slices.push_back(c);

@@ -316,7 +316,8 @@ gp_status gp_plan_tune(const gp_graph* g, const gp_plan* p, const gp_tune_opts* 
 
         // 2. sample stride: the planner's configuration gives the work; the
         //    sample keeps a balanced share of about 8 ms of it
-        const gpint::LaunchCfg base = gpint::default_launch(p->desc);
+        gpint::LaunchCfg base = gpint::default_launch(p->desc);
+        base.group = 64;  // the widths are tried from the widest on
         int64_t stride = o.sample_stride;
         if (stride <= 0) {
             const int64_t roots = std::max<int64_t>(1, gpint::root_task_count(g->dg, p->desc));
