@@ -78,7 +78,7 @@ typedef struct {
     uint64_t hash;        /* 64-bit content hash of the input CSR (cache key) */
     double load_seconds;  /* wall time of gp_load_graph */
     int64_t hub_vertices; /* vertices with a dense neighbor bitmap (the highest-degree ones) */
-    int64_t hub_bitmap_bytes;
+    int64_t hub_bitmap_bytes; /* their size: one bit per vertex up to the last with a neighbor */
 } gp_stats;
 
 /*
@@ -90,9 +90,9 @@ typedef struct {
  * On the device the graph is validated (GP_ERR_CSR_* on failure), relabelled
  * by descending degree (ties by ascending id), each list re-sorted, and its
  * triangle count computed for the cost model. The highest-degree vertices
- * (degree >= 64, at most 8 GiB in total) also get a dense n-bit neighbor
- * bitmap, so that a membership test in their lists is one bit read. Blocking
- * on `stream`.
+ * (degree >= 64, at most 8 GiB in total) also get a dense neighbor bitmap
+ * (a bit per vertex that has neighbors), so that a membership test in their
+ * lists is one bit read. Blocking on `stream`.
  */
 gp_status gp_load_graph(const int64_t* row_ptr, const int32_t* col, int64_t n, int64_t nnz,
                         uint32_t flags, void* stream, gp_graph** out);
@@ -103,7 +103,8 @@ typedef struct {
     int64_t hub_min_degree;    /* vertices of at least this degree get a dense neighbor bitmap
                                   (0 = 64) */
     int64_t hub_budget_bytes;  /* bitmaps of at most this many bytes in total, highest degrees
-                                  first (0 = 8 GiB); each takes ceil(n/32) * 4 bytes */
+                                  first (0 = 8 GiB), each counted as ceil(n/32) * 4 bytes
+                                  (isolated vertices, last in the layout, take none) */
 } gp_load_opts;
 
 void gp_load_opts_default(gp_load_opts* o);
@@ -134,7 +135,9 @@ typedef struct {
     int32_t group;         /* lanes that share one search path: 64, 32, 16 or 8 (0 = auto) */
     int32_t waves_per_cu;  /* resident wavefronts per compute unit for the persistent grid
                               (0 = auto) */
-    int32_t chunk;         /* root tasks taken per queue grab (0 = auto) */
+    int32_t chunk;         /* root tasks taken per queue grab (0 = auto; at least a group's lanes
+                              where these take different root edges: k <= 3, or
+                              inclusion-exclusion over every level after the root) */
     int32_t leaf_mode;     /* 0 auto, 1: lanes take different second-to-last candidates and
                               count the last level alone, 2: the group counts each one together,
                               3: the last two enumerated levels are flattened into one
@@ -151,16 +154,16 @@ typedef struct {
                               layout is below split_vertices, rounded down to a power of
                               two (0 = auto) */
     int32_t xcd_tasks;     /* task order over the XCDs, each with its own L2 (0 = the
-                              plan's own, one cursor unless set): > 0 deals the task space
-                              to the 8 XCDs in blocks of this many tasks (rounded up to a
+                              plan's own, one order for the device unless set): > 0 deals
+                              the task space to the 8 XCDs in blocks of this many tasks (rounded up to a
                               multiple of chunk), so one XCD's groups work on neighbouring
                               root edges, which share their hub endpoint; an XCD that runs
-                              out helps the others. -1: one task cursor for the whole
+                              out helps the others. -1: one task order for the whole
                               device (all XCDs walk the same stretch of root edges, which
                               the shared last-level cache then holds once) */
     int32_t batch_runs;    /* batches (gp_count_batch, gp_batch_create): 0 or 1 = consecutive
                               plans of one launch shape and pattern size share one persistent
-                              launch with a task cursor each; 2 = every plan gets its own
+                              launch with a task queue each; 2 = every plan gets its own
                               launch in the batch (a plan over its whole task space then
                               runs as gp_count would). gp_batch_tune measures both */
 } gp_launch;
@@ -313,10 +316,14 @@ void gp_free_plan(gp_plan* p);
  * Count the embeddings of plan p in graph g (exact, unsigned 64-bit).
  * One persistent kernel launch on `stream`: wavefront groups take root edges
  * (the first two schedule levels) from an atomic queue and search the
- * remaining levels depth first. Blocking: synchronises `stream` and writes
- * *out on the host. GP_ERR_OVERFLOW if the count does not fit in 64 bits.
+ * remaining levels depth first; a plan whose last level depends on the root and
+ * one more vertex only may instead run blocks of wavefronts on one root edge
+ * with a table in LDS (then group, chunk, leaf_mode and the splits play no part).
+ * Blocking: synchronises `stream` and writes *out on the host. GP_ERR_OVERFLOW if
+ * the count does not fit in 64 bits.
  * `launch` may be null (auto). Device memory, allocated stream-ordered per
- * call and freed at its end: the groups' candidate buffers (at most 16 GiB;
+ * call from a pool that keeps at most 8 GiB per GPU between calls, until the last
+ * graph on the GPU is freed: the groups' candidate buffers (at most 16 GiB;
  * the grid shrinks to fit) and, for plans that can use one, a memo table
  * (leaf mode 4: a word per hub per group, at most 4 GiB; inclusion-exclusion:
  * one table for the launch, at most 2 GiB). GP_ERR_NOMEM when an
@@ -435,7 +442,7 @@ gp_status gp_estimate(const gp_graph* g, const gp_plan* p, const gp_launch* laun
 /*
  * Count several plans (1..64, any pattern sizes, counted plainly or with
  * IEP) over one graph together (Section IV-E's task partitioning, across
- * patterns). Every plan keeps its own task cursor and its own launch shape:
+ * patterns). Every plan keeps its own task queue and its own launch shape:
  * lanes per group (64, 32, 16 or 8; IEP plans 64 or 32), leaf mode (1, 3 or
  * 4 where the plan allows it) and tasks per grab come from the plan's launch
  * (its tuned one after gp_plan_tune), with every non-zero field of `launch`

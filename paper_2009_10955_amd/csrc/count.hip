@@ -243,13 +243,15 @@ hipMemPool_t device_pool(int device) {
 }  // namespace
 
 hipError_t pool_malloc(void** p, size_t bytes, hipStream_t stream) {
+    size_t size = size_t(64) << 10;
+    while (size < bytes && size < kPoolMostBytes) size *= 2;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     int dev = -1;
     hipMemPool_t pool = nullptr;
-    if (hipStreamIsCapturing(stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone &&
+    if (bytes <= size && hipStreamIsCapturing(stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone &&
         hipGetDevice(&dev) == hipSuccess)
         pool = device_pool(dev);
-    if (pool && hipMallocFromPoolAsync(p, bytes, pool, stream) == hipSuccess) return hipSuccess;
+    if (pool && hipMallocFromPoolAsync(p, size, pool, stream) == hipSuccess) return hipSuccess;
     (void)hipGetLastError();  // the default pool decides
     return hipMallocAsync(p, bytes, stream);
 }
@@ -442,12 +444,19 @@ gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCf
     // resident groups if needed
     const int64_t budget = ws ? (int64_t)ws->bytes - (int64_t)kQueueBytes : int64_t(16) << 30;
     if (ws && budget < 0) return GP_ERR_ARG;
+    // the memo that the launch may use (below): one for all of it, or a word per
+    // hub in every group
+    const bool leaf4_memo = cfg.leaf == 4 && !table && mode != MODE_PER_ROOT && !iep && memo_eligible(d) &&
+                            n_tasks < (int64_t(1) << 31);
+    const bool iep_memo = iep && iep_memo_eligible(d);
     if (per_block > 0) {
         if (ws && per_block > budget) return GP_ERR_NOMEM;  // not even one block's buffers fit
         blocks = std::min(blocks, std::max<int64_t>(1, budget / per_block));
-        // within what the pool keeps, if that leaves half the grid: memory beyond
-        // it is freed after the call, and the driver clears it at 24 GB/s
-        const int64_t kept = std::max<int64_t>(1, (int64_t)kPoolKeepBytes * 7 / 8 / per_block);
+        // within what the pool hands out, if that leaves half the grid: larger
+        // regions are freed after the call, and the driver clears them at 24 GB/s
+        const int64_t l = iep_memo ? iep_memo_log2(g.n_hubs, kIepMemoBytes / 8) : -1;
+        const int64_t room = (int64_t)kPoolMostBytes - (int64_t(1) << 20) - (l >= 0 ? ((int64_t)g.n_hubs * 8) << l : 0);
+        const int64_t kept = room / (per_block + (leaf4_memo ? groups_per_block * (int64_t)g.n_hubs * 8 : 0));
         if (!ws && 2 * kept >= blocks) blocks = std::min(blocks, kept);
     }
     // a grid larger than the number of root tasks only adds idle groups
@@ -460,12 +469,9 @@ gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCf
     // (within what the workspace has left); the IEP memo: one table for the
     // launch, 2^l words per hub, within 2 GiB (or the room left)
     const int64_t memo_cap = ws ? budget - (int64_t)align_up(scratch_bytes) : (int64_t(4) << 30);
-    const int iep_log2 =
-        iep && iep_memo_eligible(d) ? iep_memo_log2(g.n_hubs, std::min(memo_cap, kIepMemoBytes) / 8) : -1;
+    const int iep_log2 = iep_memo ? iep_memo_log2(g.n_hubs, std::min(memo_cap, kIepMemoBytes) / 8) : -1;
     const int64_t memo_words = iep ? (iep_log2 >= 0 ? (int64_t)g.n_hubs << iep_log2 : 0)
                                    : blocks * groups_per_block * (int64_t)g.n_hubs;
-    const bool leaf4_memo = cfg.leaf == 4 && !table && mode != MODE_PER_ROOT && !iep && memo_eligible(d) &&
-                            n_tasks < (int64_t(1) << 31);
     const bool use_memo = (leaf4_memo || iep_log2 >= 0) && g.n_hubs > 0 && memo_words * 8 <= memo_cap;
 
     int32_t* scratch = nullptr;
@@ -939,6 +945,7 @@ gp_status arena_launch(const DeviceGraph& g, BatchArena* ar, const GpPlanDesc* d
     if (b.use_memo) room = std::min(room, ar->slots_cap);
     int64_t slots = 0;
     for (BatchRun& r : b.runs) {
+        r.table = r.table && room >= r.tab_waves;  // else no block's buffers fit
         const int64_t per_block = r.table ? r.tab_waves : (kBlock / 64) * (64 / r.group);
         r.blocks = r.table ? table_blocks(g, descs[r.p0], std::min(ar->waves_per_cu, r.waves_per_cu),
                                           std::max<int64_t>(1, r.n_roots))

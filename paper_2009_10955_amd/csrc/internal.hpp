@@ -47,13 +47,13 @@ struct LaunchCfg {
     int64_t split_vertices = 0;
     double budget_ms = 0;  // time limit per wavefront (measurement only; 0: none)
     // tasks per XCD block (the task space dealt to the XCDs in blocks); 0 or
-    // -1: one cursor for the device
+    // -1: one task order for the device
     int64_t xcd = 0;
     int batch_runs = 0;  // batches: 2 = every plan its own launch
 };
 
 // Tasks per XCD block of a launch: cfg.xcd rounded up to a multiple of the
-// grab, or 0 for one cursor (the default).
+// grab, or 0 for one task order (the default).
 int64_t xcd_block_tasks(const DeviceGraph& g, const LaunchCfg& cfg, int group);
 
 // Device memory a launch may use instead of allocating its own: the queue
@@ -189,10 +189,16 @@ gp_status check_sum(const uint64_t* values, int64_t n, uint64_t div, hipStream_t
 // Stream-ordered device memory of a call (hipFreeAsync returns it). It comes
 // from a pool of the library's own per GPU that keeps up to kPoolKeepBytes
 // between calls (the default pool keeps nothing: it unmaps at every
-// synchronisation, 0.06 ms a call for small launches and 0.3 ms from 256 MiB
-// on), and gives everything back when the last graph on the GPU is freed.
-// Under stream capture the allocation is hipMallocAsync's graph node.
-constexpr uint64_t kPoolKeepBytes = uint64_t(4) << 30;
+// synchronisation, 0.06 ms a call for small launches, and the driver clears
+// what is given back at 24 GB/s), and gives everything back when the last graph
+// on the GPU is freed. Sizes are rounded up to powers of two, so that calls
+// of different sizes find each other's blocks: with exact sizes and 4 GiB kept,
+// a 4-clique listing on R-MAT 16 took 5.8 ms after an R-MAT 19 count, whose 3.5 GiB
+// stood idle in the pool, and 1.9 alone; kPoolKeepBytes holds one block of every
+// size up to kPoolMostBytes. Larger requests, and all under stream capture
+// (there a graph node), are plain hipMallocAsync.
+constexpr uint64_t kPoolMostBytes = uint64_t(4) << 30;
+constexpr uint64_t kPoolKeepBytes = 2 * kPoolMostBytes;
 hipError_t pool_malloc(void** p, size_t bytes, hipStream_t stream);
 void pool_add_graph(int device);   // a graph now lives on the device
 void pool_drop_graph(int device);  // it is gone (its work has finished)
