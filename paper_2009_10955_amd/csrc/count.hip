@@ -285,6 +285,7 @@ LaunchCfg default_launch(const GpPlanDesc& d) {
     // Where lanes take root edges, and with inclusion-exclusion (lanes take the
     // last outer level), the width of a wavefront.
     cfg.group = d.k >= 4 && !d.iep ? 16 : 64;
+    cfg.own_group = true;
     cfg.waves_per_cu = 32;
     // where lanes take different root edges (k <= 3, or IEP over every level
     // after the root) a grab fills the lanes of a group: the 4-star with IEP on
@@ -321,7 +322,10 @@ int64_t xcd_block_tasks(const DeviceGraph& g, const LaunchCfg& cfg, int group) {
 
 LaunchCfg apply_launch(LaunchCfg cfg, const gp_launch* l) {
     if (l) {
-        if (l->group) cfg.group = l->group;
+        if (l->group) {
+            cfg.group = l->group;
+            cfg.own_group = false;
+        }
         if (l->waves_per_cu) cfg.waves_per_cu = l->waves_per_cu;
         if (l->chunk) cfg.chunk = l->chunk;
         if (l->leaf_mode) cfg.leaf = l->leaf_mode;
@@ -333,6 +337,13 @@ LaunchCfg apply_launch(LaunchCfg cfg, const gp_launch* l) {
         if (l->batch_runs) cfg.batch_runs = l->batch_runs;
     }
     return cfg;
+}
+
+void settle_group(const DeviceGraph& g, const GpPlanDesc& d, LaunchCfg* cfg, int64_t room) {
+    if (!cfg->own_group || cfg->group >= 64) return;
+    const int64_t most = (int64_t)g.num_cus * cfg->waves_per_cu * (64 / cfg->group);
+    const int64_t groups = std::min(most, root_task_count(g, d) / std::max(1, cfg->chunk) + 1);
+    if (groups * d.nbuf * std::max<int64_t>(1, g.deg2) * 4 > room) cfg->group = 64;
 }
 
 static const int2* pick_roots(const DeviceGraph& g, int root_cut, int64_t* n) {
@@ -399,18 +410,26 @@ constexpr size_t kQueueBytes = sizeof(unsigned long long) * kQueueWords;  // a m
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 }  // namespace
 
-gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCfg& cfg,
+gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCfg& launch,
                        hipStream_t stream, unsigned long long* result_dev,
                        unsigned long long* per_root, bool account, unsigned long long* busy,
                        const Workspace* ws, unsigned long long* result_host) {
+    // keep scratch within a fixed budget (or the caller's workspace): fewer
+    // resident groups if needed
+    const int64_t budget = ws ? (int64_t)ws->bytes - (int64_t)kQueueBytes : int64_t(16) << 30;
+    if (ws && budget < 0) return GP_ERR_ARG;
+    LaunchCfg cfg = launch;
+    if (ws) settle_group(g, d, &cfg, budget);
     if (cfg.group != 64 && cfg.group != 32 && cfg.group != 16 && cfg.group != 8) return GP_ERR_ARG;
     if (cfg.leaf < 1 || cfg.leaf > 4) return GP_ERR_ARG;
     if (cfg.waves_per_cu < 1 || cfg.waves_per_cu > 32 || cfg.chunk < 1) return GP_ERR_ARG;
     const int mode = account ? MODE_ACCOUNT : (per_root ? MODE_PER_ROOT : MODE_PLAIN);
     const bool iep = d.iep != 0;
     const int group = iep ? (cfg.group >= 64 ? 64 : 32) : cfg.group;  // IEP kernels: 64 or 32 lanes
-    const bool table = table_rule(g, d, mode);
     const int tab_waves = table_waves(g, d);
+    const int64_t cap = std::max<int64_t>(1, g.deg2);
+    // the table kernel, unless a workspace has no room for its larger blocks
+    const bool table = table_rule(g, d, mode) && tab_waves * d.nbuf * cap * 4 <= budget;
     KernelFn fn = table ? pick_table(d, mode, tab_waves) : pick_kernel(d.k, group, cfg.leaf, mode, d.iep);
     if (!fn) return GP_ERR_UNSUPPORTED;
 
@@ -438,12 +457,7 @@ gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCf
         blocks = table_blocks(g, d, cfg.waves_per_cu, n_roots);
         chunk = table_chunk(d, blocks, n_roots);
     }
-    const int64_t cap = std::max<int64_t>(1, g.deg2);
     const int64_t per_block = d.nbuf > 0 ? groups_per_block * d.nbuf * cap * 4 : 0;
-    // keep scratch within a fixed budget (or the caller's workspace): fewer
-    // resident groups if needed
-    const int64_t budget = ws ? (int64_t)ws->bytes - (int64_t)kQueueBytes : int64_t(16) << 30;
-    if (ws && budget < 0) return GP_ERR_ARG;
     // the memo that the launch may use (below): one for all of it, or a word per
     // hub in every group
     const bool leaf4_memo = cfg.leaf == 4 && !table && mode != MODE_PER_ROOT && !iep && memo_eligible(d) &&

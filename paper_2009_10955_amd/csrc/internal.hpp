@@ -50,6 +50,7 @@ struct LaunchCfg {
     // -1: one task order for the device
     int64_t xcd = 0;
     int batch_runs = 0;  // batches: 2 = every plan its own launch
+    bool own_group = false;  // group is the library's choice (settle_group may widen it)
 };
 
 // Tasks per XCD block of a launch: cfg.xcd rounded up to a multiple of the
@@ -212,6 +213,9 @@ int64_t task_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCfg& c
 // non-zero fields of a caller's gp_launch.
 LaunchCfg default_launch(const GpPlanDesc& d);
 LaunchCfg apply_launch(LaunchCfg cfg, const gp_launch* l);
+// Widens a group that the library chose to 64 lanes where the grid's candidate
+// buffers exceed room bytes: as many paths then fit, each on more lanes.
+void settle_group(const DeviceGraph& g, const GpPlanDesc& d, LaunchCfg* cfg, int64_t room);
 
 }  // namespace gpint
 

@@ -36,8 +36,10 @@ int64_t odd_stride(int64_t s) {
 namespace gpint {
 
 LaunchCfg launch_for_plan(const gp_plan* p, const gp_launch* l, const DeviceGraph& g) {
-    (void)g;
-    return apply_launch(p->launch, l);
+    LaunchCfg cfg = apply_launch(p->launch, l);
+    // more than the pool keeps, even at half the grid
+    settle_group(g, p->desc, &cfg, 2 * (int64_t)kPoolMostBytes);
+    return cfg;
 }
 
 gp_status estimate_begin(const DeviceGraph& g, const GpPlanDesc& d, LaunchCfg cfg, double budget_ms,
@@ -318,6 +320,7 @@ gp_status gp_plan_tune(const gp_graph* g, const gp_plan* p, const gp_tune_opts* 
         //    sample keeps a balanced share of about 8 ms of it
         gpint::LaunchCfg base = gpint::default_launch(p->desc);
         base.group = 64;  // the widths are tried from the widest on
+        base.own_group = false;
         int64_t stride = o.sample_stride;
         if (stride <= 0) {
             const int64_t roots = std::max<int64_t>(1, gpint::root_task_count(g->dg, p->desc));

@@ -181,3 +181,24 @@ def test_threads_share_a_graph():
             t.join()
         assert not bad
         graph.close()
+
+
+def test_default_width_fits_the_workspace():
+    """Two hubs over n leaves and a path of r leaf edges: r 4-cliques. Buffers
+    of n ids for a block of 16-lane groups exceed the allocation-free call's
+    workspace, those of 64-lane groups fit: a launch that names no width counts."""
+    import torch
+    n, r = 600_000, 1000
+    leaf = np.arange(2, n + 2)
+    src = np.concatenate([[0], np.zeros(n, np.int64), np.ones(n, np.int64), leaf[:r]])
+    dst = np.concatenate([[1], leaf, leaf, leaf[1:r + 1]])
+    graph = gp.Graph.from_csr(I.csr_from_edges(n + 2, src, dst), device=True)
+    plan = gp.Plan(*P["4-clique"], stats=graph.stats())
+    out = torch.zeros(2, dtype=torch.int64, device="cuda")
+    with pytest.raises(gp.GpError):
+        gp.count_noalloc(graph, plan, out, group=16)
+    gp.count_noalloc(graph, plan, out)
+    torch.cuda.synchronize()
+    assert out.tolist() == [r, 0]
+    assert gp.count(graph, plan) == r
+    graph.close()
