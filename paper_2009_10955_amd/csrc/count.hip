@@ -145,6 +145,15 @@ bool table_rule(const gpint::DeviceGraph& g, const GpPlanDesc& d, int mode) {
            ((ll.hi_src | ll.lo_src) & ~3u) == 0;
 }
 
+// With inclusion-exclusion a table is filled once for all of p's roots, so a sparse
+// sample pays for the fills: taken while the heaviest endpoint keeps 1,024 sampled
+// roots. House with and without the table, every 1st and 7th root of R-MAT 17: 10.4 and
+// 15.6, 4.4 and 3.8 ms; every 60th, 237th and 1,001st of R-MAT 22 (largest degree
+// 95,042): 221 and 504, 144 and 200, 116 and 68 ms.
+bool table_sample(const gpint::DeviceGraph& g, const GpPlanDesc& d, int64_t stride) {
+    return !d.iep || stride <= 1 || stride * 1024 <= g.max_deg;
+}
+
 // Its blocks: 4 wavefronts where a root edge has little work (one level of lanes,
 // k = 4) or the small table covers the graph, else 16: 4-cycle on G(1000, 0.01), a
 // whole call, 76 us with 16 and 54 with 4; 5-cycle on G(5000, 0.004) 0.74 and 0.31 ms.
@@ -298,7 +307,7 @@ LaunchCfg default_launch(const GpPlanDesc& d) {
 }
 
 int resident_waves_per_cu(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCfg& cfg) {
-    if (table_rule(g, d, MODE_PLAIN)) {
+    if (table_rule(g, d, MODE_PLAIN) && table_sample(g, d, cfg.root_stride)) {
         const int w = table_waves(g, d);
         return std::max(1, std::min(cfg.waves_per_cu, d.iep ? 3 * w : 32) / w) * w;
     }
@@ -429,7 +438,8 @@ gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCf
     const int tab_waves = table_waves(g, d);
     const int64_t cap = std::max<int64_t>(1, g.deg2);
     // the table kernel, unless a workspace has no room for its larger blocks
-    const bool table = table_rule(g, d, mode) && tab_waves * d.nbuf * cap * 4 <= budget;
+    const bool table =
+        table_rule(g, d, mode) && table_sample(g, d, cfg.root_stride) && tab_waves * d.nbuf * cap * 4 <= budget;
     KernelFn fn = table ? pick_table(d, mode, tab_waves) : pick_kernel(d.k, group, cfg.leaf, mode, d.iep);
     if (!fn) return GP_ERR_UNSUPPORTED;
 

@@ -57,7 +57,9 @@ double estimate_end(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCfg& 
                     const unsigned long long* h, int64_t stride) {
     if (h[1] & 4ull) return 1e300;  // a wavefront of the sample alone ran past the budget
     const double busy = (double)h[2] / g.wall_khz, chunk = (double)h[4] / g.wall_khz;
-    const double resident = (double)g.num_cus * resident_waves_per_cu(g, d, cfg);
+    LaunchCfg sample = cfg;
+    sample.root_stride = stride;
+    const double resident = (double)g.num_cus * resident_waves_per_cu(g, d, sample);
     return std::max(busy * (double)stride / resident, chunk);
 }
 
@@ -332,7 +334,7 @@ gp_status gp_plan_tune(const gp_graph* g, const gp_plan* p, const gp_tune_opts* 
             Timing t = time_launch(g->dg, p->desc, cfg, s, res);
             if (t.wall < 0) st = GP_ERR_HIP;
             spent += std::max(0.0, t.wall);
-            const double resident = (double)g->dg.num_cus * gpint::resident_waves_per_cu(g->dg, p->desc, base);
+            const double resident = (double)g->dg.num_cus * gpint::resident_waves_per_cu(g->dg, p->desc, cfg);
             const double full_ms = t.busy * (double)s0 / resident;
             stride = std::max<int64_t>(1, (int64_t)(full_ms / 8.0));
             stride = std::min(stride, s0);

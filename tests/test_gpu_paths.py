@@ -183,6 +183,31 @@ def test_threads_share_a_graph():
         graph.close()
 
 
+@pytest.mark.parametrize("stride", [1, 2, 3, 64])
+def test_iep_table_by_sample_stride(stride):
+    """Samples dense enough for the table and samples past that rule, around a hub
+    of 2,400 neighbors: the parts sum to the oracle's count, alone and in a batch."""
+    k, e = P["house"]
+    rng = np.random.default_rng(stride)
+    n = 2500
+    src = np.concatenate([np.zeros(2400, np.int64), rng.integers(0, n, 5000)])
+    dst = np.concatenate([np.arange(1, 2401), rng.integers(0, n, 5000)])
+    g = I.csr_from_edges(n, src, dst)
+    want = O.count(g, k, e)
+    graph = gp.Graph.from_csr(g, device=True)
+    plan = gp.Plan(k, e, stats=graph.stats(), force_order=(0, 1, 2, 3, 4), force_restr=[(1, 0)], iep=True)
+    assert plan.info().iep == 2 and plan.info().iep_div == 1
+    assert sum(gp.count(graph, plan, root_stride=stride, root_offset=o) for o in range(stride)) == want
+    batch = gp.Batch(graph, [plan])
+    total = 0
+    for o in range(stride):
+        batch.set_sample(stride, o)
+        total += batch.run()[0]
+    assert total == want
+    batch.close()
+    graph.close()
+
+
 def test_default_width_fits_the_workspace():
     """Two hubs over n leaves and a path of r leaf edges: r 4-cliques. Buffers
     of n ids for a block of 16-lane groups exceed the allocation-free call's
