@@ -59,6 +59,8 @@ __device__ void run_piece(const BatchArgs& a, const GpPlanDesc& d, const BatchPl
     c.tab = nullptr;
     c.tab_n = 0;
     c.filt = nullptr;
+    c.flat = nullptr;
+    c.starts = nullptr;
     __shared__ uint32_t s_cnt[IEP > 0 ? ((1 << IEP) - 1) * kBlock : 1];
     c.cnt = &s_cnt[IEP > 0 ? threadIdx.x : 0];
     TaskSpace ts;

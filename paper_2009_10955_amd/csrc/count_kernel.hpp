@@ -243,6 +243,8 @@ __device__ __forceinline__ Set trim_u(Set s, int32_t lo, int32_t hi) {
     return Set{s.p + b, e - b, s.bits};
 }
 
+struct FlatRoot;
+
 template <int G>
 struct Ctx {
     const int64_t* row_ptr;
@@ -264,6 +266,8 @@ struct Ctx {
     int32_t tab_n;
     int32_t out;               // leaf mode 5: the root endpoint left out of the table, a neighbor of p (-1: none)
     const uint32_t* filt;      // IEP with the table: N(p) hashed to kFiltWords words of bits in LDS
+    FlatRoot* flat;               // k = 3: 64 edges' walks and the flags of their starts in LDS (null: none)
+    int32_t* starts;
     Group<G> g;
 
     __device__ __forceinline__ bool expired() const {
@@ -1476,6 +1480,107 @@ __device__ __forceinline__ int64_t entry_index(const int64_t* row_ptr, const int
     return b + lower_bound(col + b, (int32_t)(row_ptr[v0 + 1] - b), v1);
 }
 
+// One root edge's last level as roots_flat shares it out: element e of the
+// wavefront's walk is walk[e] for the edge that holds it.
+struct alignas(16) FlatRoot {
+    const int32_t* walk;  // the walked list, moved back by where it starts in the walk
+    const void* test;     // the other list, or its bitmap
+    int32_t test_n;       // the other list's length; -1: a bitmap
+    int32_t lo, hi;       // the level's cut
+    int32_t pad;
+};
+constexpr int kFlatWindows = 4;  // windows of 64 elements in flight
+
+// Last levels N(v0) & N(v1) of 64 root edges (k = 3), one per lane, walked
+// as one list: the wavefront takes 64 elements of all the edges' shorter lists
+// at a time, each lane finding its edge by a count of the lists that start up
+// to its element. One lane per edge waits for the longest list of the 64,
+// several times the mean on a power-law graph, and reads 64 lists at once; here
+// the lanes read runs of a list. What bounds it is the chain from LDS to the
+// element to the bitmap's word, and the first chunk, whose lists are the longest:
+// four windows in flight. Triangles, a whole call, one lane per edge and 1, 2, 4
+// windows: R-MAT 17 (971,517 edges) 159 and 139, 131, 129 us; R-MAT 20 (8.4M) 1,508
+// and 993, 891, 860. Without bitmaps the test is a search per element, and lanes
+// that merge two lists alone are as fast: there the old way stays.
+template <int G, int MODE>
+__device__ __forceinline__ uint32_t roots_flat(const GpPlanDesc& d, const Ctx<G>& c, int32_t v0, int32_t v1,
+                                               bool active) {
+    static_assert(G == 64, "one wavefront");
+    const GpLevel& lv = d.lv[2];
+    FlatRoot me{nullptr, nullptr, 0, 0, 0, 0};
+    int32_t n = 0;
+    if (active) {
+        const int32_t v[3] = {v0, v1, 0};
+        bounds<3>(lv.hi_src, lv.lo_src, v, me.lo, me.hi);
+        Set W = c.nbr(v0), T = c.nbr(v1);
+        if (T.n < W.n) {
+            const Set t = W;
+            W = T;
+            T = t;
+        }
+        if (W.n > kShortList) {
+            if constexpr (MODE == MODE_ACCOUNT) *c.bytes += cut_bytes(W, me.lo, me.hi);
+            W = trim(W, me.lo, me.hi);
+        }
+        n = W.n;
+        if constexpr (MODE == MODE_ACCOUNT) *c.bytes += (uint64_t)n * (4 + test_bytes(T));
+        me.walk = W.p;
+        me.test = T.bits ? (const void*)T.bits : (const void*)T.p;
+        me.test_n = T.bits ? -1 : T.n;
+    }
+    int32_t end = n;  // inclusive scan
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int32_t o = __shfl_up(end, off, 64);
+        if (c.g.gl >= off) end += o;
+    }
+    const int32_t total = uni<64>(__shfl(end, 63, 64));
+    const int32_t start = end - n;
+    const uint64_t full = __ballot(n > 0);
+    group_fence();  // the last call's reads
+    if (n > 0) {
+        me.walk = (const int32_t*)((uintptr_t)me.walk - 4 * (uintptr_t)start);
+        c.flat[(int)__popcll(full & ((1ull << c.g.gl) - 1))] = me;
+    }
+#pragma unroll
+    for (int u = 0; u < kFlatWindows; ++u) c.starts[u * 64 + c.g.gl] = 0;
+    group_fence();
+    uint32_t cnt = 0;
+    int32_t before = -1;  // lists that start before the window, less one
+    for (int32_t t = 0; t < total; t += 64 * kFlatWindows) {
+        const bool in = n > 0 && start >= t && start < t + 64 * kFlatWindows;
+        if (in) c.starts[start - t] = 1;
+        group_fence();
+        uint64_t m[kFlatWindows];
+#pragma unroll
+        for (int u = 0; u < kFlatWindows; ++u) m[u] = __ballot(c.starts[u * 64 + c.g.gl] != 0);
+        group_fence();
+        if (in) c.starts[start - t] = 0;
+        FlatRoot r[kFlatWindows];
+        int32_t x[kFlatWindows];
+#pragma unroll
+        for (int u = 0; u < kFlatWindows; ++u) {
+            const int32_t e = t + u * 64 + c.g.gl;
+            const int32_t own = before + (int)__popcll(m[u] & ((2ull << c.g.gl) - 1));
+            before += (int)__popcll(m[u]);
+            x[u] = -1;
+            r[u] = FlatRoot{nullptr, nullptr, 0, 0, 0, 0};
+            if (e < total) {
+                r[u] = c.flat[own];
+                x[u] = r[u].walk[e];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kFlatWindows; ++u) {
+            if (x[u] >= r[u].lo && x[u] < r[u].hi) {
+                if (r[u].test_n < 0) cnt += (((const uint32_t*)r[u].test)[x[u] >> 5] >> (x[u] & 31)) & 1u;
+                else cnt += member(Set{(const int32_t*)r[u].test, r[u].test_n, nullptr}, x[u]) ? 1u : 0u;
+            }
+        }
+    }
+    return cnt;
+}
+
 // One group's root tasks [t0, t1) of task space ts: every task binds its root
 // edge (levels 0 and 1) and searches the rest. Patterns whose search ends at
 // the root (k <= 3, or IEP over all k-2 levels after it) take different roots
@@ -1507,6 +1612,23 @@ __device__ __forceinline__ void run_tasks(const GpPlanDesc& d, Ctx<G>& c, const 
             }
         }
         return;
+    }
+    if constexpr (K == 3 && LEAF != 2 && G == 64 && !PER_ROOT) {
+        // intersections of many edges shared out evenly, where bitmaps test the long lists
+        // (and 64 shorter lists, of at most deg2 = cap elements, are counted in 32 bits)
+        if (c.flat && d.lv[2].last_list >= 0 && d.lv[2].pre_buf < 0 && d.lv[2].inj == 0 && c.n_hubs > 0 &&
+            c.cap < (1 << 25)) {
+            for (int64_t base = t0; base < t1; base += G) {
+                const int64_t r = base + c.g.gl;
+                int2 e = make_int2(0, 0);
+                if (r < t1) {
+                    e = ts.roots[ts.offset + r * ts.stride];
+                    if constexpr (MODE == MODE_ACCOUNT) *c.bytes += 8;
+                }
+                add_count(acc, roots_flat<G, MODE>(d, c, e.x, e.y, r < t1), carry);
+            }
+            return;
+        }
     }
     if constexpr (K <= 3 && LEAF != 2) {
         // lanes take different roots
@@ -1695,6 +1817,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(occupanc
     c.tab = nullptr;
     c.tab_n = 0;
     c.filt = nullptr;
+    constexpr bool kFlat = K == 3 && IEP == 0 && G == 64 && LEAF != 2 && MODE != MODE_PER_ROOT;
+    __shared__ __attribute__((aligned(16))) FlatRoot s_flat[kFlat ? kBlock : 1];
+    __shared__ int32_t s_starts[kFlat ? kBlock * kFlatWindows : 1];
+    c.flat = kFlat ? s_flat + grp * G : nullptr;
+    c.starts = s_starts + (kFlat ? grp * G * kFlatWindows : 0);
     __shared__ uint32_t s_cnt[IEP > 0 ? ((1 << IEP) - 1) * kBlock : 1];
     c.cnt = &s_cnt[IEP > 0 ? threadIdx.x : 0];
     const uint64_t t_begin = a.busy ? wall_clock64() : 0;

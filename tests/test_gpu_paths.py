@@ -227,3 +227,27 @@ def test_default_width_fits_the_workspace():
     assert out.tolist() == [r, 0]
     assert gp.count(graph, plan) == r
     graph.close()
+
+
+@pytest.mark.parametrize("n,m,hub", [(3, 3, 0), (12, 64, 0), (30, 65, 0), (40, 129, 0), (200, 800, 70), (600, 500, 599),
+                                     (2000, 20000, 1500)])
+def test_triangles_with_edges_sharing_a_walk(n, m, hub):
+    """Triangle counts that walk 64 edges' lists as one: few edges, last
+    windows of every length, lists with and without bitmaps, hubs whose lists
+    pass one step of the walk, samples, and every configuration of the pattern."""
+    rng = np.random.default_rng(m)
+    src = np.concatenate([rng.integers(0, n, m), np.zeros(hub, np.int64)])
+    dst = np.concatenate([rng.integers(0, n, m), np.arange(1, hub + 1)])
+    g = I.csr_from_edges(n, src, dst)
+    k, e = P["triangle"]
+    want = O.count(g, k, e)
+    for opts in (dict(), dict(hub_min_degree=200), dict(hub_bitmaps="dense"), dict(hub_bitmaps="none")):
+        graph = gp.Graph.from_csr(g, device=True, **opts)
+        for order in itertools.permutations(range(3)):
+            for fs in range(gp.Plan(k, e).info().n_sets):
+                plan = gp.Plan(k, e, stats=graph.stats(), force_order=order, force_set=fs)
+                assert gp.count(graph, plan) == want, (opts, order, fs)
+                assert gp.count_traffic(graph, plan)[0] == want
+                assert sum(gp.count(graph, plan, root_stride=3, root_offset=o) for o in range(3)) == want
+                assert gp.count(graph, plan, group=32) == want
+        graph.close()
