@@ -227,7 +227,7 @@ struct TempPool {
     int n = 0;
     explicit TempPool(hipStream_t st) : s(st) {}
     hipError_t get(void** p, size_t bytes) {
-        hipError_t e = gpint::pool_malloc(p, bytes ? bytes : 8, s);
+        hipError_t e = hipMallocAsync(p, bytes ? bytes : 8, s);
         if (e == hipSuccess && n < 32) ptrs[n++] = *p;
         return e;
     }
