@@ -214,7 +214,8 @@ int64_t task_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCfg& c
 LaunchCfg default_launch(const GpPlanDesc& d);
 LaunchCfg apply_launch(LaunchCfg cfg, const gp_launch* l);
 // Widens a group that the library chose to 64 lanes where the grid's candidate
-// buffers exceed room bytes: as many paths then fit, each on more lanes.
+// buffers exceed room bytes (as many paths then fit, each on more lanes), or the
+// root edges are fewer than the groups.
 void settle_group(const DeviceGraph& g, const GpPlanDesc& d, LaunchCfg* cfg, int64_t room);
 
 }  // namespace gpint
