@@ -53,6 +53,14 @@ void free_device_graph(gpint::DeviceGraph& g) {
     g = gpint::DeviceGraph{};
 }
 
+// The device's result slots, or null past the last device they are kept for. Never
+// destroyed: the HIP runtime may be gone by the time static objects are.
+ResultSlots* result_slots(int device) {
+    constexpr int kMaxDevices = 64;
+    static ResultSlots* const slots = new ResultSlots[kMaxDevices];
+    return device >= 0 && device < kMaxDevices ? slots + device : nullptr;
+}
+
 // Frees a graph whose device work has finished.
 void delete_graph(gp_graph* g) {
     const int dev = g->dg.device;
@@ -100,13 +108,14 @@ gp_status count_to_host(const gp_graph* g, const GpPlanDesc& d, const gpint::Lau
                         hipStream_t s, unsigned long long* per_root, uint64_t* out,
                         uint64_t* alg_bytes = nullptr) {
     unsigned long long h[3] = {0, 0, 0};
-    if (unsigned long long* slot = alg_bytes ? nullptr : g->results.acquire()) {
+    ResultSlots* results = alg_bytes ? nullptr : result_slots(g->dg.device);
+    if (unsigned long long* slot = results ? results->acquire() : nullptr) {
         slot[0] = slot[1] = 0;
         gp_status st = gpint::launch_count(g->dg, d, cfg, s, nullptr, per_root, false, nullptr, nullptr, slot);
         if (hipStreamSynchronize(s) != hipSuccess && st == GP_OK) st = GP_ERR_HIP;
         h[0] = slot[0];
         h[1] = slot[1];
-        g->results.release(slot);
+        results->release(slot);
         if (st != GP_OK) return st;
         if (h[1] & 2) return GP_ERR_INTERNAL;
         if (h[1]) return GP_ERR_OVERFLOW;

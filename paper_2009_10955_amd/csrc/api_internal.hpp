@@ -7,20 +7,23 @@
 #include "internal.hpp"
 #include "planner.hpp"
 
-// Pinned words that blocking calls on a graph receive their results in: the
-// last kernel writes them, so no copy is enqueued. One page, allocated on the
-// first call, a slot per call in flight; a call that finds none copies instead.
+// Pinned words that blocking calls receive their results in: the last kernel
+// writes them, so no copy is enqueued. One page per device, shared by its graphs
+// and held until the process ends, a slot per call in flight; a call that finds
+// none, or no page, copies instead. (A page per graph cost every load its
+// allocation and every free its release.)
 struct ResultSlots {
     static constexpr int kSlots = 64, kWords = 8;
     std::mutex mu;
     unsigned long long* page = nullptr;
     uint64_t used = 0;
-    bool failed = false;
     unsigned long long* acquire() {
         std::lock_guard<std::mutex> lk(mu);
-        if (!page && !failed)
-            failed = hipHostMalloc((void**)&page, sizeof(unsigned long long) * kSlots * kWords, hipHostMallocDefault) !=
-                     hipSuccess;
+        if (!page && hipHostMalloc((void**)&page, sizeof(unsigned long long) * kSlots * kWords, hipHostMallocDefault) !=
+                         hipSuccess) {
+            page = nullptr;
+            (void)hipGetLastError();  // or the next launch would report it
+        }
         if (!page || ~used == 0) return nullptr;
         const int i = __builtin_ctzll(~used);
         used |= uint64_t(1) << i;
@@ -31,14 +34,10 @@ struct ResultSlots {
         std::lock_guard<std::mutex> lk(mu);
         used &= ~(uint64_t(1) << ((p - page) / kWords));
     }
-    ~ResultSlots() {
-        if (page) (void)hipHostFree(page);
-    }
 };
 
 struct gp_graph {
     gpint::DeviceGraph dg;
-    mutable ResultSlots results;
     bool pooled = false;  // counted by pool_add_graph
 };
 
