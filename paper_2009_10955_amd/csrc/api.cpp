@@ -217,8 +217,8 @@ gp_status gp_load_graph_opts(const int64_t* row_ptr, const int32_t* col, int64_t
     if (!(flags & GP_IN_DEVICE)) {
         ends[0] = row_ptr[0];
         ends[1] = row_ptr[n];
-        if (hipMalloc((void**)&own_row, sizeof(int64_t) * (n + 1)) != hipSuccess ||
-            hipMalloc((void**)&own_col, sizeof(int32_t) * (nnz > 0 ? nnz : 1)) != hipSuccess) {
+        if (gpint::device_malloc((void**)&own_row, sizeof(int64_t) * (n + 1)) != hipSuccess ||
+            gpint::device_malloc((void**)&own_col, sizeof(int32_t) * (nnz > 0 ? nnz : 1)) != hipSuccess) {
             st = GP_ERR_NOMEM;
         } else if (hipMemcpyAsync(own_row, row_ptr, sizeof(int64_t) * (n + 1), hipMemcpyHostToDevice, s) !=
                        hipSuccess ||

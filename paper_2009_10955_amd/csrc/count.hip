@@ -226,10 +226,12 @@ hipMemPool_t g_pool[kMaxDevices] = {};
 bool g_pool_failed[kMaxDevices] = {};
 int g_pool_graphs[kMaxDevices] = {};
 
-// The device's pool, made on first use; null if it cannot be made.
+// The device's pool, made on first use; null if it cannot be made or no graph is
+// there (nothing would give its memory back).
 hipMemPool_t device_pool(int device) {
     if (device < 0 || device >= kMaxDevices) return nullptr;
     std::lock_guard<std::mutex> lk(g_pool_mu);
+    if (g_pool_graphs[device] <= 0) return nullptr;
     if (!g_pool[device] && !g_pool_failed[device]) {
         hipMemPoolProps props;
         std::memset(&props, 0, sizeof props);
@@ -251,6 +253,34 @@ hipMemPool_t device_pool(int device) {
 }
 }  // namespace
 
+// Gives the device memory that its pool holds and no call uses back to the driver.
+static void pool_trim() {
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return;
+    std::lock_guard<std::mutex> lk(g_pool_mu);
+    if (g_pool[dev]) (void)hipMemPoolTrimTo(g_pool[dev], 0);
+}
+
+hipError_t device_malloc(void** p, size_t bytes) {
+    hipError_t e = hipMalloc(p, bytes);
+    if (e == hipSuccess) return e;
+    (void)hipGetLastError();
+    pool_trim();
+    e = hipMalloc(p, bytes);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e;
+}
+
+hipError_t stream_malloc(void** p, size_t bytes, hipStream_t stream) {
+    hipError_t e = hipMallocAsync(p, bytes, stream);
+    if (e == hipSuccess) return e;
+    (void)hipGetLastError();
+    pool_trim();
+    e = hipMallocAsync(p, bytes, stream);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e;
+}
+
 hipError_t pool_malloc(void** p, size_t bytes, hipStream_t stream) {
     size_t size = size_t(64) << 10;
     while (size < bytes && size < kPoolMostBytes) size *= 2;
@@ -262,7 +292,7 @@ hipError_t pool_malloc(void** p, size_t bytes, hipStream_t stream) {
         pool = device_pool(dev);
     if (pool && hipMallocFromPoolAsync(p, size, pool, stream) == hipSuccess) return hipSuccess;
     (void)hipGetLastError();  // the default pool decides
-    return hipMallocAsync(p, bytes, stream);
+    return stream_malloc(p, bytes, stream);
 }
 
 void pool_add_graph(int device) {
@@ -812,10 +842,10 @@ gp_status batch_prepare(const DeviceGraph& g, const GpPlanDesc* descs, const Lau
                 const int l = iep_memo_log2(g.n_hubs, kIepMemoBytes / 8);
                 if (l >= 0) b.memo_words = std::max(b.memo_words, (int64_t)g.n_hubs << l);
             }
-    if (hipMalloc((void**)&b.queues, kQueueBytes * np) != hipSuccess ||
-        hipMalloc((void**)&b.result, 4 * sizeof(unsigned long long) * np) != hipSuccess ||
-        (b.nbuf > 0 && hipMalloc((void**)&b.scratch, (size_t)(slots * b.nbuf * b.cap * 4)) != hipSuccess) ||
-        (b.memo_words > 0 && hipMalloc((void**)&b.memo, (size_t)b.memo_words * 8) != hipSuccess))
+    if (device_malloc((void**)&b.queues, kQueueBytes * np) != hipSuccess ||
+        device_malloc((void**)&b.result, 4 * sizeof(unsigned long long) * np) != hipSuccess ||
+        (b.nbuf > 0 && device_malloc((void**)&b.scratch, (size_t)(slots * b.nbuf * b.cap * 4)) != hipSuccess) ||
+        (b.memo_words > 0 && device_malloc((void**)&b.memo, (size_t)b.memo_words * 8) != hipSuccess))
         rc = GP_ERR_NOMEM;
     if (rc == GP_OK && hipStreamSynchronize(stream) != hipSuccess) rc = GP_ERR_HIP;
     if (rc != GP_OK) {
@@ -943,11 +973,11 @@ gp_status arena_create(const DeviceGraph& g, int nbuf_cap, int waves_per_cu, int
     a.blocks_cap = batch_blocks(g, waves_per_cu, 64 / a.min_group, a.nbuf_cap, b.cap, true);
     a.slots_cap = a.blocks_cap * (kBlock / 64) * (64 / a.min_group);
     a.memo_words_cap = g.n_hubs > 0 ? a.slots_cap * (int64_t)g.n_hubs : 0;
-    bool ok = hipMalloc((void**)&b.queues, kQueueBytes * kBatchMaxPlans) == hipSuccess &&
-              hipMalloc((void**)&b.result, 4 * sizeof(unsigned long long) * kBatchMaxPlans) == hipSuccess &&
+    bool ok = device_malloc((void**)&b.queues, kQueueBytes * kBatchMaxPlans) == hipSuccess &&
+              device_malloc((void**)&b.result, 4 * sizeof(unsigned long long) * kBatchMaxPlans) == hipSuccess &&
               (a.nbuf_cap == 0 ||
-               hipMalloc((void**)&b.scratch, (size_t)(a.slots_cap * a.nbuf_cap * b.cap * 4)) == hipSuccess) &&
-              (a.memo_words_cap == 0 || hipMalloc((void**)&b.memo, (size_t)a.memo_words_cap * 8) == hipSuccess) &&
+               device_malloc((void**)&b.scratch, (size_t)(a.slots_cap * a.nbuf_cap * b.cap * 4)) == hipSuccess) &&
+              (a.memo_words_cap == 0 || device_malloc((void**)&b.memo, (size_t)a.memo_words_cap * 8) == hipSuccess) &&
               hipHostMalloc((void**)&a.h_result, 4 * sizeof(unsigned long long) * kBatchMaxPlans,
                             hipHostMallocDefault) == hipSuccess;
     if (!ok) {

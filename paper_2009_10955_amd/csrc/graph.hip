@@ -227,7 +227,7 @@ struct TempPool {
     int n = 0;
     explicit TempPool(hipStream_t st) : s(st) {}
     hipError_t get(void** p, size_t bytes) {
-        hipError_t e = hipMallocAsync(p, bytes ? bytes : 8, s);
+        hipError_t e = gpint::stream_malloc(p, bytes ? bytes : 8, s);
         if (e == hipSuccess && n < 32) ptrs[n++] = *p;
         return e;
     }
@@ -273,10 +273,10 @@ gp_status build_layout(const int64_t* row_ptr, const int32_t* col, int64_t n, in
     // device buffers owned by the graph
     const int64_t nn = n > 0 ? n : 1;
     const int64_t ne = nnz > 0 ? nnz : 1;
-    GP_HIP_TRY(hipMalloc((void**)&g->row_ptr, sizeof(int64_t) * (n + 1)));
-    GP_HIP_TRY(hipMalloc((void**)&g->col, sizeof(int32_t) * ne));
-    GP_HIP_TRY(hipMalloc((void**)&g->roots_all, sizeof(int2) * ne));
-    GP_HIP_TRY(hipMalloc((void**)&g->new_id, sizeof(int32_t) * nn));
+    GP_HIP_TRY(device_malloc((void**)&g->row_ptr, sizeof(int64_t) * (n + 1)));
+    GP_HIP_TRY(device_malloc((void**)&g->col, sizeof(int32_t) * ne));
+    GP_HIP_TRY(device_malloc((void**)&g->roots_all, sizeof(int2) * ne));
+    GP_HIP_TRY(device_malloc((void**)&g->new_id, sizeof(int32_t) * nn));
 
     // 2. relabel by descending degree, ties by ascending id
     uint64_t *vkeys = nullptr, *vkeys_sorted = nullptr;
@@ -349,8 +349,8 @@ gp_status build_layout(const int64_t* row_ptr, const int32_t* col, int64_t n, in
     GP_HIP_TRY(hipStreamSynchronize(s));
     g->n_lower = hv[0];
     g->n_upper = hv[1];
-    GP_HIP_TRY(hipMalloc((void**)&g->roots_lower, sizeof(int2) * (hv[0] > 0 ? hv[0] : 1)));
-    GP_HIP_TRY(hipMalloc((void**)&g->roots_upper, sizeof(int2) * (hv[1] > 0 ? hv[1] : 1)));
+    GP_HIP_TRY(device_malloc((void**)&g->roots_lower, sizeof(int2) * (hv[0] > 0 ? hv[0] : 1)));
+    GP_HIP_TRY(device_malloc((void**)&g->roots_upper, sizeof(int2) * (hv[1] > 0 ? hv[1] : 1)));
     if (nnz > 0)
         hipLaunchKernelGGL(scatter_roots, dim3(grid_for(nnz)), dim3(256), 0, s, g->row_ptr, g->roots_all,
                            n, nnz, lower_cnt, lower_off, upper_off, g->roots_lower, g->roots_upper);
@@ -405,7 +405,7 @@ gp_status build_hub_bitmaps(DeviceGraph* g, int64_t min_degree, int64_t budget_b
     if (h == 0) return GP_OK;
     g->hub_words = (found[1] + 31) / 32;
     const int64_t per = g->hub_words * 4;
-    GP_HIP_TRY(hipMalloc((void**)&g->hub_bits, (size_t)(h * per)));
+    GP_HIP_TRY(device_malloc((void**)&g->hub_bits, (size_t)(h * per)));
     GP_HIP_TRY(hipMemsetAsync(g->hub_bits, 0, (size_t)(h * per), s));
     hipLaunchKernelGGL(fill_hub_bits, dim3(grid_for(entries)), dim3(256), 0, s, g->row_ptr, g->col, h,
                        entries, g->hub_words, g->hub_bits);

@@ -196,11 +196,15 @@ gp_status check_sum(const uint64_t* values, int64_t n, uint64_t div, hipStream_t
 // of different sizes find each other's blocks: with exact sizes and 4 GiB kept,
 // a 4-clique listing on R-MAT 16 took 5.8 ms after an R-MAT 19 count, whose 3.5 GiB
 // stood idle in the pool, and 1.9 alone; kPoolKeepBytes holds one block of every
-// size up to kPoolMostBytes. Larger requests, and all under stream capture
-// (there a graph node), are plain hipMallocAsync.
+// size up to kPoolMostBytes. Larger requests, all under stream capture (there a
+// graph node) and all while no graph is loaded are plain hipMallocAsync.
 constexpr uint64_t kPoolMostBytes = uint64_t(4) << 30;
 constexpr uint64_t kPoolKeepBytes = 2 * kPoolMostBytes;
 hipError_t pool_malloc(void** p, size_t bytes, hipStream_t stream);
+// hipMalloc and hipMallocAsync that, refused, take back what the pool holds idle and
+// try again. A refusal is returned and not left for the next launch to report.
+hipError_t device_malloc(void** p, size_t bytes);
+hipError_t stream_malloc(void** p, size_t bytes, hipStream_t stream);
 void pool_add_graph(int device);   // a graph now lives on the device
 void pool_drop_graph(int device);  // it is gone (its work has finished)
 

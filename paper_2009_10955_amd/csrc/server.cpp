@@ -237,7 +237,7 @@ void poll_estimates(gp_server* S) {
         if (!x->stream)
             ok = hipStreamCreateWithFlags(&x->stream, hipStreamNonBlocking) == hipSuccess &&
                  hipEventCreateWithFlags(&x->done, hipEventDisableTiming) == hipSuccess &&
-                 hipMalloc((void**)&x->dev, 5 * sizeof(unsigned long long)) == hipSuccess &&
+                 gpint::device_malloc((void**)&x->dev, 5 * sizeof(unsigned long long)) == hipSuccess &&
                  hipHostMalloc((void**)&x->host, 5 * sizeof(unsigned long long), hipHostMallocDefault) ==
                      hipSuccess;
         gpint::LaunchCfg cfg = server_launch(S);

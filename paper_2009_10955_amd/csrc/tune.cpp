@@ -213,7 +213,7 @@ gp_status gp_plan_tune(const gp_graph* g, const gp_plan* p, const gp_tune_opts* 
     gp_status st = GP_OK;
     unsigned long long* res = nullptr;
     if (!np->tuned) {
-        if (hipMallocAsync((void**)&res, 5 * sizeof(unsigned long long), s) != hipSuccess) {  // {count, flags, busy[3]}
+        if (gpint::stream_malloc((void**)&res, 5 * sizeof(unsigned long long), s) != hipSuccess) {  // {count, flags, busy[3]}
             delete np;
             return GP_ERR_HIP;
         }
@@ -696,7 +696,7 @@ gp_status gp_estimate(const gp_graph* g, const gp_plan* p, const gp_launch* laun
     hipStream_t s = (hipStream_t)stream;
     unsigned long long* res = nullptr;
     gp_status st = GP_OK;
-    if (hipMallocAsync((void**)&res, 5 * sizeof(unsigned long long), s) != hipSuccess) {
+    if (gpint::stream_malloc((void**)&res, 5 * sizeof(unsigned long long), s) != hipSuccess) {
         st = GP_ERR_NOMEM;
     } else {
         gpint::LaunchCfg cfg = gpint::launch_for_plan(p, launch, g->dg);

@@ -65,3 +65,44 @@ for n in (3, 5, 9):
     g.close()
 assert stub.stub_host_allocs() == 1, stub.stub_host_allocs()
 """)
+
+
+def test_idle_pool_memory_is_given_back_to_a_refused_allocation(stub):
+    """Memory that the calls' pool holds idle does not fail a load: the pool is
+    trimmed and the allocation tried again."""
+    _run(stub, """
+g = edgeless()
+assert gp.check_sum(np.ones(1 << 20, np.uint64), stream=0) is not None
+idle = stub.stub_pool_idle()
+assert idle >= 8 << 20
+stub.stub_device_limit(idle + (4 << 20))
+big = edgeless((1 << 20) - 1)  # 8 MB of row pointers
+assert stub.stub_trims() == 1 and stub.stub_pool_idle() < idle
+big.close()
+g.close()
+""")
+
+
+def test_refused_scratch_leaves_no_error_behind(stub):
+    """A count whose scratch is refused returns GP_ERR_NOMEM, and the next one, with
+    memory there again, counts."""
+    _run(stub, """
+g = edgeless()
+plan = gp.Plan(*I.PATTERNS["4-cycle"])
+stub.stub_device_limit(1)
+try:
+    gp.count(g, plan, stream=0)
+    raise SystemExit("not refused")
+except gp.GpError as e:
+    assert e.status == -7, e
+stub.stub_device_limit(0)
+assert gp.count(g, plan, stream=0) == 0
+""")
+
+
+def test_pool_is_not_used_while_no_graph_is_loaded(stub):
+    """Nothing would give the pool's memory back then."""
+    _run(stub, """
+gp.check_sum(np.ones(1 << 20, np.uint64), stream=0)
+assert stub.stub_pool_idle() == 0
+""")
