@@ -317,8 +317,9 @@ void gp_free_plan(gp_plan* p);
  * One persistent kernel launch on `stream`: wavefront groups take root edges
  * (the first two schedule levels) from an atomic queue and search the
  * remaining levels depth first; a plan whose last level depends on the root and
- * one more vertex only may instead run blocks of wavefronts on one root edge
- * with a table in LDS (then group, chunk, leaf_mode and the splits play no part).
+ * one more vertex only runs blocks of wavefronts on one root edge with a table in
+ * LDS where the graph's degrees make that pay (then group, chunk, leaf_mode, the
+ * splits and xcd_tasks play no part; gp_count_shape tells).
  * Blocking: synchronises `stream` and writes *out on the host. GP_ERR_OVERFLOW if
  * the count does not fit in 64 bits.
  * `launch` may be null (auto). Device memory, allocated stream-ordered per
@@ -331,6 +332,18 @@ void gp_free_plan(gp_plan* p);
  */
 gp_status gp_count(const gp_graph* g, const gp_plan* p, const gp_launch* launch, void* stream,
                    uint64_t* out);
+
+/* How gp_count would launch a plan (host only: nothing runs). */
+typedef struct {
+    int32_t table;   /* 1: blocks of wavefronts with a table in LDS, 0: the general search */
+    int32_t memo;    /* 1: sizes are kept in device memory (leaf mode 4, inclusion-exclusion) */
+    int32_t group;   /* lanes that share one search path */
+    int32_t chunk;   /* tasks per grab */
+    int32_t blocks;  /* the grid */
+    int32_t threads; /* per block */
+} gp_shape;
+
+gp_status gp_count_shape(const gp_graph* g, const gp_plan* p, const gp_launch* launch, gp_shape* out);
 
 /* As gp_count, without host synchronisation: dev_out (device memory, 2
  * uint64) receives {count, flags} when the stream reaches it; flag bit 0:

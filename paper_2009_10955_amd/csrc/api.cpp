@@ -595,6 +595,11 @@ gp_status gp_count(const gp_graph* g, const gp_plan* p, const gp_launch* launch,
     return count_to_host(g, p->desc, cfg, (hipStream_t)stream, nullptr, out);
 }
 
+gp_status gp_count_shape(const gp_graph* g, const gp_plan* p, const gp_launch* launch, gp_shape* out) {
+    if (!g || !p || !out) return GP_ERR_ARG;
+    return gpint::describe_count(g->dg, p->desc, gpint::launch_for_plan(p, launch, g->dg), out);
+}
+
 gp_status gp_count_async(const gp_graph* g, const gp_plan* p, const gp_launch* launch, void* stream,
                          uint64_t* dev_out) {
     if (!g || !p || !dev_out) return GP_ERR_ARG;

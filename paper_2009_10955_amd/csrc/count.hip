@@ -120,7 +120,7 @@ bool memo_eligible(const GpPlanDesc& d) {
     return (ll.inj & ~(uint32_t)d.lv[d.k - 2].parents) == 0;
 }
 
-// Whether a count of d over g runs on the table kernel (count_table.hip): every
+// Whether the table kernel (count_table.hip) can count d over g: every
 // plan whose last level is N(x) & N(root endpoint) cut by root levels, whole
 // counts and samples alike, while its sizes fit 16 bits. Not with builds at the
 // root level, which each of the block's 16 wavefronts would repeat, and not
@@ -128,9 +128,8 @@ bool memo_eligible(const GpPlanDesc& d) {
 // N(root endpoint) & N(x). Without and with the table: R-MAT 17 5-cycle (64 lanes, split 4
 // ways, leaf mode 4 with a memo) 477 and 31 ms; 5-cycle of the cost model's plan on
 // R-MAT (20,000 vertices, 160K edges) 100 and 11.5 ms; 6-cycle on Chung-Lu (3,000
-// vertices, 30K edges) 199 and 24 ms; 4-cycle on G(1000, 0.01), a whole call,
-// 109 and 76 us.
-bool table_rule(const gpint::DeviceGraph& g, const GpPlanDesc& d, int mode) {
+// vertices, 30K edges) 199 and 24 ms.
+bool table_form(const gpint::DeviceGraph& g, const GpPlanDesc& d, int mode) {
     if (mode == MODE_PER_ROOT || d.k < 4 || g.deg2 >= 65536) return false;
     if (d.iep) {
         // the set of the last outer vertex: N(p) & N(x), uncut, p the endpoint
@@ -145,6 +144,52 @@ bool table_rule(const gpint::DeviceGraph& g, const GpPlanDesc& d, int mode) {
            ((ll.hi_src | ll.lo_src) & ~3u) == 0;
 }
 
+// Bindings that a search of d is expected to make below one root edge, through
+// level to: the product of the levels' candidate sets, from the graph's means. Cuts
+// count only where they are by the root's hub, which leaves few candidates; sets
+// built from several lists count as an edge's common neighbors.
+double expected_bindings(const gpint::DeviceGraph& g, const GpPlanDesc& d, int to) {
+    const int hub = d.root_cut == 1 ? 1 : (d.root_cut == 2 ? 0 : -1);  // its level
+    double w = 1;
+    for (int l = 2; l <= to; ++l) {
+        const GpLevel& L = d.lv[l];
+        if (L.list < 0) w *= g.mean_common();
+        else if (L.list >= 2 || hub < 0) w *= g.mean_deg;
+        else if ((L.hi_src >> hub) & 1) w *= L.list == hub ? g.hub_below : g.other_below;
+        else w *= L.list == hub ? g.hub_deg : g.other_deg;
+    }
+    return w;
+}
+
+int table_waves(const gpint::DeviceGraph& g, const GpPlanDesc& d);
+
+// Whether the table pays for its fills. A fill costs a block a fixed time (clearing
+// 16 to 64 KB of LDS, barriers), 6 to 8 us per root edge where every root has one. What
+// it saves is a walk per binding of the level above the last, of mean_deg
+// elements, where the table covers it; the eighth is what a lookup costs itself.
+// So the line is a product of these, per root edge, above which the table won on uniform, Chung-Lu and
+// R-MAT graphs of 1,000 to 1M vertices. Table and general kernel at saved / least
+// (uniform graphs, vertices and edges): 5-cycle 20K, 160K 0.8: 2.03 and 1.32 ms; 100K, 1.6M 1.8:
+// 57 and 72; 20K, 400K 11: 6.5 and 26; 1M, 8M 0.3: 219 and 86; a 4-regular torus of 1M
+// vertices 0: 26 and 1.2. 4-cycle 1M, 8M: 37 and 6.3, 20K, 1M 1.7: 4.5 and 10.6;
+// R-MAT (65,536, 400K) 7.6: 2.1 and 2.6. 6-cycle 100K, 800K 0.7: 129 and 124, 20K, 160K
+// 2.1: 7.6 and 19.6. House with inclusion-exclusion 20K, 400K 0.94: 0.81 and
+// 0.73, 20K, 1M 5.8: 4.5 and 11.
+bool table_pays(const gpint::DeviceGraph& g, const GpPlanDesc& d) {
+    const int waves = table_waves(g, d);
+    const int t = waves == 4 ? 0 : (waves == 8 ? 1 : 2);
+    static_assert(gpint::kTableSizes[0] == table_max(4) && gpint::kTableSizes[1] == table_max(8) &&
+                      gpint::kTableSizes[2] == table_max(16),
+                  "entries counted for the tables' sizes");
+    const double covered = (double)g.first_entries[t] / (double)std::max<int64_t>(1, g.nnz);
+    const double saved = expected_bindings(g, d, d.iep ? d.k - 3 : d.k - 2) * g.mean_deg * (covered - 0.125);
+    return saved >= (d.iep ? 1200 : (waves == 4 ? 600 : (d.k == 5 ? 6000 : 40000)));
+}
+
+bool table_rule(const gpint::DeviceGraph& g, const GpPlanDesc& d, int mode) {
+    return table_form(g, d, mode) && table_pays(g, d);
+}
+
 // With inclusion-exclusion a table is filled once for all of p's roots, so a sparse
 // sample pays for the fills: taken while the heaviest endpoint keeps 1,024 sampled
 // roots. House with and without the table, every 1st and 7th root of R-MAT 17: 10.4 and
@@ -155,8 +200,8 @@ bool table_sample(const gpint::DeviceGraph& g, const GpPlanDesc& d, int64_t stri
 }
 
 // Its blocks: 4 wavefronts where a root edge has little work (one level of lanes,
-// k = 4) or the small table covers the graph, else 16: 4-cycle on G(1000, 0.01), a
-// whole call, 76 us with 16 and 54 with 4; 5-cycle on G(5000, 0.004) 0.74 and 0.31 ms.
+// k = 4) or the small table covers the graph, else 16: 5-cycle on G(5000, 0.004) 0.74
+// ms with 16 and 0.31 with 4.
 int table_waves(const gpint::DeviceGraph& g, const GpPlanDesc& d) {
     if (d.iep) return kIepTableWaves;
     return d.k == 4 || g.n <= table_max(4) ? 4 : 16;
@@ -452,84 +497,132 @@ constexpr size_t kQueueBytes = sizeof(unsigned long long) * kQueueWords;  // a m
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 }  // namespace
 
-gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCfg& launch,
-                       hipStream_t stream, unsigned long long* result_dev,
-                       unsigned long long* per_root, bool account, unsigned long long* busy,
-                       const Workspace* ws, unsigned long long* result_host) {
+namespace {
+// What one launch of the counting kernels is made of.
+struct CountShape {
+    LaunchCfg cfg;
+    KernelFn fn = nullptr;
+    bool table = false;  // the table kernel
+    int mode = MODE_PLAIN, group = 64, tab_waves = 16;
+    int64_t cap = 1;
+    const int2* roots = nullptr;
+    int64_t n_roots = 0, split_roots = 0, n_tasks = 0, need = 0;
+    int split_ways = 1;
+    int32_t chunk = 1;
+    int64_t blocks = 1, groups_per_block = 4;
+    size_t scratch_bytes = 0;
+    int iep_log2 = -1;
+    int64_t memo_words = 0;
+    bool use_memo = false;
+    int threads() const { return table ? tab_waves * 64 : kBlock; }
+};
+}  // namespace
+
+static gp_status count_shape(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCfg& launch, int mode,
+                             const Workspace* ws, CountShape* out) {
+    CountShape& z = *out;
     // keep scratch within a fixed budget (or the caller's workspace): fewer
     // resident groups if needed
     const int64_t budget = ws ? (int64_t)ws->bytes - (int64_t)kQueueBytes : int64_t(16) << 30;
     if (ws && budget < 0) return GP_ERR_ARG;
-    LaunchCfg cfg = launch;
+    z.cfg = launch;
+    LaunchCfg& cfg = z.cfg;
     if (ws) settle_group(g, d, &cfg, budget);
     if (cfg.group != 64 && cfg.group != 32 && cfg.group != 16 && cfg.group != 8) return GP_ERR_ARG;
     if (cfg.leaf < 1 || cfg.leaf > 4) return GP_ERR_ARG;
     if (cfg.waves_per_cu < 1 || cfg.waves_per_cu > 32 || cfg.chunk < 1) return GP_ERR_ARG;
-    const int mode = account ? MODE_ACCOUNT : (per_root ? MODE_PER_ROOT : MODE_PLAIN);
+    z.mode = mode;
     const bool iep = d.iep != 0;
-    const int group = iep ? (cfg.group >= 64 ? 64 : 32) : cfg.group;  // IEP kernels: 64 or 32 lanes
-    const int tab_waves = table_waves(g, d);
-    const int64_t cap = std::max<int64_t>(1, g.deg2);
+    z.group = iep ? (cfg.group >= 64 ? 64 : 32) : cfg.group;  // IEP kernels: 64 or 32 lanes
+    z.tab_waves = table_waves(g, d);
+    z.cap = std::max<int64_t>(1, g.deg2);
     // the table kernel, unless a workspace has no room for its larger blocks
-    const bool table =
-        table_rule(g, d, mode) && table_sample(g, d, cfg.root_stride) && tab_waves * d.nbuf * cap * 4 <= budget;
-    KernelFn fn = table ? pick_table(d, mode, tab_waves) : pick_kernel(d.k, group, cfg.leaf, mode, d.iep);
-    if (!fn) return GP_ERR_UNSUPPORTED;
+    z.table = table_rule(g, d, mode) && table_sample(g, d, cfg.root_stride) &&
+              z.tab_waves * d.nbuf * z.cap * 4 <= budget;
+    z.fn = z.table ? pick_table(d, mode, z.tab_waves) : pick_kernel(d.k, z.group, cfg.leaf, mode, d.iep);
+    if (!z.fn) return GP_ERR_UNSUPPORTED;
 
     int64_t all_roots = 0;
-    const int2* roots = pick_roots(g, d.root_cut, &all_roots);
+    z.roots = pick_roots(g, d.root_cut, &all_roots);
     if (cfg.root_stride < 1 || cfg.root_offset < 0) return GP_ERR_ARG;
     if (cfg.split_ways < 1 || cfg.split_ways > 4096 || cfg.split_vertices < 0 || cfg.budget_ms < 0)
         return GP_ERR_ARG;
     // sampled roots: roots[offset + r * stride]
-    auto sampled = [&](int64_t n) {
-        return n > cfg.root_offset ? (n - cfg.root_offset + cfg.root_stride - 1) / cfg.root_stride : 0;
-    };
-    const int64_t n_roots = sampled(all_roots);
-    const SplitPlan sp = split_plan(g, d, cfg, mode, n_roots, cfg.root_stride, cfg.root_offset);
-    const int64_t split_roots = sp.roots;
-    const int split_ways = sp.ways;
-    const int64_t n_tasks = n_roots + split_roots * (split_ways - 1);
+    z.n_roots =
+        all_roots > cfg.root_offset ? (all_roots - cfg.root_offset + cfg.root_stride - 1) / cfg.root_stride : 0;
+    const SplitPlan sp = split_plan(g, d, cfg, mode, z.n_roots, cfg.root_stride, cfg.root_offset);
+    z.split_roots = sp.roots;
+    z.split_ways = sp.ways;
+    z.n_tasks = z.n_roots + sp.roots * (sp.ways - 1);
 
     const int waves_per_block = kBlock / 64;
-    int64_t blocks = std::max<int64_t>(1, (int64_t)g.num_cus * cfg.waves_per_cu / waves_per_block);
-    int64_t groups_per_block = kBlock / group;
-    int32_t chunk = grab_tasks_of(d, cfg, group);
-    if (table) {
-        groups_per_block = tab_waves;
-        blocks = table_blocks(g, d, cfg.waves_per_cu, n_roots);
-        chunk = table_chunk(d, blocks, n_roots);
+    z.blocks = std::max<int64_t>(1, (int64_t)g.num_cus * cfg.waves_per_cu / waves_per_block);
+    z.groups_per_block = kBlock / z.group;
+    z.chunk = grab_tasks_of(d, cfg, z.group);
+    if (z.table) {
+        z.groups_per_block = z.tab_waves;
+        z.blocks = table_blocks(g, d, cfg.waves_per_cu, z.n_roots);
+        z.chunk = table_chunk(d, z.blocks, z.n_roots);
     }
-    const int64_t per_block = d.nbuf > 0 ? groups_per_block * d.nbuf * cap * 4 : 0;
+    const int64_t per_block = d.nbuf > 0 ? z.groups_per_block * d.nbuf * z.cap * 4 : 0;
     // the memo that the launch may use (below): one for all of it, or a word per
     // hub in every group
-    const bool leaf4_memo = cfg.leaf == 4 && !table && mode != MODE_PER_ROOT && !iep && memo_eligible(d) &&
-                            n_tasks < (int64_t(1) << 31);
+    const bool leaf4_memo = cfg.leaf == 4 && !z.table && mode != MODE_PER_ROOT && !iep && memo_eligible(d) &&
+                            z.n_tasks < (int64_t(1) << 31);
     const bool iep_memo = iep && iep_memo_eligible(d);
     if (per_block > 0) {
         if (ws && per_block > budget) return GP_ERR_NOMEM;  // not even one block's buffers fit
-        blocks = std::min(blocks, std::max<int64_t>(1, budget / per_block));
+        z.blocks = std::min(z.blocks, std::max<int64_t>(1, budget / per_block));
         // within what the pool hands out, if that leaves half the grid: larger
         // regions are freed after the call, and the driver clears them at 24 GB/s
         const int64_t l = iep_memo ? iep_memo_log2(g.n_hubs, kIepMemoBytes / 8) : -1;
         const int64_t room = (int64_t)kPoolMostBytes - (int64_t(1) << 20) - (l >= 0 ? ((int64_t)g.n_hubs * 8) << l : 0);
-        const int64_t kept = room / (per_block + (leaf4_memo ? groups_per_block * (int64_t)g.n_hubs * 8 : 0));
-        if (!ws && 2 * kept >= blocks) blocks = std::min(blocks, kept);
+        const int64_t kept = room / (per_block + (leaf4_memo ? z.groups_per_block * (int64_t)g.n_hubs * 8 : 0));
+        if (!ws && 2 * kept >= z.blocks) z.blocks = std::min(z.blocks, kept);
     }
     // a grid larger than the number of root tasks only adds idle groups
-    int64_t need = (n_tasks + chunk - 1) / chunk;
-    int64_t need_blocks = std::max<int64_t>(1, (need + groups_per_block - 1) / groups_per_block);
-    if (!table) blocks = std::min(blocks, need_blocks);
+    z.need = (z.n_tasks + z.chunk - 1) / z.chunk;
+    if (!z.table)
+        z.blocks =
+            std::min(z.blocks, std::max<int64_t>(1, (z.need + z.groups_per_block - 1) / z.groups_per_block));
 
-    const size_t scratch_bytes = (size_t)(blocks * per_block);
+    z.scratch_bytes = (size_t)(z.blocks * per_block);
     // leaf mode 4's per-task memo: one word per hub per group, within 4 GiB
     // (within what the workspace has left); the IEP memo: one table for the
     // launch, 2^l words per hub, within 2 GiB (or the room left)
-    const int64_t memo_cap = ws ? budget - (int64_t)align_up(scratch_bytes) : (int64_t(4) << 30);
-    const int iep_log2 = iep_memo ? iep_memo_log2(g.n_hubs, std::min(memo_cap, kIepMemoBytes) / 8) : -1;
-    const int64_t memo_words = iep ? (iep_log2 >= 0 ? (int64_t)g.n_hubs << iep_log2 : 0)
-                                   : blocks * groups_per_block * (int64_t)g.n_hubs;
-    const bool use_memo = (leaf4_memo || iep_log2 >= 0) && g.n_hubs > 0 && memo_words * 8 <= memo_cap;
+    const int64_t memo_cap = ws ? budget - (int64_t)align_up(z.scratch_bytes) : (int64_t(4) << 30);
+    z.iep_log2 = iep_memo ? iep_memo_log2(g.n_hubs, std::min(memo_cap, kIepMemoBytes) / 8) : -1;
+    z.memo_words = iep ? (z.iep_log2 >= 0 ? (int64_t)g.n_hubs << z.iep_log2 : 0)
+                       : z.blocks * z.groups_per_block * (int64_t)g.n_hubs;
+    z.use_memo = (leaf4_memo || z.iep_log2 >= 0) && g.n_hubs > 0 && z.memo_words * 8 <= memo_cap;
+    return GP_OK;
+}
+
+gp_status describe_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCfg& cfg, gp_shape* out) {
+    CountShape z;
+    const gp_status st = count_shape(g, d, cfg, MODE_PLAIN, nullptr, &z);
+    if (st != GP_OK) return st;
+    out->table = z.table ? 1 : 0;
+    out->memo = z.use_memo ? 1 : 0;
+    out->group = z.table ? 64 : z.group;
+    out->chunk = z.chunk;
+    out->blocks = (int32_t)z.blocks;
+    out->threads = z.threads();
+    return GP_OK;
+}
+
+gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCfg& launch,
+                       hipStream_t stream, unsigned long long* result_dev,
+                       unsigned long long* per_root, bool account, unsigned long long* busy,
+                       const Workspace* ws, unsigned long long* result_host) {
+    CountShape z;
+    const gp_status shaped =
+        count_shape(g, d, launch, account ? MODE_ACCOUNT : (per_root ? MODE_PER_ROOT : MODE_PLAIN), ws, &z);
+    if (shaped != GP_OK) return shaped;
+    const LaunchCfg& cfg = z.cfg;
+    const size_t scratch_bytes = z.scratch_bytes;
+    const bool use_memo = z.use_memo;
+    const int64_t memo_words = z.memo_words;
 
     int32_t* scratch = nullptr;
     unsigned long long* queue = nullptr;
@@ -555,13 +648,13 @@ gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCf
     CountArgs a;
     a.row_ptr = g.row_ptr;
     a.col = g.col;
-    a.roots = roots;
-    a.n_roots = n_roots;
-    a.n_tasks = n_tasks;
-    a.n_chunks = table ? (n_roots + chunk - 1) / chunk : need;
-    a.tab_n = (int32_t)std::min<int64_t>(g.n, table_max(tab_waves));
-    a.split_roots = split_roots;
-    a.split_ways = split_ways;
+    a.roots = z.roots;
+    a.n_roots = z.n_roots;
+    a.n_tasks = z.n_tasks;
+    a.n_chunks = z.table ? (z.n_roots + z.chunk - 1) / z.chunk : z.need;
+    a.tab_n = (int32_t)std::min<int64_t>(g.n, table_max(z.tab_waves));
+    a.split_roots = z.split_roots;
+    a.split_ways = z.split_ways;
     a.budget_ticks = busy && cfg.budget_ms > 0 ? (uint64_t)(cfg.budget_ms * g.wall_khz) : 0;
     a.root_offset = cfg.root_offset;
     a.hub_bits = g.hub_bits;
@@ -569,24 +662,24 @@ gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCf
     a.n_hubs = g.n_hubs;
     a.root_stride = cfg.root_stride;
     a.scratch = scratch;
-    a.buf_cap = cap;
+    a.buf_cap = z.cap;
     a.queue = queue;
     a.result = result_dev;
     a.per_root = per_root;
     a.busy = busy;
     a.memo = memo;
-    a.chunk = chunk;
-    a.memo_ways_log2 = std::max(iep_log2, 0);
+    a.chunk = z.chunk;
+    a.memo_ways_log2 = std::max(z.iep_log2, 0);
     LaunchCfg grab = cfg;
-    grab.chunk = chunk;
-    a.xcd_block = xcd_block_tasks(g, grab, group);
-    if (n_tasks > 0)
-        hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(table ? tab_waves * 64 : kBlock), 0, stream, d, a);
+    grab.chunk = z.chunk;
+    a.xcd_block = xcd_block_tasks(g, grab, z.group);
+    if (z.n_tasks > 0)
+        hipLaunchKernelGGL(z.fn, dim3((unsigned)z.blocks), dim3((unsigned)z.threads()), 0, stream, d, a);
     // a sample's total need not be a multiple of the over-count: its quotient
     // is an estimate, not checked
     const bool whole = cfg.root_stride == 1 && cfg.root_offset == 0 && !(busy && cfg.budget_ms > 0);
     hipLaunchKernelGGL(finish_count, dim3(1), dim3(64), 0, stream, result_dev, queue,
-                       (unsigned long long)(iep ? d.iep_div : 1), whole ? 1 : 0, result_host);
+                       (unsigned long long)(d.iep ? d.iep_div : 1), whole ? 1 : 0, result_host);
     hipError_t le = hipGetLastError();
     if (!ws) (void)hipFreeAsync(base, stream);
     if (le != hipSuccess) return GP_ERR_HIP;

@@ -157,6 +157,49 @@ __global__ void count_lower(const int64_t* row_ptr, const int32_t* col, int64_t 
     }
 }
 
+// out[0..2] += the sums over the vertices of degree^2, lower * degree and lower^2,
+// lower: a vertex's neighbors of smaller id.
+__global__ void degree_sums(const int64_t* row_ptr, const int64_t* lower, int64_t n, unsigned long long* out) {
+    uint64_t s[3] = {0, 0, 0};
+    for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
+        const uint64_t d = (uint64_t)(row_ptr[v + 1] - row_ptr[v]), l = (uint64_t)lower[v];
+        s[0] += d * d;
+        s[1] += l * d;
+        s[2] += l * l;
+    }
+    __shared__ uint64_t s_sum[4];
+    for (int i = 0; i < 3; ++i) {
+        for (int off = 32; off >= 1; off >>= 1) s[i] += __shfl_xor(s[i], off, 64);
+        __syncthreads();
+        if (__lane_id() == 0) s_sum[threadIdx.x / 64] = s[i];
+        __syncthreads();
+        if (threadIdx.x == 0) atomicAdd(&out[i], (unsigned long long)(s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3]));
+    }
+}
+
+// The numbers the host keeps of a layout, gathered for one copy (a copy each was
+// 37 round trips).
+struct LayoutWords {
+    unsigned long long sums[3];  // degree_sums
+    unsigned long long hash;
+    int64_t n_lower, n_upper, deg[2];
+    int64_t first_entries[3];
+    int64_t upper_pref[32];
+};
+
+// w->sums and w->hash are there already; one block.
+__global__ void layout_words(const int64_t* row_ptr, const int64_t* lower_off, const int64_t* upper_off, int64_t n,
+                             int64_t t0, int64_t t1, int64_t t2, LayoutWords* w) {
+    const int i = threadIdx.x;
+    if (i < 32) w->upper_pref[i] = upper_off[min(int64_t(1) << i, n)];
+    if (i < 2) w->deg[i] = i < n ? row_ptr[i + 1] - row_ptr[i] : 0;
+    if (i < 3) w->first_entries[i] = row_ptr[min(i == 0 ? t0 : (i == 1 ? t1 : t2), n)];
+    if (i == 0) {
+        w->n_lower = lower_off[n];
+        w->n_upper = upper_off[n];
+    }
+}
+
 __global__ void scatter_roots(const int64_t* row_ptr, const int2* roots_all, int64_t n, int64_t nnz,
                               const int64_t* lower_cnt, const int64_t* lower_off,
                               const int64_t* upper_off, int2* roots_lower, int2* roots_upper) {
@@ -245,11 +288,11 @@ gp_status build_layout(const int64_t* row_ptr, const int32_t* col, int64_t n, in
                        hipStream_t s, DeviceGraph* g) {
     TempPool tmp(s);
     unsigned* flags = nullptr;
-    unsigned long long* hash = nullptr;
+    LayoutWords* words = nullptr;
     GP_HIP_TRY(tmp.get((void**)&flags, sizeof(unsigned)));
-    GP_HIP_TRY(tmp.get((void**)&hash, sizeof(unsigned long long)));
+    GP_HIP_TRY(tmp.get((void**)&words, sizeof(LayoutWords)));
     GP_HIP_TRY(hipMemsetAsync(flags, 0, sizeof(unsigned), s));
-    GP_HIP_TRY(hipMemsetAsync(hash, 0, sizeof(unsigned long long), s));
+    GP_HIP_TRY(hipMemsetAsync(words, 0, sizeof(LayoutWords), s));
     if (n > 0) hipLaunchKernelGGL(check_rows, dim3(grid_for(n)), dim3(256), 0, s, row_ptr, n, nnz, flags);
     unsigned hflags = 0;
     GP_HIP_TRY(hipMemcpyAsync(&hflags, flags, sizeof(unsigned), hipMemcpyDeviceToHost, s));
@@ -268,7 +311,7 @@ gp_status build_layout(const int64_t* row_ptr, const int32_t* col, int64_t n, in
         if (hflags & F_ASYM) return GP_ERR_CSR_ASYMMETRIC;
     }
     hipLaunchKernelGGL(hash_input, dim3(std::min(2048u, grid_for(nnz + n + 1))), dim3(256), 0, s, row_ptr, col, n, nnz,
-                       hash);
+                       &words->hash);
 
     // device buffers owned by the graph
     const int64_t nn = n > 0 ? n : 1;
@@ -338,15 +381,15 @@ gp_status build_layout(const int64_t* row_ptr, const int32_t* col, int64_t n, in
     GP_HIP_TRY(tmp.get(&tscan2, tb));
     GP_HIP_TRY(hipcub::DeviceScan::ExclusiveSum(tscan2, tb, lower_cnt, lower_off, (int)(n + 1), s));
     GP_HIP_TRY(hipcub::DeviceScan::ExclusiveSum(tscan2, tb, upper_cnt, upper_off, (int)(n + 1), s));
-    int64_t hv[2] = {0, 0};
-    GP_HIP_TRY(hipMemcpyAsync(&hv[0], lower_off + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    GP_HIP_TRY(hipMemcpyAsync(&hv[1], upper_off + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    int64_t degs[2] = {0, 0};
-    if (n > 0) GP_HIP_TRY(hipMemcpyAsync(&degs[0], new_deg, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    if (n > 1) GP_HIP_TRY(hipMemcpyAsync(&degs[1], new_deg + 1, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    unsigned long long hhash = 0;
-    GP_HIP_TRY(hipMemcpyAsync(&hhash, hash, sizeof(hhash), hipMemcpyDeviceToHost, s));
+    if (n > 0)
+        hipLaunchKernelGGL(degree_sums, dim3(std::min(1024u, grid_for(n))), dim3(256), 0, s, g->row_ptr, lower_cnt, n,
+                           words->sums);
+    hipLaunchKernelGGL(layout_words, dim3(1), dim3(64), 0, s, g->row_ptr, lower_off, upper_off, n,
+                       (int64_t)kTableSizes[0], (int64_t)kTableSizes[1], (int64_t)kTableSizes[2], words);
+    LayoutWords lw;
+    GP_HIP_TRY(hipMemcpyAsync(&lw, words, sizeof lw, hipMemcpyDeviceToHost, s));
     GP_HIP_TRY(hipStreamSynchronize(s));
+    const int64_t hv[2] = {lw.n_lower, lw.n_upper};
     g->n_lower = hv[0];
     g->n_upper = hv[1];
     GP_HIP_TRY(device_malloc((void**)&g->roots_lower, sizeof(int2) * (hv[0] > 0 ? hv[0] : 1)));
@@ -360,21 +403,27 @@ gp_status build_layout(const int64_t* row_ptr, const int32_t* col, int64_t n, in
         hipLaunchKernelGGL(order_roots, dim3(grid_for(hv[1])), dim3(256), 0, s, g->roots_upper, hv[1],
                            g->roots_lower, g->roots_all);
     GP_HIP_TRY(hipGetLastError());
-    // upper_pref[i]: roots of each ordered array per orientation whose smaller
-    // endpoint is below 2^i
-    for (int i = 0; i < 32; ++i) {
-        const int64_t v = std::min<int64_t>(int64_t(1) << i, n);
-        GP_HIP_TRY(hipMemcpyAsync(&g->upper_pref[i], upper_off + v, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    }
     GP_HIP_TRY(hipStreamSynchronize(s));
+    for (int i = 0; i < 32; ++i) g->upper_pref[i] = lw.upper_pref[i];
+    for (int i = 0; i < 3; ++i) g->first_entries[i] = lw.first_entries[i];
     g->n = n;
     g->nnz = nnz;
-    g->max_deg = degs[0];
-    g->deg2 = degs[1];
+    g->max_deg = lw.deg[0];
+    g->deg2 = lw.deg[1];
+    if (nnz > 0) {
+        // a vertex is the other endpoint of as many root edges as it has
+        // neighbors of smaller id, and the hub of the rest
+        const double m = (double)nnz / 2, dd = (double)lw.sums[0], ld = (double)lw.sums[1], ll = (double)lw.sums[2];
+        g->mean_deg = dd / (double)nnz;
+        g->other_deg = ld / m;
+        g->hub_deg = (dd - ld) / m;
+        g->other_below = (ll - m) / 2 / m;
+        g->hub_below = (ld - ll) / m;
+    }
     g->stats.n = n;
     g->stats.m = nnz / 2;
-    g->stats.max_degree = degs[0];
-    g->stats.hash = hhash;
+    g->stats.max_degree = lw.deg[0];
+    g->stats.hash = lw.hash;
     return GP_OK;
 }
 

@@ -10,6 +10,9 @@
 
 namespace gpint {
 
+// Vertices that the path tables of 4, 8 and 16 wavefronts cover (count_table.hip).
+constexpr int kTableSizes[3] = {8192, 16384, 32768};
+
 // Graph as resident in HBM: relabelled by descending degree, each list
 // ascending, plus the root-edge arrays the counting kernel walks.
 struct DeviceGraph {
@@ -30,6 +33,12 @@ struct DeviceGraph {
     int64_t hub_words = 0;        // uint32 words per bitmap: up to the last vertex with a neighbor
     int32_t n_hubs = 0;
     int64_t max_deg = 0;          // largest degree
+    // Means over root edges (u, v), h the endpoint of smaller id (the hub) and o the
+    // other: degrees of either, of h and of o, neighbors of h and of o with an id
+    // below h; and common neighbors of u and v.
+    double mean_deg = 0, hub_deg = 0, other_deg = 0, hub_below = 0, other_below = 0;
+    double mean_common() const { return nnz > 0 ? (double)stats.tri_cnt / (double)nnz : 0; }
+    int64_t first_entries[3] = {}; // CSR entries of the first kTableSizes[i] vertices
     int64_t deg2 = 0;             // second largest degree (bound on any |N(a) & N(b)|, a != b)
     gp_stats stats{};
 };
@@ -79,6 +88,9 @@ gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCf
                        unsigned long long* per_root, bool account = false,
                        unsigned long long* busy = nullptr, const Workspace* ws = nullptr,
                        unsigned long long* result_host = nullptr);
+
+// What launch_count would launch (no workspace): see gp_count_shape.
+gp_status describe_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCfg& cfg, gp_shape* out);
 
 // launch_count without allocating: the queue (kNoallocQueueBytes), candidate
 // buffers and memo (kNoallocWorkspaceBytes) come from one static device array per GPU

@@ -66,6 +66,11 @@ class Launch(ctypes.Structure):
                 ("xcd_tasks", ctypes.c_int32), ("batch_runs", ctypes.c_int32)]
 
 
+class Shape(ctypes.Structure):
+    _fields_ = [("table", ctypes.c_int32), ("memo", ctypes.c_int32), ("group", ctypes.c_int32),
+                ("chunk", ctypes.c_int32), ("blocks", ctypes.c_int32), ("threads", ctypes.c_int32)]
+
+
 class TuneOpts(ctypes.Structure):
     _fields_ = [("max_configs", ctypes.c_int32), ("sample_stride", ctypes.c_int32),
                 ("tune_launch", ctypes.c_int32), ("budget_seconds", ctypes.c_double),
@@ -127,6 +132,7 @@ SIGNATURES = {
     "gp_plan_with_launch": (_I32, [_P, ctypes.POINTER(Launch), ctypes.POINTER(_P)]),
     "gp_launch_default": (None, [ctypes.POINTER(Launch)]),
     "gp_count": (_I32, [_P, _P, ctypes.POINTER(Launch), _P, ctypes.POINTER(ctypes.c_uint64)]),
+    "gp_count_shape": (_I32, [_P, _P, ctypes.POINTER(Launch), ctypes.POINTER(Shape)]),
     "gp_count_async": (_I32, [_P, _P, ctypes.POINTER(Launch), _P, _P]),
     "gp_count_noalloc": (_I32, [_P, _P, ctypes.POINTER(Launch), _P, _P]),
     "gp_count_per_root": (_I32, [_P, _P, ctypes.POINTER(Launch), _P, _P,
@@ -413,6 +419,14 @@ def count(graph: Graph, plan: Plan, stream=None, **launch) -> int:
     _check(_lib().gp_count(graph.handle, plan.handle, ctypes.byref(lp), _stream_handle(stream),
                            ctypes.byref(out)), "gp_count")
     return out.value
+
+
+def count_shape(graph: Graph, plan: Plan, **launch) -> dict:
+    """How count would launch the plan (see gp_count_shape); runs nothing."""
+    out = Shape()
+    lp = _launch(**launch)
+    _check(_lib().gp_count_shape(graph.handle, plan.handle, ctypes.byref(lp), ctypes.byref(out)), "gp_count_shape")
+    return {f: getattr(out, f) for f, _ in Shape._fields_}
 
 
 def count_async(graph: Graph, plan: Plan, dev_out, stream=None, **launch) -> None:

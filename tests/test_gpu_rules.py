@@ -1,0 +1,124 @@
+"""Rules that pick a kernel or a launch from the plan and the graph: which side of
+them a graph falls on, and the same counts on both. Counts are integers: every
+comparison is exact."""
+import itertools
+import random
+
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_2009_10955_amd import gp
+from paper_2009_10955_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+P = I.PATTERNS
+# the path-table form of these patterns, and the house with inclusion-exclusion
+HOUSE = dict(force_order=(0, 1, 2, 3, 4), force_restr=[(1, 0)], iep=True)
+FIVE = dict(force_order=(0, 1, 2, 3, 4), force_restr=[(1, 0), (1, 2), (1, 3), (1, 4), (2, 0)])
+
+
+def _uniform(n, m, seed=1):
+    rng = np.random.default_rng(seed)
+    return I.csr_from_edges(n, rng.integers(0, n, m), rng.integers(0, n, m))
+
+
+def _torus(w):
+    x = np.arange(w * w)
+    r, c = x // w, x % w
+    return I.csr_from_edges(w * w, np.concatenate([x, x]), np.concatenate([r * w + (c + 1) % w, (r + 1) % w * w + c]))
+
+
+def _hubs(n, m, hubs, deg, seed=1):
+    """A uniform graph with hubs of degree deg."""
+    rng = np.random.default_rng(seed)
+    src = np.concatenate([rng.integers(0, n, m), np.repeat(np.arange(hubs), deg)])
+    dst = np.concatenate([rng.integers(0, n, m), rng.integers(0, n, hubs * deg)])
+    return I.csr_from_edges(n, src, dst)
+
+
+def _orders(k, edges):
+    adj = {(a, b) for a, b in edges} | {(b, a) for a, b in edges}
+    return [o for o in itertools.permutations(range(k))
+            if all(any((o[i], o[j]) in adj for j in range(i)) for i in range(1, k))]
+
+
+# ------------------------------------------------------- path table or general search
+
+@pytest.mark.parametrize("g", [_uniform(20000, 160000), _uniform(100000, 400000), _torus(300)],
+                         ids=["G20000", "G100000", "torus"])
+@pytest.mark.parametrize("pname,opts", [("4-cycle", {}), ("5-cycle", {}), ("5-cycle", FIVE), ("house", HOUSE)])
+def test_no_path_table_where_degrees_are_small_and_even(g, pname, opts):
+    """A fill of the table per root edge costs more than the search there (5-cycle on
+    the torus of 1M vertices 26 ms with tables, 1.2 without)."""
+    graph = gp.Graph.from_csr(g, device=True)
+    plan = gp.Plan(*P[pname], stats=graph.stats(), **opts)
+    assert gp.count_shape(graph, plan)["table"] == 0
+    assert gp.count(graph, plan) == gp.count_per_root(graph, plan)[0]
+    graph.close()
+
+
+@pytest.mark.parametrize("pname,n,m,hubs,deg", [("4-cycle", 3000, 9000, 30, 900), ("4-cycle", 8193, 30000, 30, 1500),
+                                                ("5-cycle", 8192, 20000, 8, 900), ("5-cycle", 8193, 20000, 8, 1500),
+                                                ("5-cycle", 40000, 60000, 6, 3000), ("6-cycle", 9000, 9000, 3, 500)])
+def test_path_table_kernels_count_as_the_general_search(pname, n, m, hubs, deg):
+    """Graphs on the table's side of the rule, with fewer vertices than the table holds,
+    one more and many more: counted whole, sampled, in a batch, with accounting,
+    against the general search (per-root counts never use the table), over schedules
+    and sets that leave an endpoint out of the table or fill it anew at every root."""
+    k, e = P[pname]
+    rnd = random.Random(n)
+    orders = _orders(k, e)
+    for bits in ("auto", "none"):
+        graph = gp.Graph.from_csr(_hubs(n, m, hubs, deg), device=True, hub_bitmaps=bits)
+        st = graph.stats()
+        plans = [gp.Plan(k, e, stats=st)]
+        for _ in range(400):
+            if len(plans) == 6:
+                break
+            p = gp.Plan(k, e, stats=st, force_order=rnd.choice(orders), force_set=rnd.randrange(plans[0].info().n_sets))
+            if gp.count_shape(graph, p)["table"]:
+                plans.append(p)
+        assert len(plans) == 6 and gp.count_shape(graph, plans[0])["table"]
+        want = gp.count_per_root(graph, plans[0])[0]
+        for p in plans:
+            assert gp.count(graph, p) == want, (bits, p.order, p.restrictions)
+            assert sum(gp.count(graph, p, root_stride=5, root_offset=o) for o in range(5)) == want
+            assert gp.count_traffic(graph, p)[0] == want
+        assert gp.count_batch(graph, plans, batch_runs=2) == [want] * 6
+        graph.close()
+
+
+@pytest.mark.parametrize("n", [3000, 16385, 40000])
+def test_iep_table_kernel_counts_as_the_general_search(n):
+    """The house by the inclusion-exclusion table, with vertices below and past its end."""
+    graph = gp.Graph.from_csr(_hubs(n, 2 * n, 12, n // 4), device=True)
+    plan = gp.Plan(*P["house"], stats=graph.stats(), **HOUSE)
+    shape = gp.count_shape(graph, plan)
+    assert shape["table"] == 1 and shape["threads"] == 512 and plan.info().iep == 2
+    want = gp.count_per_root(graph, plan)[0]
+    assert gp.count(graph, plan) == want
+    assert gp.count_traffic(graph, plan)[0] == want
+    graph.close()
+
+
+def test_tables_against_the_oracle():
+    """The 5-cycle against the oracle, the 4-cycle against its closed form over the
+    adjacency matrix, both counted with tables."""
+    g = _hubs(600, 1500, 6, 250)
+    graph = gp.Graph.from_csr(g, device=True)
+    for opts in ({}, FIVE):
+        plan = gp.Plan(*P["5-cycle"], stats=graph.stats(), **opts)
+        assert gp.count_shape(graph, plan)["table"] == 1
+        assert gp.count(graph, plan) == O.count(g, *P["5-cycle"])
+    graph.close()
+    g = _hubs(2000, 6000, 40, 700)
+    a = np.zeros((2000, 2000))
+    a[np.repeat(np.arange(2000), g.degrees()), g.col] = 1
+    common = a @ a
+    np.fill_diagonal(common, 0)
+    graph = gp.Graph.from_csr(g, device=True)
+    plan = gp.Plan(*P["4-cycle"], stats=graph.stats())
+    assert gp.count_shape(graph, plan)["table"] == 1
+    assert gp.count(graph, plan) == int((common * (common - 1) / 2).sum()) // 4
+    graph.close()
