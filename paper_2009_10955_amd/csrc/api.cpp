@@ -650,7 +650,9 @@ gp_status gp_list(const gp_graph* g, const gp_plan* p, const gp_launch* launch, 
     if (p->desc.iep) return GP_ERR_UNSUPPORTED;
     DeviceGuard dgd(g->dg.device);
     hipStream_t s = (hipStream_t)stream;
-    gpint::LaunchCfg cfg = gpint::launch_for_plan(p, launch, g->dg);
+    // its groups have 64 lanes: the width that a count would settle on, and the grab that
+    // goes with it, play no part
+    gpint::LaunchCfg cfg = gpint::apply_launch(p->launch, launch);
     int32_t order[GP_MAX_K] = {};
     for (int i = 0; i < k; ++i) order[i] = p->order[i];
     unsigned long long* res = nullptr;

@@ -172,8 +172,8 @@ int table_waves(const gpint::DeviceGraph& g, const GpPlanDesc& d);
 // (uniform graphs, vertices and edges): 5-cycle 20K, 160K 0.8: 2.03 and 1.32 ms; 100K, 1.6M 1.8:
 // 57 and 72; 20K, 400K 11: 6.5 and 26; 1M, 8M 0.3: 219 and 86; a 4-regular torus of 1M
 // vertices 0: 26 and 1.2. 4-cycle 1M, 8M: 37 and 6.3, 20K, 1M 1.7: 4.5 and 10.6;
-// R-MAT (65,536, 400K) 7.6: 2.1 and 2.6. 6-cycle 100K, 800K 0.7: 129 and 124, 20K, 160K
-// 2.1: 7.6 and 19.6. House with inclusion-exclusion 20K, 400K 0.94: 0.81 and
+// R-MAT (65,536, 400K) 7.6: 2.1 and 2.6. 6-cycle 100K, 400K 0.2: 18 and 9, 40K, 200K 1.1: 6.4
+// and 7.5, 100K, 800K 2.3: 129 and 124, 20K, 160K 6.8: 7.6 and 19.6. House with inclusion-exclusion 20K, 400K 0.94: 0.81 and
 // 0.73, 20K, 1M 5.8: 4.5 and 11.
 bool table_pays(const gpint::DeviceGraph& g, const GpPlanDesc& d) {
     const int waves = table_waves(g, d);
@@ -183,7 +183,7 @@ bool table_pays(const gpint::DeviceGraph& g, const GpPlanDesc& d) {
                   "entries counted for the tables' sizes");
     const double covered = (double)g.first_entries[t] / (double)std::max<int64_t>(1, g.nnz);
     const double saved = expected_bindings(g, d, d.iep ? d.k - 3 : d.k - 2) * g.mean_deg * (covered - 0.125);
-    return saved >= (d.iep ? 1200 : (waves == 4 ? 600 : (d.k == 5 ? 6000 : 40000)));
+    return saved >= (d.iep ? 1200 : (waves == 4 ? 600 : (d.k == 5 ? 6000 : 12000)));
 }
 
 bool table_rule(const gpint::DeviceGraph& g, const GpPlanDesc& d, int mode) {
@@ -369,7 +369,7 @@ LaunchCfg default_launch(const GpPlanDesc& d) {
     // Where lanes take root edges, and with inclusion-exclusion (lanes take the
     // last outer level), the width of a wavefront.
     cfg.group = d.k >= 4 && !d.iep ? 16 : 64;
-    cfg.own_group = true;
+    cfg.own_group = cfg.own_chunk = true;
     cfg.waves_per_cu = 32;
     // where lanes take different root edges (k <= 3, or IEP over every level
     // after the root) a grab fills the lanes of a group: the 4-star with IEP on
@@ -411,7 +411,10 @@ LaunchCfg apply_launch(LaunchCfg cfg, const gp_launch* l) {
             cfg.own_group = false;
         }
         if (l->waves_per_cu) cfg.waves_per_cu = l->waves_per_cu;
-        if (l->chunk) cfg.chunk = l->chunk;
+        if (l->chunk) {
+            cfg.chunk = l->chunk;
+            cfg.own_chunk = false;
+        }
         if (l->leaf_mode) cfg.leaf = l->leaf_mode;
         if (l->root_stride) cfg.root_stride = l->root_stride;
         cfg.root_offset = l->root_offset;
@@ -423,6 +426,33 @@ LaunchCfg apply_launch(LaunchCfg cfg, const gp_launch* l) {
     return cfg;
 }
 
+// Five and more levels, on graphs whose heaviest roots decide (a root edge's endpoints
+// have 64 neighbors or more in the mean): where the level-2 candidates are a list that is
+// not cut below the hub, a grab of four such roots by a group a quarter as wide
+// ends last, so grabs are single tasks: R-MAT (131,072 vertices, 200K edges)
+// 5-cycle of schedule 0,1,2,4,3 301 and 100 ms (64 lanes, four a grab: 152), house of
+// 1,4,2,3,0 120 and 43 (81). Below 64 neighbors, tasks are short and even, and the
+// queue counts: 5-cycle on G(100,000, 400K edges) 1.07 and 1.35 ms.
+// Where they are a built set, but the lanes then take whole lists (the level above the
+// last), 32 lanes, two a grab, while the heaviest root has more work than a group's
+// share: R-MAT (131,072, 200K) house of 4,1,0,2,3 131 ms on 16 lanes, 54 on 32 (64: 67).
+static void settle_tail(const DeviceGraph& g, const GpPlanDesc& d, LaunchCfg* cfg, int64_t roots) {
+    if (d.k < 5 || d.iep || g.mean_deg < 64) return;
+    const int hub = d.root_cut == 1 ? 1 : (d.root_cut == 2 ? 0 : -1);
+    const GpLevel &l2 = d.lv[2], &lanes = d.lv[d.k - 2];
+    if (l2.list >= 0) {
+        if (cfg->own_chunk && (hub < 0 || !((l2.hi_src >> hub) & 1))) cfg->chunk = 1;
+    } else if (lanes.list >= 0 && lanes.hi_src == 0) {
+        const int64_t most = (int64_t)g.num_cus * cfg->waves_per_cu * (64 / cfg->group);
+        // of six levels and more it has to be well above: K4 + path of 2,1,0,3,4,5 on R-MAT
+        // (200,000 vertices, 600K edges; 1.2 shares) 970 ms on 16 lanes, 1,151 on 32
+        const double share = (double)roots / (double)most * g.mean_deg;
+        if ((double)g.max_deg < (d.k > 5 ? 1.5 : 1.0) * share) return;
+        cfg->group = 32;
+        if (cfg->own_chunk) cfg->chunk = 2;
+    }
+}
+
 void settle_group(const DeviceGraph& g, const GpPlanDesc& d, LaunchCfg* cfg, int64_t room) {
     if (!cfg->own_group || cfg->group >= 64) return;
     const int64_t most = (int64_t)g.num_cus * cfg->waves_per_cu * (64 / cfg->group);
@@ -430,7 +460,11 @@ void settle_group(const DeviceGraph& g, const GpPlanDesc& d, LaunchCfg* cfg, int
     const int64_t groups = std::min(most, roots / std::max(1, cfg->chunk) + 1);
     // fewer roots than groups: the heaviest decide, and finish sooner on more lanes
     // (5-cycle per root on Chung-Lu, 4,709 edges: 7.3 ms on 16 lanes, 5.6 on 64)
-    if (roots < most || groups * d.nbuf * std::max<int64_t>(1, g.deg2) * 4 > room) cfg->group = 64;
+    if (roots < most || groups * d.nbuf * std::max<int64_t>(1, g.deg2) * 4 > room) {
+        cfg->group = 64;
+        return;
+    }
+    settle_tail(g, d, cfg, roots);
 }
 
 static const int2* pick_roots(const DeviceGraph& g, int root_cut, int64_t* n) {

@@ -59,7 +59,8 @@ struct LaunchCfg {
     // -1: one task order for the device
     int64_t xcd = 0;
     int batch_runs = 0;  // batches: 2 = every plan its own launch
-    bool own_group = false;  // group is the library's choice (settle_group may widen it)
+    bool own_group = false;  // group is the library's choice (settle_group may change it)
+    bool own_chunk = false;  // likewise the tasks per grab
 };
 
 // Tasks per XCD block of a launch: cfg.xcd rounded up to a multiple of the
@@ -231,7 +232,8 @@ LaunchCfg default_launch(const GpPlanDesc& d);
 LaunchCfg apply_launch(LaunchCfg cfg, const gp_launch* l);
 // Widens a group that the library chose to 64 lanes where the grid's candidate
 // buffers exceed room bytes (as many paths then fit, each on more lanes), or the
-// root edges are fewer than the groups.
+// root edges are fewer than the groups; else fits width and grab to the weight of the
+// heaviest roots.
 void settle_group(const DeviceGraph& g, const GpPlanDesc& d, LaunchCfg* cfg, int64_t room);
 
 }  // namespace gpint

@@ -322,7 +322,7 @@ gp_status gp_plan_tune(const gp_graph* g, const gp_plan* p, const gp_tune_opts* 
         //    sample keeps a balanced share of about 8 ms of it
         gpint::LaunchCfg base = gpint::default_launch(p->desc);
         base.group = 64;  // the widths are tried from the widest on
-        base.own_group = false;
+        base.own_group = base.own_chunk = false;
         int64_t stride = o.sample_stride;
         if (stride <= 0) {
             const int64_t roots = std::max<int64_t>(1, gpint::root_task_count(g->dg, p->desc));
