@@ -129,8 +129,8 @@ bool memo_eligible(const GpPlanDesc& d) {
 // ways, leaf mode 4 with a memo) 477 and 31 ms; 5-cycle of the cost model's plan on
 // R-MAT (20,000 vertices, 160K edges) 100 and 11.5 ms; 6-cycle on Chung-Lu (3,000
 // vertices, 30K edges) 199 and 24 ms.
-bool table_form(const gpint::DeviceGraph& g, const GpPlanDesc& d, int mode) {
-    if (mode == MODE_PER_ROOT || d.k < 4 || g.deg2 >= 65536) return false;
+bool table_form(const gpint::DeviceGraph& g, const GpPlanDesc& d) {
+    if (d.k < 4 || g.deg2 >= 65536) return false;
     if (d.iep) {
         // the set of the last outer vertex: N(p) & N(x), uncut, p the endpoint
         // that the root array is ordered by
@@ -186,8 +186,8 @@ bool table_pays(const gpint::DeviceGraph& g, const GpPlanDesc& d) {
     return saved >= (d.iep ? 1200 : (waves == 4 ? 600 : (d.k == 5 ? 6000 : 12000)));
 }
 
-bool table_rule(const gpint::DeviceGraph& g, const GpPlanDesc& d, int mode) {
-    return table_form(g, d, mode) && table_pays(g, d);
+bool table_rule(const gpint::DeviceGraph& g, const GpPlanDesc& d) {
+    return table_form(g, d) && table_pays(g, d);
 }
 
 // With inclusion-exclusion a table is filled once for all of p's roots, so a sparse
@@ -381,8 +381,12 @@ LaunchCfg default_launch(const GpPlanDesc& d) {
     return cfg;
 }
 
+bool uses_table(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCfg& cfg) {
+    return cfg.table >= 0 && table_rule(g, d) && (cfg.table > 0 || table_sample(g, d, cfg.root_stride));
+}
+
 int resident_waves_per_cu(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCfg& cfg) {
-    if (table_rule(g, d, MODE_PLAIN) && table_sample(g, d, cfg.root_stride)) {
+    if (uses_table(g, d, cfg)) {
         const int w = table_waves(g, d);
         return std::max(1, std::min(cfg.waves_per_cu, d.iep ? 3 * w : 32) / w) * w;
     }
@@ -542,7 +546,7 @@ struct CountShape {
     const int2* roots = nullptr;
     int64_t n_roots = 0, split_roots = 0, n_tasks = 0, need = 0;
     int split_ways = 1;
-    int32_t chunk = 1;
+    int32_t chunk = 1, whole_chunk = 1;
     int64_t blocks = 1, groups_per_block = 4;
     size_t scratch_bytes = 0;
     int iep_log2 = -1;
@@ -571,8 +575,7 @@ static gp_status count_shape(const DeviceGraph& g, const GpPlanDesc& d, const La
     z.tab_waves = table_waves(g, d);
     z.cap = std::max<int64_t>(1, g.deg2);
     // the table kernel, unless a workspace has no room for its larger blocks
-    z.table = table_rule(g, d, mode) && table_sample(g, d, cfg.root_stride) &&
-              z.tab_waves * d.nbuf * z.cap * 4 <= budget;
+    z.table = mode != MODE_PER_ROOT && uses_table(g, d, cfg) && z.tab_waves * d.nbuf * z.cap * 4 <= budget;
     z.fn = z.table ? pick_table(d, mode, z.tab_waves) : pick_kernel(d.k, z.group, cfg.leaf, mode, d.iep);
     if (!z.fn) return GP_ERR_UNSUPPORTED;
 
@@ -597,6 +600,7 @@ static gp_status count_shape(const DeviceGraph& g, const GpPlanDesc& d, const La
         z.groups_per_block = z.tab_waves;
         z.blocks = table_blocks(g, d, cfg.waves_per_cu, z.n_roots);
         z.chunk = table_chunk(d, z.blocks, z.n_roots);
+        z.whole_chunk = table_chunk(d, table_blocks(g, d, cfg.waves_per_cu, all_roots), all_roots);
     }
     const int64_t per_block = d.nbuf > 0 ? z.groups_per_block * d.nbuf * z.cap * 4 : 0;
     // the memo that the launch may use (below): one for all of it, or a word per
@@ -687,6 +691,7 @@ gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCf
     a.n_tasks = z.n_tasks;
     a.n_chunks = z.table ? (z.n_roots + z.chunk - 1) / z.chunk : z.need;
     a.tab_n = (int32_t)std::min<int64_t>(g.n, table_max(z.tab_waves));
+    a.whole_chunk = z.whole_chunk;
     a.split_roots = z.split_roots;
     a.split_ways = z.split_ways;
     a.budget_ticks = busy && cfg.budget_ms > 0 ? (uint64_t)(cfg.budget_ms * g.wall_khz) : 0;
@@ -864,7 +869,7 @@ static gp_status batch_layout(const DeviceGraph& g, const GpPlanDesc* descs, con
         // their descriptors are its kernel arguments)
         const int iep_depth = descs[i].iep;
         const int ksize = std::min((int)descs[i].k, 7);  // sizes 7 and 8 share a kernel
-        const bool table = whole[i] && table_rule(g, descs[i], MODE_PLAIN);
+        const bool table = whole[i] && table_rule(g, descs[i]);
         if (b->runs.empty() || table || b->runs.back().table || b->runs.back().group != bp.group || b->runs.back().leaf != bp.leaf ||
             b->runs.back().iep != iep_depth || std::min(b->runs.back().kmin, 7) != ksize ||
             b->runs.back().p1 - b->runs.back().p0 >= kRunMaxPlans || cfgs[i].batch_runs == 2) {
@@ -1033,6 +1038,7 @@ gp_status batch_enqueue(const DeviceGraph& g, const BatchState& st, hipStream_t 
             a.n_tasks = r.n_tasks;
             a.n_chunks = ((r.table ? r.n_roots : r.n_tasks) + chunk - 1) / chunk;
             a.tab_n = (int32_t)std::min<int64_t>(g.n, table_max(r.tab_waves));
+            a.whole_chunk = chunk;
             a.split_roots = r.split_roots;
             a.split_ways = r.split_ways;
             a.budget_ticks = 0;

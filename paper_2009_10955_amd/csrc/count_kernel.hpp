@@ -136,6 +136,7 @@ struct CountArgs {
     // one cursor for the device
     int64_t xcd_block;
     int32_t tab_n;  // table kernel: vertices its table covers
+    int32_t whole_chunk;  // table kernel, with busy: tasks per grab of a whole count
 };
 
 typedef void (*KernelFn)(GpPlanDesc, CountArgs);

@@ -63,6 +63,19 @@ __device__ __forceinline__ void add_lists(const Ctx<64>& c, int32_t p, const Set
     }
 }
 
+// Root edges of p in the root array that p, their hub, orders (L), and how many of them
+// in a row a whole count's block takes with one fill of the table.
+__device__ __forceinline__ int32_t whole_run(const Ctx<64>& c, int32_t p, const Set& P, int32_t whole_chunk, int32_t& L) {
+    L = max(1, P.n - uni<64>(lower_bound_group<64>(c.g, P.p, P.n, p)));
+    return min(whole_chunk, L);
+}
+
+// Time that a sample spent and a whole count, per root edge, does not: part of dt
+// clock ticks, of which the whole count has the share num / den.
+__device__ __forceinline__ uint64_t beyond_share(uint64_t dt, int32_t num, int32_t den) {
+    return num >= den ? 0 : dt - (uint64_t)((float)dt * (float)num / (float)den);
+}
+
 template <int K, int MODE, int kWaves>
 __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(8))) void table_kernel(GpPlanDesc d,
                                                                                                     CountArgs a) {
@@ -71,6 +84,7 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(8))
     __shared__ int32_t s_len[kWaves][GP_DESC_MAX_BUILDS];
     __shared__ int64_t s_chunk;
     __shared__ int32_t s_cur;
+    __shared__ uint64_t s_beyond[kWaves];  // per wavefront: clock ticks that only a sample spends
     Ctx<64> c;
     const int wave = uni<64>((int)(threadIdx.x / 64));
     c.row_ptr = a.row_ptr;
@@ -99,6 +113,11 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(8))
     uint64_t acc = 0, carry = 0;
 
     const GpLevel& ll = d.lv[K - 1];
+    // whether the roots of a hub p share a fill: p orders the array, and the other
+    // endpoint only raises the cut
+    const int hub = d.root_cut == 1 ? 1 : (d.root_cut == 2 ? 0 : -1), rest = 1 - ll.pre_list;
+    const bool shared = hub == ll.pre_list && !(((ll.inj | ll.lo_src) >> rest) & 1u);
+    if (c.g.gl == 0) s_beyond[wave] = 0;
     int32_t cur_p = -1, cur_lo = 0, cur_hi = 0, cur_pos = 0;
     c.out = -1;
     if (threadIdx.x == 0) s_cur = (int)(blockIdx.x & (kCursors - 1));
@@ -128,8 +147,10 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(8))
             const Set P = c.nbr_u(p);
             const int q = 1 - ll.pre_list;
             const int32_t out = (ll.inj >> q) & 1u ? v[q] : -1;
+            const uint64_t t_fill = a.busy ? wall_clock64() : 0;
+            const bool anew = p != cur_p || lo != cur_lo || hi < cur_hi || out != c.out;
             // every wavefront of the block takes the same way here
-            if (p != cur_p || lo != cur_lo || hi < cur_hi || out != c.out) {
+            if (anew) {
                 for (int i = threadIdx.x; i < (a.tab_n + 7) / 8; i += kTabBlock)
                     reinterpret_cast<uint4*>(s_tab)[i] = make_uint4(0, 0, 0, 0);
                 cur_pos = lo > 0 ? uni<64>(lower_bound_group<64>(c.g, P.p, P.n, lo)) : 0;
@@ -145,6 +166,17 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(8))
             cur_lo = lo;
             cur_hi = hi;
             __syncthreads();
+            if (a.busy && shared && a.root_stride > 1) {
+                // a sampled root starts a table, or adds the lists of the roots left out;
+                // a whole count does either once for a run of them
+                const uint64_t dt = wall_clock64() - t_fill;
+                const int32_t s = (int32_t)a.root_stride;
+                int32_t L = 1;
+                const int32_t run = whole_run(c, p, P, a.whole_chunk, L);
+                if (c.g.gl == 0)
+                    s_beyond[wave] +=
+                        anew ? beyond_share(dt, min(a.chunk, max(1, L / s)), run) : beyond_share(dt, 1, s);
+            }
             search<K, 2, 64, 5, MODE, 0>(d, c, v, acc, carry);
             __syncthreads();
         }
@@ -168,7 +200,7 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(8))
         publish128(&slot[SLOT_LO], &slot[SLOT_HI], s, s_hi);
         if (stopped) atomicOr(&a.result[1], 4ull);
         if (a.busy) {
-            atomicAdd(&a.busy[0], (unsigned long long)(wall_clock64() - t_begin));
+            atomicAdd(&a.busy[0], (unsigned long long)(wall_clock64() - t_begin - s_beyond[wave]));
             atomicAdd(&a.busy[1], 1ull);
             atomicMax(&a.busy[2], (unsigned long long)chunk_max);
         }
@@ -195,6 +227,7 @@ __global__ __launch_bounds__(kIepWaves * 64) __attribute__((amdgpu_waves_per_eu(
     __shared__ int32_t s_len[kIepWaves][GP_DESC_MAX_BUILDS];
     __shared__ int64_t s_chunk;
     __shared__ int32_t s_cur, s_next;
+    __shared__ uint64_t s_beyond[kIepWaves];  // as above
     Ctx<64> c;
     const int wave = uni<64>((int)(threadIdx.x / 64));
     c.row_ptr = a.row_ptr;
@@ -223,6 +256,7 @@ __global__ __launch_bounds__(kIepWaves * 64) __attribute__((amdgpu_waves_per_eu(
     bool stopped = false;
     uint64_t acc = 0, carry = 0;
     const bool second = d.it[d.iep_sum - 1].op[0] == 1;
+    if (c.g.gl == 0) s_beyond[wave] = 0;
     int32_t cur_p = -1;
     if (threadIdx.x == 0) s_cur = (int)(blockIdx.x & (kCursors - 1));
     __syncthreads();
@@ -249,7 +283,14 @@ __global__ __launch_bounds__(kIepWaves * 64) __attribute__((amdgpu_waves_per_eu(
             const int run = other ? __builtin_ctzll(other) : 64;
             __syncthreads();  // the last run's readers are done
             if (threadIdx.x == 0) s_next = 0;
-            if (p != cur_p) {
+            const uint64_t t_fill = a.busy ? wall_clock64() : 0;
+            int32_t of_run = run;  // roots that a whole count takes with one fill
+            if (a.busy && a.root_stride > 1) {
+                int32_t L = 1;
+                of_run = whole_run(c, p, c.nbr_u(p), a.whole_chunk, L);
+            }
+            const bool anew = p != cur_p;
+            if (anew) {
                 const Set P = c.nbr_u(p);
                 for (int i = threadIdx.x; i < (a.tab_n + 7) / 8; i += kIepWaves * 64)
                     reinterpret_cast<uint4*>(s_tab)[i] = make_uint4(0, 0, 0, 0);
@@ -264,6 +305,7 @@ __global__ __launch_bounds__(kIepWaves * 64) __attribute__((amdgpu_waves_per_eu(
                 cur_p = p;
             }
             __syncthreads();
+            if (a.busy && anew && c.g.gl == 0) s_beyond[wave] += beyond_share(wall_clock64() - t_fill, run, of_run);
             for (;;) {
                 int t = 0;
                 if (c.g.gl == 0) t = atomicAdd(&s_next, 1);
@@ -277,6 +319,12 @@ __global__ __launch_bounds__(kIepWaves * 64) __attribute__((amdgpu_waves_per_eu(
                 v[0] = uni<64>(e.x);
                 v[1] = uni<64>(e.y);
                 if (run_builds<K, 64, MODE>(d, c, 1, v)) search<K, 2, 64, 5, MODE, 2>(d, c, v, acc, carry);
+            }
+            if (a.busy) {
+                // a run of one sampled root leaves the other wavefronts waiting
+                const uint64_t t_wait = wall_clock64();
+                __syncthreads();
+                if (c.g.gl == 0) s_beyond[wave] += beyond_share(wall_clock64() - t_wait, run, of_run);
             }
             r += run;
         }
@@ -300,7 +348,7 @@ __global__ __launch_bounds__(kIepWaves * 64) __attribute__((amdgpu_waves_per_eu(
         publish128(&slot[SLOT_LO], &slot[SLOT_HI], s, s_hi);
         if (stopped) atomicOr(&a.result[1], 4ull);
         if (a.busy) {
-            atomicAdd(&a.busy[0], (unsigned long long)(wall_clock64() - t_begin));
+            atomicAdd(&a.busy[0], (unsigned long long)(wall_clock64() - t_begin - s_beyond[wave]));
             atomicAdd(&a.busy[1], 1ull);
             atomicMax(&a.busy[2], (unsigned long long)chunk_max);
         }

@@ -59,6 +59,10 @@ struct LaunchCfg {
     // -1: one task order for the device
     int64_t xcd = 0;
     int batch_runs = 0;  // batches: 2 = every plan its own launch
+    // path tables: 0: for whole counts and dense samples that they pay for; 1: for every
+    // sample of such a plan, with what its busy time counts of the fills scaled to a
+    // whole count's (estimates); -1: never
+    int table = 0;
     bool own_group = false;  // group is the library's choice (settle_group may change it)
     bool own_chunk = false;  // likewise the tasks per grab
 };
@@ -76,6 +80,7 @@ struct Workspace {
 };
 
 // Wavefronts per compute unit that a launch of d with cfg keeps resident.
+bool uses_table(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCfg& cfg);
 int resident_waves_per_cu(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCfg& cfg);
 
 // Launch one count of plan d over g on `stream`. result_dev: {count,

@@ -50,6 +50,7 @@ gp_status estimate_begin(const DeviceGraph& g, const GpPlanDesc& d, LaunchCfg cf
     cfg.root_stride = stride;
     cfg.root_offset = 0;  // the first root is the heaviest: its tail shows
     cfg.budget_ms = budget_ms;
+    if (cfg.table == 0) cfg.table = 1;  // the kernel that the whole count runs on
     return launch_count(g, d, cfg, s, res, nullptr, false, res + 2);
 }
 
@@ -59,6 +60,7 @@ double estimate_end(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCfg& 
     const double busy = (double)h[2] / g.wall_khz, chunk = (double)h[4] / g.wall_khz;
     LaunchCfg sample = cfg;
     sample.root_stride = stride;
+    if (sample.table == 0) sample.table = 1;
     const double resident = (double)g.num_cus * resident_waves_per_cu(g, d, sample);
     return std::max(busy * (double)stride / resident, chunk);
 }
@@ -321,6 +323,7 @@ gp_status gp_plan_tune(const gp_graph* g, const gp_plan* p, const gp_tune_opts* 
         // 2. sample stride: the planner's configuration gives the work; the
         //    sample keeps a balanced share of about 8 ms of it
         gpint::LaunchCfg base = gpint::default_launch(p->desc);
+        base.table = 1;  // samples run on the kernel that the whole count runs on
         base.group = 64;  // the widths are tried from the widest on
         base.own_group = base.own_chunk = false;
         int64_t stride = o.sample_stride;
@@ -394,6 +397,9 @@ gp_status gp_plan_tune(const gp_graph* g, const gp_plan* p, const gp_tune_opts* 
             if (lm == 4) return k >= 4 && !bd.iep && bd.lv[k - 1].last_list == k - 2;
             return true;
         };
+        // configurations that run on path tables have one shape: group, leaf mode, splits
+        // and grabs play no part there
+        auto on_table = [&](size_t c) { return gpint::uses_table(g->dg, cands[c].desc, base); };
         // pass A: every leaf mode with 64-lane groups, for each configuration
         for (size_t r = 0; st == GP_OK && r < shape_set.size(); ++r) {
             const size_t c = shape_set[r].second;
@@ -408,7 +414,7 @@ gp_status gp_plan_tune(const gp_graph* g, const gp_plan* p, const gp_tune_opts* 
                 // k >= 5, and its samples are the slowest, so the budget that
                 // remains goes to it
                 for (int lm : {3, 4, 2}) {
-                    if (!leaf_ok(bd, lm) || spent > 2.5 * budget_ms) continue;
+                    if (!leaf_ok(bd, lm) || on_table(c) || spent > 2.5 * budget_ms) continue;
                     gpint::LaunchCfg cfg = base;
                     cfg.leaf = lm;
                     double t = measure(bd, cfg, stride, "shape", c, true);
@@ -429,7 +435,7 @@ gp_status gp_plan_tune(const gp_graph* g, const gp_plan* p, const gp_tune_opts* 
             const GpPlanDesc& bd = cands[pk.c].desc;
             best_est = pk.est;
             for (int grp : {32, 16, 8}) {
-                if (bd.iep && grp < 32) continue;
+                if ((bd.iep && grp < 32) || on_table(pk.c)) continue;
                 double best_g = inf;
                 for (int lm : {1, 2, 3, 4}) {
                     if (!leaf_ok(bd, lm) || spent > 2.5 * budget_ms) continue;
@@ -604,22 +610,23 @@ gp_status gp_plan_tune(const gp_graph* g, const gp_plan* p, const gp_tune_opts* 
                 }
             };
             const gpint::LaunchCfg won = best_launch;
+            const bool table = on_table(best);
             for (int ways : {4, 1}) {
-                if (ways == won.split_ways) continue;
+                if (ways == won.split_ways || table) continue;
                 gpint::LaunchCfg cfg = best_launch;
                 cfg.split_ways = ways;
                 try_cfg(cfg);
             }
             const int chunk0 = best_launch.chunk;
             for (int ch : {2, 1, 8, 16}) {
-                if (ch == chunk0) continue;
+                if (ch == chunk0 || table) continue;
                 gpint::LaunchCfg cfg = best_launch;
                 cfg.chunk = ch;
                 try_cfg(cfg);
             }
             // the heavy-root threshold T (roots whose hub endpoint is below it
             // are split), where roots are split at all
-            if (best_launch.split_ways > 1) {
+            if (best_launch.split_ways > 1 && !table) {
                 const int64_t t0v = best_launch.split_vertices;
                 for (int64_t tv : {64, 1024, 4096}) {
                     if (tv == t0v) continue;
@@ -638,9 +645,17 @@ gp_status gp_plan_tune(const gp_graph* g, const gp_plan* p, const gp_tune_opts* 
                 try_cfg(cfg);
             }
         }
+        if (st == GP_OK && on_table(best)) {
+            // its per-root counts and slices run on the general search: at the default
+            // shape, as none was measured
+            const int waves = best_launch.waves_per_cu;
+            best_launch = gpint::default_launch(cands[best].desc);
+            best_launch.waves_per_cu = waves;
+        }
         best_launch.root_stride = 1;
         best_launch.root_offset = 0;
         best_launch.budget_ms = 0;
+        best_launch.table = 0;
         if (st == GP_OK) {
             np->order = cands[best].order;
             np->set = cands[best].rel;
