@@ -498,10 +498,12 @@ gp_status gp_batch_run(gp_batch* b, void* stream, uint64_t* out);
  * stride s partition every plan's embeddings (for an IEP plan with an
  * over-count above 1 a sample's raw total is divided with the quotient
  * rounded down, so its parts may add up to less, by under one per part).
- * Copies the new task table to the device before returning (waits
- * for `stream`); the captured graph is unchanged. Errors: GP_ERR_ARG.
+ * Waits for `stream` and captures the batch again. Errors: GP_ERR_ARG.
  */
 gp_status gp_batch_set_sample(gp_batch* b, int64_t root_stride, int64_t root_offset, void* stream);
+
+/* How the batch launches its plan `plan`, at its present sample (as gp_count_shape). */
+gp_status gp_batch_shape(const gp_batch* b, int32_t plan, gp_shape* out);
 
 /*
  * Pick the launch shape of a batch of these plans on g by measurement: one

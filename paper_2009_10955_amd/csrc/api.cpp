@@ -822,6 +822,11 @@ gp_status gp_batch_run(gp_batch* b, void* stream, uint64_t* out) {
     return batch_counts(b->descs, b->cfgs, b->slot, b->host_res, out);
 }
 
+gp_status gp_batch_shape(const gp_batch* b, int32_t plan, gp_shape* out) {
+    if (!b || !out || plan < 0 || plan >= b->np) return GP_ERR_ARG;
+    return gpint::describe_batch(b->st, b->slot[plan], out);
+}
+
 gp_status gp_batch_set_sample(gp_batch* b, int64_t root_stride, int64_t root_offset, void* stream) {
     if (!b || root_stride < 1 || root_offset < 0) return GP_ERR_ARG;
     DeviceGuard dgd(b->g->dg.device);

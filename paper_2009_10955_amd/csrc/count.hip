@@ -869,8 +869,10 @@ static gp_status batch_layout(const DeviceGraph& g, const GpPlanDesc* descs, con
         // their descriptors are its kernel arguments)
         const int iep_depth = descs[i].iep;
         const int ksize = std::min((int)descs[i].k, 7);  // sizes 7 and 8 share a kernel
-        const bool table = whole[i] && table_rule(g, descs[i]);
-        if (b->runs.empty() || table || b->runs.back().table || b->runs.back().group != bp.group || b->runs.back().leaf != bp.leaf ||
+        // runs are laid out for every sample that the batch may be set to: a plan that may
+        // run on path tables is alone, whether its present sample does or not
+        const bool may_table = whole[i] && cfgs[i].table >= 0 && table_rule(g, descs[i]);
+        if (b->runs.empty() || may_table || b->runs.back().may_table || b->runs.back().group != bp.group || b->runs.back().leaf != bp.leaf ||
             b->runs.back().iep != iep_depth || std::min(b->runs.back().kmin, 7) != ksize ||
             b->runs.back().p1 - b->runs.back().p0 >= kRunMaxPlans || cfgs[i].batch_runs == 2) {
             BatchRun r;
@@ -879,7 +881,8 @@ static gp_status batch_layout(const DeviceGraph& g, const GpPlanDesc* descs, con
             r.leaf = bp.leaf;
             r.iep = iep_depth;
             r.kmin = r.kmax = descs[i].k;
-            r.table = table;
+            r.may_table = may_table;
+            r.table = may_table && uses_table(g, descs[i], cfgs[i]);
             r.tab_waves = table_waves(g, descs[i]);
             b->runs.push_back(r);
         }
@@ -888,7 +891,7 @@ static gp_status batch_layout(const DeviceGraph& g, const GpPlanDesc* descs, con
         b->runs.back().kmax = std::max(b->runs.back().kmax, (int)descs[i].k);
         b->runs.back().waves_per_cu = std::max(b->runs.back().waves_per_cu, cfgs[i].waves_per_cu);
         bp.tag_base = 0;
-        if (bp.leaf == 4 && !table && !descs[i].iep && g.n_hubs > 0 && memo_eligible(descs[i]) &&
+        if (bp.leaf == 4 && !may_table && !descs[i].iep && g.n_hubs > 0 && memo_eligible(descs[i]) &&
             tag_next + n_all < (int64_t(1) << 31) - 1) {  // below the IEP memo's tags
             bp.tag_base = (uint32_t)tag_next - 1;  // tags tag_base + root + 1 >= tag_next
             tag_next += n_all;
@@ -938,9 +941,9 @@ static int64_t batch_blocks(const DeviceGraph& g, int waves_per_cu, int slots_pe
     return blocks;
 }
 
-// Group slots (scratch and memo tables) a run's launch addresses.
-static int64_t run_group_slots(const BatchRun& r) {
-    return r.table ? r.blocks * r.tab_waves : r.blocks * (kBlock / 64) * (64 / r.group);
+// Group slots (scratch and memo tables) a run's launch addresses, on path tables or not.
+static int64_t run_group_slots(const BatchRun& r, bool table) {
+    return table ? r.table_blocks * r.tab_waves : r.plain_blocks * (kBlock / 64) * (64 / r.group);
 }
 
 gp_status batch_prepare(const DeviceGraph& g, const GpPlanDesc* descs, const LaunchCfg* cfgs,
@@ -955,16 +958,19 @@ gp_status batch_prepare(const DeviceGraph& g, const GpPlanDesc* descs, const Lau
     // every run at its own width and residency; the regions fit the largest
     int64_t slots = 0;
     for (BatchRun& r : b.runs) {
-        r.blocks = batch_blocks(g, std::min(waves_per_cu, r.waves_per_cu), 64 / r.group, b.nbuf, b.cap, b.use_memo);
-        if (r.table) {
+        r.plain_blocks =
+            batch_blocks(g, std::min(waves_per_cu, r.waves_per_cu), 64 / r.group, b.nbuf, b.cap, b.use_memo);
+        slots = std::max(slots, run_group_slots(r, false));
+        if (r.may_table) {
             // within the scratch budget, as batch_blocks keeps the others
-            r.blocks = table_blocks(g, descs[r.p0], std::min(waves_per_cu, r.waves_per_cu),
-                                    std::max<int64_t>(1, r.n_roots));
+            r.table_blocks = table_blocks(g, descs[r.p0], std::min(waves_per_cu, r.waves_per_cu),
+                                          std::max<int64_t>(1, r.n_roots));
             if (b.nbuf > 0)
-                r.blocks = std::max<int64_t>(
-                    1, std::min(r.blocks, (int64_t(16) << 30) / (r.tab_waves * b.nbuf * b.cap * 4)));
+                r.table_blocks = std::max<int64_t>(
+                    1, std::min(r.table_blocks, (int64_t(16) << 30) / (r.tab_waves * b.nbuf * b.cap * 4)));
+            slots = std::max(slots, run_group_slots(r, true));
         }
-        slots = std::max(slots, run_group_slots(r));
+        r.blocks = r.table ? r.table_blocks : r.plain_blocks;
     }
     b.memo_words = b.use_memo ? slots * (int64_t)g.n_hubs : 0;
     // room for the IEP memo's most ways when an eligible IEP plan runs alone
@@ -998,15 +1004,36 @@ gp_status batch_update(const DeviceGraph& g, BatchState* st, const GpPlanDesc* d
     for (size_t i = 0; same && i < b.runs.size(); ++i)
         same = b.runs[i].p0 == st->runs[i].p0 && b.runs[i].p1 == st->runs[i].p1 &&
                b.runs[i].group == st->runs[i].group && b.runs[i].leaf == st->runs[i].leaf &&
-               b.runs[i].iep == st->runs[i].iep;
+               b.runs[i].iep == st->runs[i].iep && b.runs[i].may_table == st->runs[i].may_table;
     if (!same) return GP_ERR_ARG;  // the shapes the buffers were carved for must not change
     (void)stream;
     // launches take their task ranges as kernel arguments: the caller
     // enqueues (or captures) the batch again
-    for (size_t i = 0; i < b.runs.size(); ++i) b.runs[i].blocks = st->runs[i].blocks;  // the carved grids
+    for (size_t i = 0; i < b.runs.size(); ++i) {
+        BatchRun& r = b.runs[i];
+        r.table_blocks = st->runs[i].table_blocks;  // the carved grids
+        r.plain_blocks = st->runs[i].plain_blocks;
+        r.blocks = r.table ? r.table_blocks : r.plain_blocks;
+    }
     st->runs = b.runs;
     st->h_plans = b.h_plans;
     return GP_OK;
+}
+
+gp_status describe_batch(const BatchState& st, int plan, gp_shape* out) {
+    for (const BatchRun& r : st.runs) {
+        if (plan < r.p0 || plan >= r.p1) continue;
+        const BatchPlan& bp = reinterpret_cast<const BatchPlan*>(st.h_plans.data())[plan];
+        const bool iep = st.h_descs[plan].iep != 0;
+        out->table = r.table ? 1 : 0;
+        out->memo = st.memo_words > 0 && (iep ? iep_memo_eligible(st.h_descs[plan]) : bp.tag_base != 0) ? 1 : 0;
+        out->group = r.table ? 64 : r.group;
+        out->chunk = r.table ? table_chunk(st.h_descs[plan], r.blocks, r.n_roots) : bp.chunk;
+        out->blocks = (int32_t)r.blocks;
+        out->threads = r.table ? r.tab_waves * 64 : kBlock;
+        return GP_OK;
+    }
+    return GP_ERR_ARG;
 }
 
 gp_status batch_enqueue(const DeviceGraph& g, const BatchState& st, hipStream_t stream) {
@@ -1142,7 +1169,7 @@ gp_status arena_launch(const DeviceGraph& g, BatchArena* ar, const GpPlanDesc* d
                            : batch_blocks(g, std::min(ar->waves_per_cu, r.waves_per_cu), 64 / r.group, b.nbuf, b.cap,
                                           b.use_memo);
         r.blocks = std::max<int64_t>(1, std::min(r.blocks, room / per_block));
-        slots = std::max(slots, run_group_slots(r));
+        slots = std::max(slots, r.blocks * per_block);
     }
     b.memo_words = b.use_memo ? slots * (int64_t)g.n_hubs : 0;
     if (b.memo_words > ar->memo_words_cap) {

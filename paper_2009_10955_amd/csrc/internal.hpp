@@ -127,7 +127,9 @@ struct BatchRun {
     // per-plan machinery of the batched kernel only slows down; its task
     // space as that kernel takes it
     bool solo = false;
-    bool table = false;  // solo, by the table kernel
+    bool may_table = false;  // a whole count of it is solo, by the table kernel
+    bool table = false;      // this one, of its sample, is
+    int64_t table_blocks = 1, plain_blocks = 1;  // its grid either way
     int tab_waves = 16;  // wavefronts of its blocks
     const int2* roots = nullptr;
     int64_t n_roots = 0, root_offset = 0, root_stride = 1, n_tasks = 0, split_roots = 0;
@@ -194,6 +196,8 @@ gp_status batch_update(const DeviceGraph& g, BatchState* st, const GpPlanDesc* d
 // key.
 int batch_shape_key(const GpPlanDesc& d, const LaunchCfg& c, int min_group);
 // Enqueue counter reset + one launch per run on `stream` (no allocation).
+// How the batch launches its plan at position `plan` of the batch order: see gp_batch_shape.
+gp_status describe_batch(const BatchState& st, int plan, gp_shape* out);
 gp_status batch_enqueue(const DeviceGraph& g, const BatchState& st, hipStream_t stream);
 void batch_release(BatchState* st);
 // A plan's 128-bit batch total {low, flags, busy, high} divided by its IEP

@@ -151,6 +151,7 @@ SIGNATURES = {
     "gp_batch_tune": (_I32, [_P, _P, _I32, _P, ctypes.POINTER(Launch), ctypes.POINTER(ctypes.c_double)]),
     "gp_batch_run": (_I32, [_P, _P, _P]),
     "gp_batch_set_sample": (_I32, [_P, _I64, _I64, _P]),
+    "gp_batch_shape": (_I32, [_P, _I32, ctypes.POINTER(Shape)]),
     "gp_free_batch": (None, [_P]),
     "gp_server_opts_default": (None, [ctypes.POINTER(ServerOpts)]),
     "gp_server_create": (_I32, [_P, _I32, ctypes.POINTER(ServerOpts), ctypes.POINTER(_P)]),
@@ -555,6 +556,12 @@ class Batch:
         run on (see gp_batch_set_sample)."""
         _check(_lib().gp_batch_set_sample(self._h, int(root_stride), int(root_offset),
                                           _stream_handle(stream)), "gp_batch_set_sample")
+
+    def shape(self, plan: int) -> dict:
+        """How plan number `plan` is launched at the present sample (see gp_batch_shape)."""
+        out = Shape()
+        _check(_lib().gp_batch_shape(self._h, int(plan), ctypes.byref(out)), "gp_batch_shape")
+        return {f: getattr(out, f) for f, _ in Shape._fields_}
 
     def close(self) -> None:
         if self._h:

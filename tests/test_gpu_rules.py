@@ -223,3 +223,26 @@ def test_tuning_keeps_the_default_shape_of_table_plans():
            {k: v for k, v in plan.launch().items() if k not in skip}
     assert gp.count(graph, tuned) == gp.count(graph, plan)
     graph.close()
+
+
+# ------------------------------------------------------- batches
+
+def test_batches_follow_the_sampling_rule():
+    """A batch set to a sparse sample with inclusion-exclusion leaves the table, as a count
+    of that sample does, and takes it again; counts are those of the samples."""
+    graph = gp.Graph.from_csr(_hubs(3000, 6000, 12, 2500), device=True)
+    st = graph.stats()
+    plans = [gp.Plan(*P["house"], stats=st, **HOUSE), gp.Plan(*P["4-clique"], stats=st),
+             gp.Plan(*P["5-cycle"], stats=st)]
+    batch = gp.Batch(graph, plans)
+    sparse = st.max_degree // 1024 + 1
+    for stride, offset in ((1, 0), (sparse, 1), (64, 5), (1, 0), (sparse, 0), (1, 0)):
+        batch.set_sample(stride, offset)
+        la = dict(root_stride=stride, root_offset=offset)
+        for i, p in enumerate(plans):
+            assert batch.shape(i)["table"] == gp.count_shape(graph, p, **la)["table"], (stride, i)
+        assert batch.shape(0)["table"] == (stride == 1) and batch.shape(1)["table"] == 0
+        for _ in range(2):
+            assert batch.run() == [gp.count(graph, p, **la) for p in plans], stride
+    batch.close()
+    graph.close()
