@@ -246,3 +246,21 @@ def test_batches_follow_the_sampling_rule():
             assert batch.run() == [gp.count(graph, p, **la) for p in plans], stride
     batch.close()
     graph.close()
+
+
+# ------------------------------------------------------- serving
+
+def test_admission_estimates_what_is_served(rmat16):
+    """With max_query_ms a query's slices run on the general search, also where a whole
+    count of its plan runs on path tables, ten times faster: a limit between the two
+    refuses it, and one above both serves it."""
+    plan = gp.Plan(*P["5-cycle"], stats=rmat16.stats())
+    assert gp.count_shape(rmat16, plan)["table"] == 1
+    table_ms = gp.estimate(rmat16, plan)["ms"]
+    for limit, want in ((3 * table_ms, -10), (100 * table_ms, 0)):
+        srv = gp.Server([rmat16], max_query_ms=limit)
+        status, count, _ = srv.wait(srv.submit(0, *P["5-cycle"]))
+        srv.close()
+        assert status == want, (limit, status)
+        if want == 0:
+            assert count == gp.count(rmat16, plan)
