@@ -522,10 +522,12 @@ static SplitPlan split_plan(const DeviceGraph& g, const GpPlanDesc& d, const Lau
     return sp;
 }
 
-int64_t task_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCfg& cfg) {
+int64_t task_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCfg& cfg, TaskSplit* split) {
     int64_t n = 0;
     (void)pick_roots(g, d.root_cut, &n);
     const SplitPlan sp = split_plan(g, d, cfg, MODE_PLAIN, n, 1, 0);
+    split->tasks = sp.roots * sp.ways;
+    split->ways = sp.ways;
     return n + sp.roots * (sp.ways - 1);
 }
 

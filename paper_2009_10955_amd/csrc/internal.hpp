@@ -7,6 +7,7 @@
 
 #include "gp.h"
 #include "plan_desc.h"
+#include "slices.hpp"
 
 namespace gpint {
 
@@ -232,8 +233,9 @@ void pool_drop_graph(int device);  // it is gone (its work has finished)
 
 // Number of root tasks of a descriptor (its cut picks the root array).
 int64_t root_task_count(const DeviceGraph& g, const GpPlanDesc& d);
-// Tasks of plan d over g with cfg's root splitting (no sampling).
-int64_t task_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCfg& cfg);
+// Tasks of plan d over g with cfg's root splitting (no sampling), and which of them
+// are shares of a root.
+int64_t task_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCfg& cfg, TaskSplit* split);
 
 // Launch defaults for a plan descriptor, and overriding them with the
 // non-zero fields of a caller's gp_launch.

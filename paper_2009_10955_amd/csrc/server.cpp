@@ -42,6 +42,7 @@
 #include <vector>
 
 #include "api_internal.hpp"
+#include "slices.hpp"
 
 namespace {
 
@@ -59,6 +60,7 @@ struct Query {
     std::vector<int32_t> edges;
     const gp_plan* plan = nullptr;  // owned by the plan cache
     int64_t n_tasks = 0, progress = 0, slice = 0;
+    gpint::TaskSplit split;
     int64_t launched = 0;  // tasks handed to launches (progress: tasks collected)
     int inflight = 0;      // launches in flight that hold a slice of this query
     uint64_t count = 0;
@@ -92,7 +94,7 @@ struct gp_server {
     struct Launch {
         int graph = 0, slot = 0;
         std::vector<Query*> qs;
-        std::vector<int64_t> slices;
+        std::vector<int64_t> slices, firsts;  // tasks of each query's slice, and where it starts
     };
     std::deque<Launch> inflight;
     std::vector<int> slot_busy;  // [graph * 2 + slot]
@@ -180,7 +182,7 @@ gp_status plan_query(gp_server* S, Query* q) {
     }
     q->plan = it->second;
     // slices cut the query's task space, in which a split root counts once per task
-    q->n_tasks = gpint::task_count(S->graphs[q->graph]->dg, q->plan->desc, server_launch(S));
+    q->n_tasks = gpint::task_count(S->graphs[q->graph]->dg, q->plan->desc, server_launch(S), &q->split);
     return GP_OK;
 }
 
@@ -430,6 +432,7 @@ void worker_main(gp_server* S) {
                 offs.push_back(q->launched);
                 L.qs.push_back(q);
                 L.slices.push_back(c);
+                L.firsts.push_back(q->launched);
             }
             if (L.qs.empty()) continue;
             const int idx = 2 * g + slot;
@@ -494,14 +497,9 @@ void worker_main(gp_server* S) {
                 finish(S, q, fs);
                 continue;
             }
-            // next slice: this query's task rate times its fair share of the target
-            const double t_q = std::max(1e-7, (double)r[4 * i + 2] * tick_s / groups);
-            const double rate = (double)L.slices[i] / t_q;
-            double next = rate * fair;
-            // the first tasks are the heaviest, so the rate errs low: let it grow fast
-            next = std::min(next, 32.0 * (double)L.slices[i] + 1);
-            next = std::max(next, 64.0);
-            q->slice = (int64_t)std::min(next, 1e12);
+            // next slice: this query's rate times its fair share of the target
+            const double t_q = (double)r[4 * i + 2] * tick_s / groups;
+            q->slice = gpint::next_slice(q->split, L.firsts[i], L.slices[i], t_q, q->launched, fair);
         }
     }
     for (int i = 0; i < 2 * ng; ++i) {
