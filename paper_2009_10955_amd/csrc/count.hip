@@ -165,16 +165,19 @@ int table_waves(const gpint::DeviceGraph& g, const GpPlanDesc& d);
 
 // Whether the table pays for its fills. A fill costs a block a fixed time (clearing
 // 16 to 64 KB of LDS, barriers), 6 to 8 us per root edge where every root has one. What
-// it saves is a walk per binding of the level above the last, of mean_deg
-// elements, where the table covers it; the eighth is what a lookup costs itself.
-// So the line is a product of these, per root edge, above which the table won on uniform, Chung-Lu and
-// R-MAT graphs of 1,000 to 1M vertices. Table and general kernel at saved / least
-// (uniform graphs, vertices and edges): 5-cycle 20K, 160K 0.8: 2.03 and 1.32 ms; 100K, 1.6M 1.8:
-// 57 and 72; 20K, 400K 11: 6.5 and 26; 1M, 8M 0.3: 219 and 86; a 4-regular torus of 1M
-// vertices 0: 26 and 1.2. 4-cycle 1M, 8M: 37 and 6.3, 20K, 1M 1.7: 4.5 and 10.6;
-// R-MAT (65,536, 400K) 7.6: 2.1 and 2.6. 6-cycle 100K, 400K 0.2: 18 and 9, 40K, 200K 1.1: 6.4
-// and 7.5, 100K, 800K 2.3: 129 and 124, 20K, 160K 6.8: 7.6 and 19.6. House with inclusion-exclusion 20K, 400K 0.94: 0.81 and
-// 0.73, 20K, 1M 5.8: 4.5 and 11.
+// it saves is a walk per binding of the level above the last, where the table covers
+// it; the eighth is what a lookup costs itself. The lines lie where the table
+// began to win on uniform, Chung-Lu and R-MAT graphs of 200 to 1M vertices (below, V, E:
+// vertices, edges of uniform graphs; saved as a multiple of the line; table and general kernel).
+// Four levels: 4-cycle 1M V, 8M E below 0: 37 and 6.3 ms; 20K, 160K 0.5: 0.37 and
+// 0.16; 20K, 400K 1.1: 1.23 and 1.34; 20K, 1M 2.8: 4.5 and 10.6. More levels, a walk counted
+// with mean_deg elements: 5-cycle on a 4-regular torus of 1M V 0: 26 and 1.2; 1M, 8M 0:
+// 219 and 86; 20K, 160K 0.8: 2.03 and 1.32; 100K, 1.6M 1.8: 57 and 72; 20K, 400K 11:
+// 6.5 and 26. 6-cycle 100K, 400K 0.2: 18 and 9; 40K, 200K 1.1: 6.4 and 7.5; 20K, 160K 6.8:
+// 7.6 and 19.6. House with inclusion-exclusion 20K, 400K 0.94: 0.81 and 0.73; 20K, 1M 5.8:
+// 4.5 and 11.
+// A small graph's roots do not fill the device, and a block finishes one sooner than a
+// group: 4-cycle on R-MAT (451 V, 2,541 E) 48 and 110 us, G(606, 5,861 E) 61 and 66.
 bool table_pays(const gpint::DeviceGraph& g, const GpPlanDesc& d) {
     const int waves = table_waves(g, d);
     const int t = waves == 4 ? 0 : (waves == 8 ? 1 : 2);
@@ -182,7 +185,14 @@ bool table_pays(const gpint::DeviceGraph& g, const GpPlanDesc& d) {
                       gpint::kTableSizes[2] == table_max(16),
                   "entries counted for the tables' sizes");
     const double covered = (double)g.first_entries[t] / (double)std::max<int64_t>(1, g.nnz);
-    const double saved = expected_bindings(g, d, d.iep ? d.k - 3 : d.k - 2) * g.mean_deg * (covered - 0.125);
+    if (g.nnz <= 2 * 8192 && covered > 0.99) return true;
+    double saved = expected_bindings(g, d, d.iep ? d.k - 3 : d.k - 2) * (covered - 0.125);
+    if (d.k == 4) {
+        const int hub = d.root_cut == 1 ? 1 : 0;
+        const bool below = d.root_cut != 0 && ((d.lv[2].hi_src >> hub) & 1);  // candidates of higher degree than the hub
+        return saved >= (below ? 3.5 : 10);
+    }
+    saved *= g.mean_deg;
     return saved >= (d.iep ? 1200 : (waves == 4 ? 600 : (d.k == 5 ? 6000 : 12000)));
 }
 
