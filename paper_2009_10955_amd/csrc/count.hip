@@ -669,6 +669,7 @@ gp_status launch_count(const DeviceGraph& g, const GpPlanDesc& d, const LaunchCf
     const gp_status shaped =
         count_shape(g, d, launch, account ? MODE_ACCOUNT : (per_root ? MODE_PER_ROOT : MODE_PLAIN), ws, &z);
     if (shaped != GP_OK) return shaped;
+    if (z.table && busy) z.fn = pick_table(d, MODE_SAMPLE, z.tab_waves);
     const LaunchCfg& cfg = z.cfg;
     const size_t scratch_bytes = z.scratch_bytes;
     const bool use_memo = z.use_memo;

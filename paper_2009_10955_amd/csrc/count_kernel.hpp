@@ -64,9 +64,10 @@ constexpr int table_max(int waves) { return waves * 2048; }
 constexpr int kFiltWords = 2048;
 constexpr int kIepTableWaves = 8;  // its blocks: 32 KB of table, 8 of filter, three blocks per CU
 
-// Kernel modes: plain count, per-root counts, or accounting of the bytes the
-// search reads and writes (never timed).
-enum { MODE_PLAIN = 0, MODE_PER_ROOT = 1, MODE_ACCOUNT = 2 };
+// Kernel modes: plain count, per-root counts, accounting of the bytes the
+// search reads and writes (never timed), or (table kernels: clocks in the plain one cost a
+// small 4-cycle count 3 of 55 us) a plain count that reports its busy time.
+enum { MODE_PLAIN = 0, MODE_PER_ROOT = 1, MODE_ACCOUNT = 2, MODE_SAMPLE = 3 };
 
 // Inclusion-exclusion over at most this many innermost levels.
 constexpr int kIepMaxN = GP_IEP_MAX_INNER;

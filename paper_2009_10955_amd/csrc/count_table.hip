@@ -84,7 +84,7 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(8))
     __shared__ int32_t s_len[kWaves][GP_DESC_MAX_BUILDS];
     __shared__ int64_t s_chunk;
     __shared__ int32_t s_cur;
-    __shared__ uint64_t s_beyond[kWaves];  // per wavefront: clock ticks that only a sample spends
+    __shared__ uint64_t s_beyond[MODE == MODE_SAMPLE ? kWaves : 1];  // per wavefront: clock ticks that only a sample spends
     Ctx<64> c;
     const int wave = uni<64>((int)(threadIdx.x / 64));
     c.row_ptr = a.row_ptr;
@@ -106,8 +106,10 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(8))
     c.tab = (const uint16_t*)s_tab;
     c.tab_n = a.tab_n;
     c.filt = nullptr;
-    const uint64_t t_begin = a.busy ? wall_clock64() : 0;
-    c.deadline = a.busy && a.budget_ticks ? t_begin + a.budget_ticks : 0;
+    // with a.busy
+    constexpr bool kTimed = MODE == MODE_SAMPLE;
+    const uint64_t t_begin = kTimed ? wall_clock64() : 0;
+    c.deadline = kTimed && a.budget_ticks ? t_begin + a.budget_ticks : 0;
     uint64_t chunk_max = 0;
     bool stopped = false;
     uint64_t acc = 0, carry = 0;
@@ -117,7 +119,7 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(8))
     // endpoint only raises the cut
     const int hub = d.root_cut == 1 ? 1 : (d.root_cut == 2 ? 0 : -1), rest = 1 - ll.pre_list;
     const bool shared = hub == ll.pre_list && !(((ll.inj | ll.lo_src) >> rest) & 1u);
-    if (c.g.gl == 0) s_beyond[wave] = 0;
+    if (kTimed && c.g.gl == 0) s_beyond[wave] = 0;
     int32_t cur_p = -1, cur_lo = 0, cur_hi = 0, cur_pos = 0;
     c.out = -1;
     if (threadIdx.x == 0) s_cur = (int)(blockIdx.x & (kCursors - 1));
@@ -131,7 +133,7 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(8))
         const int64_t q = uni64<64>(s_chunk);
         __syncthreads();
         if (q < 0) break;
-        const uint64_t t_chunk = a.busy ? wall_clock64() : 0;
+        const uint64_t t_chunk = kTimed ? wall_clock64() : 0;
         const int64_t r1 = min((q + 1) * a.chunk, a.n_roots);
         for (int64_t r = q * a.chunk; r < r1; ++r) {
             const int2 e = a.roots[a.root_offset + r * a.root_stride];
@@ -147,7 +149,7 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(8))
             const Set P = c.nbr_u(p);
             const int q = 1 - ll.pre_list;
             const int32_t out = (ll.inj >> q) & 1u ? v[q] : -1;
-            const uint64_t t_fill = a.busy ? wall_clock64() : 0;
+            const uint64_t t_fill = kTimed ? wall_clock64() : 0;
             const bool anew = p != cur_p || lo != cur_lo || hi < cur_hi || out != c.out;
             // every wavefront of the block takes the same way here
             if (anew) {
@@ -166,7 +168,7 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(8))
             cur_lo = lo;
             cur_hi = hi;
             __syncthreads();
-            if (a.busy && shared && a.root_stride > 1) {
+            if (kTimed && shared && a.root_stride > 1) {
                 // a sampled root starts a table, or adds the lists of the roots left out;
                 // a whole count does either once for a run of them
                 const uint64_t dt = wall_clock64() - t_fill;
@@ -180,7 +182,7 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(8))
             search<K, 2, 64, 5, MODE, 0>(d, c, v, acc, carry);
             __syncthreads();
         }
-        if (a.busy) {
+        if constexpr (kTimed) {
             const uint64_t now = wall_clock64();
             chunk_max = max(chunk_max, now - t_chunk);
             // the whole block stops together
@@ -199,7 +201,7 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(8))
         unsigned long long* slot = a.queue + (blockIdx.x & (kSlots - 1)) * kSlotWords;
         publish128(&slot[SLOT_LO], &slot[SLOT_HI], s, s_hi);
         if (stopped) atomicOr(&a.result[1], 4ull);
-        if (a.busy) {
+        if constexpr (kTimed) {
             atomicAdd(&a.busy[0], (unsigned long long)(wall_clock64() - t_begin - s_beyond[wave]));
             atomicAdd(&a.busy[1], 1ull);
             atomicMax(&a.busy[2], (unsigned long long)chunk_max);
@@ -227,7 +229,7 @@ __global__ __launch_bounds__(kIepWaves * 64) __attribute__((amdgpu_waves_per_eu(
     __shared__ int32_t s_len[kIepWaves][GP_DESC_MAX_BUILDS];
     __shared__ int64_t s_chunk;
     __shared__ int32_t s_cur, s_next;
-    __shared__ uint64_t s_beyond[kIepWaves];  // as above
+    __shared__ uint64_t s_beyond[MODE == MODE_SAMPLE ? kIepWaves : 1];  // as above
     Ctx<64> c;
     const int wave = uni<64>((int)(threadIdx.x / 64));
     c.row_ptr = a.row_ptr;
@@ -250,13 +252,15 @@ __global__ __launch_bounds__(kIepWaves * 64) __attribute__((amdgpu_waves_per_eu(
     c.tab_n = a.tab_n;
     c.out = -1;
     c.filt = s_filt;
-    const uint64_t t_begin = a.busy ? wall_clock64() : 0;
-    c.deadline = a.busy && a.budget_ticks ? t_begin + a.budget_ticks : 0;
+    // with a.busy
+    constexpr bool kTimed = MODE == MODE_SAMPLE;
+    const uint64_t t_begin = kTimed ? wall_clock64() : 0;
+    c.deadline = kTimed && a.budget_ticks ? t_begin + a.budget_ticks : 0;
     uint64_t chunk_max = 0;
     bool stopped = false;
     uint64_t acc = 0, carry = 0;
     const bool second = d.it[d.iep_sum - 1].op[0] == 1;
-    if (c.g.gl == 0) s_beyond[wave] = 0;
+    if (kTimed && c.g.gl == 0) s_beyond[wave] = 0;
     int32_t cur_p = -1;
     if (threadIdx.x == 0) s_cur = (int)(blockIdx.x & (kCursors - 1));
     __syncthreads();
@@ -268,7 +272,7 @@ __global__ __launch_bounds__(kIepWaves * 64) __attribute__((amdgpu_waves_per_eu(
         __syncthreads();
         const int64_t q = uni64<64>(s_chunk);
         if (q < 0) break;
-        const uint64_t t_chunk = a.busy ? wall_clock64() : 0;
+        const uint64_t t_chunk = kTimed ? wall_clock64() : 0;
         const int64_t r1 = min((q + 1) * a.chunk, a.n_roots);
         for (int64_t r = q * a.chunk; r < r1;) {
             // the chunk's next run of roots of one p (a chunk has at most 64)
@@ -283,9 +287,9 @@ __global__ __launch_bounds__(kIepWaves * 64) __attribute__((amdgpu_waves_per_eu(
             const int run = other ? __builtin_ctzll(other) : 64;
             __syncthreads();  // the last run's readers are done
             if (threadIdx.x == 0) s_next = 0;
-            const uint64_t t_fill = a.busy ? wall_clock64() : 0;
+            const uint64_t t_fill = kTimed ? wall_clock64() : 0;
             int32_t of_run = run;  // roots that a whole count takes with one fill
-            if (a.busy && a.root_stride > 1) {
+            if (kTimed && a.root_stride > 1) {
                 int32_t L = 1;
                 of_run = whole_run(c, p, c.nbr_u(p), a.whole_chunk, L);
             }
@@ -305,7 +309,7 @@ __global__ __launch_bounds__(kIepWaves * 64) __attribute__((amdgpu_waves_per_eu(
                 cur_p = p;
             }
             __syncthreads();
-            if (a.busy && anew && c.g.gl == 0) s_beyond[wave] += beyond_share(wall_clock64() - t_fill, run, of_run);
+            if (kTimed && anew && c.g.gl == 0) s_beyond[wave] += beyond_share(wall_clock64() - t_fill, run, of_run);
             for (;;) {
                 int t = 0;
                 if (c.g.gl == 0) t = atomicAdd(&s_next, 1);
@@ -320,7 +324,7 @@ __global__ __launch_bounds__(kIepWaves * 64) __attribute__((amdgpu_waves_per_eu(
                 v[1] = uni<64>(e.y);
                 if (run_builds<K, 64, MODE>(d, c, 1, v)) search<K, 2, 64, 5, MODE, 2>(d, c, v, acc, carry);
             }
-            if (a.busy) {
+            if constexpr (kTimed) {
                 // a run of one sampled root leaves the other wavefronts waiting
                 const uint64_t t_wait = wall_clock64();
                 __syncthreads();
@@ -328,7 +332,7 @@ __global__ __launch_bounds__(kIepWaves * 64) __attribute__((amdgpu_waves_per_eu(
             }
             r += run;
         }
-        if (a.busy) {
+        if constexpr (kTimed) {
             const uint64_t now = wall_clock64();
             chunk_max = max(chunk_max, now - t_chunk);
             if (__syncthreads_or(c.deadline && now > c.deadline)) {
@@ -347,7 +351,7 @@ __global__ __launch_bounds__(kIepWaves * 64) __attribute__((amdgpu_waves_per_eu(
         unsigned long long* slot = a.queue + (blockIdx.x & (kSlots - 1)) * kSlotWords;
         publish128(&slot[SLOT_LO], &slot[SLOT_HI], s, s_hi);
         if (stopped) atomicOr(&a.result[1], 4ull);
-        if (a.busy) {
+        if constexpr (kTimed) {
             atomicAdd(&a.busy[0], (unsigned long long)(wall_clock64() - t_begin - s_beyond[wave]));
             atomicAdd(&a.busy[1], 1ull);
             atomicMax(&a.busy[2], (unsigned long long)chunk_max);
@@ -360,9 +364,11 @@ __global__ __launch_bounds__(kIepWaves * 64) __attribute__((amdgpu_waves_per_eu(
 // The kernel for IEP plans: k from 5 on (two inner levels below one more outer
 // level than the root edge).
 KernelFn pick_table_iep_kernel(int k, int mode) {
-    if (mode != MODE_PLAIN && mode != MODE_ACCOUNT) return nullptr;
-#define GP_TABLE_CASE(KK) \
-    case KK: return mode == MODE_PLAIN ? table_iep_kernel<KK, MODE_PLAIN> : table_iep_kernel<KK, MODE_ACCOUNT>;
+#define GP_TABLE_CASE(KK)                                                 \
+    case KK:                                                              \
+        if (mode == MODE_PLAIN) return table_iep_kernel<KK, MODE_PLAIN>;  \
+        if (mode == MODE_SAMPLE) return table_iep_kernel<KK, MODE_SAMPLE>; \
+        return mode == MODE_ACCOUNT ? table_iep_kernel<KK, MODE_ACCOUNT> : nullptr;
     switch (k) {
         GP_TABLE_CASE(5)
         GP_TABLE_CASE(6)
@@ -373,12 +379,17 @@ KernelFn pick_table_iep_kernel(int k, int mode) {
 #undef GP_TABLE_CASE
 }
 
+template <int K, int W>
+static KernelFn table_kernel_of(int mode) {
+    if (mode == MODE_PLAIN) return table_kernel<K, MODE_PLAIN, W>;
+    if (mode == MODE_SAMPLE) return table_kernel<K, MODE_SAMPLE, W>;
+    return mode == MODE_ACCOUNT ? table_kernel<K, MODE_ACCOUNT, W> : nullptr;
+}
+
 KernelFn pick_table_kernel(int k, int mode, int waves) {
-    if ((mode != MODE_PLAIN && mode != MODE_ACCOUNT) || (waves != 4 && waves != 16)) return nullptr;
-#define GP_TABLE_CASE(KK)                                                                                \
-    case KK:                                                                                             \
-        if (waves == 4) return mode == MODE_PLAIN ? table_kernel<KK, MODE_PLAIN, 4> : table_kernel<KK, MODE_ACCOUNT, 4>; \
-        return mode == MODE_PLAIN ? table_kernel<KK, MODE_PLAIN, 16> : table_kernel<KK, MODE_ACCOUNT, 16>;
+    if (waves != 4 && waves != 16) return nullptr;
+#define GP_TABLE_CASE(KK) \
+    case KK: return waves == 4 ? table_kernel_of<KK, 4>(mode) : table_kernel_of<KK, 16>(mode);
     switch (k) {
         GP_TABLE_CASE(4)
         GP_TABLE_CASE(5)
