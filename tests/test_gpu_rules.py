@@ -264,3 +264,72 @@ def test_admission_estimates_what_is_served(rmat16):
         assert status == want, (limit, status)
         if want == 0:
             assert count == gp.count(rmat16, plan)
+
+
+# ------------------------------------------------------- the general search's paths, off the tables
+
+# 5-vertex patterns whose last level is N(x) & N(root endpoint), cut by root levels, below
+# a set that is built at the root: leaf mode 4 keeps its sizes, path tables do not take it
+MEMO_PLANS = [
+    ([(0, 1), (0, 2), (0, 3), (0, 4), (1, 2), (1, 4), (2, 3)], (4, 0, 1, 2, 3), 2),
+    ([(0, 2), (0, 3), (0, 4), (1, 2), (1, 3), (1, 4), (2, 3)], (0, 2, 3, 1, 4), 0),
+    ([(0, 2), (0, 3), (0, 4), (1, 2), (1, 3), (1, 4), (2, 3)], (2, 1, 3, 0, 4), 0),
+    ([(0, 1), (0, 2), (0, 3), (0, 4), (1, 2), (1, 3), (1, 4), (2, 3)], (2, 0, 3, 1, 4), 0),
+]
+
+
+@pytest.mark.parametrize("edges,order,fs", MEMO_PLANS, ids=range(len(MEMO_PLANS)))
+def test_leaf4_memo_on_plans_without_a_table(edges, order, fs):
+    """Leaf mode 4's sizes per root, with hits (a candidate comes up below several level-2
+    bindings of a root): every grab, split and width, with every vertex a hub and with hubs
+    by degree, counted, accounted, without allocation and in a batch: the oracle's
+    count."""
+    import torch
+    g = I.er(120, 0.3, seed=5)
+    want = O.count(g, 5, edges)
+    for bits in ("dense", "auto"):
+        graph = gp.Graph.from_csr(g, device=True, hub_bitmaps=bits)
+        plan = gp.Plan(5, edges, stats=graph.stats(), force_order=order, force_set=fs)
+        for ch in (1, 4, 16):
+            for sw, sv in ((1, 0), (16, 1 << 20), (3, 8)):
+                for grp in (64, 32, 16, 8):
+                    la = dict(group=grp, leaf_mode=4, chunk=ch, split_ways=sw, split_vertices=sv)
+                    s = gp.count_shape(graph, plan, **la)
+                    assert (s["table"], s["group"]) == (0, grp)
+                    assert s["memo"] == (graph.stats().hub_vertices > 0)
+                    assert gp.count(graph, plan, **la) == want, (bits, la)
+        assert gp.count_traffic(graph, plan, group=64, leaf_mode=4)[0] == want
+        out = torch.zeros(2, dtype=torch.int64, device="cuda")
+        gp.count_noalloc(graph, plan, out, group=64, leaf_mode=4)
+        torch.cuda.synchronize()
+        assert out.tolist() == [want, 0]
+        assert gp.count_batch(graph, [plan, plan, plan], group=32, leaf_mode=4) == [want] * 3
+        graph.close()
+
+
+@pytest.mark.parametrize("pname", ["4-cycle", "5-cycle", "6-cycle"])
+def test_cycles_off_the_tables(pname):
+    """Schedules and sets of the cycles that path tables do not take, over every width, leaf
+    mode and split, per root too: the oracle's count, by the general search."""
+    k, e = P[pname]
+    g = I.er(48, 0.3, seed=21)
+    want = O.count(g, k, e)
+    rnd = random.Random(k)
+    orders, n_sets = _orders(k, e), gp.Plan(k, e).info().n_sets
+    for bits in ("dense", "none"):
+        graph = gp.Graph.from_csr(g, device=True, hub_bitmaps=bits)
+        plans = []
+        for _ in range(400):
+            p = gp.Plan(k, e, stats=graph.stats(), force_order=rnd.choice(orders), force_set=rnd.randrange(n_sets))
+            if not gp.count_shape(graph, p)["table"]:
+                plans.append(p)
+            if len(plans) == 4:
+                break
+        assert len(plans) == 4
+        for p in plans:
+            for grp, leaf in itertools.product((64, 32, 16, 8), (1, 2, 3, 4)):
+                la = dict(group=grp, leaf_mode=leaf, chunk=rnd.choice((1, 3, 4)), split_ways=rnd.choice((1, 5, 16)),
+                          split_vertices=rnd.choice((8, 1 << 20)))
+                assert gp.count(graph, p, **la) == want, (bits, p.order, p.restrictions, la)
+            assert gp.count_per_root(graph, p, group=16, leaf_mode=4)[0] == want
+        graph.close()
