@@ -149,7 +149,11 @@ typedef struct {
     int32_t root_offset;   /* starting at root_offset: a seeded root sample for tuning */
     int32_t split_ways;    /* 0 auto, 1 none, else: each heavy root edge runs as split_ways
                               tasks that bind disjoint slices of its level-2 candidates
-                              (shortens the tail that single hub roots leave; k >= 4) */
+                              (shortens the tail that single hub roots leave; k >= 4).
+                              Fewer tasks where the lanes take the level-2 candidates and
+                              so many would leave lanes idle; none for 4-vertex plans
+                              whose candidates are cut below the hub endpoint, per-root
+                              counts and path tables */
     int32_t split_vertices;/* heavy roots: those whose smaller endpoint in the degree-sorted
                               layout is below split_vertices, rounded down to a power of
                               two (0 = auto) */

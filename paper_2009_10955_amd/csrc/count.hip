@@ -126,7 +126,7 @@ bool memo_eligible(const GpPlanDesc& d) {
 // root level, which each of the block's 16 wavefronts would repeat, and not
 // per root. With inclusion-exclusion: plans whose set of the last outer vertex x is
 // N(root endpoint) & N(x). Without and with the table: R-MAT 17 5-cycle (64 lanes, split 4
-// ways, leaf mode 4 with a memo) 477 and 31 ms; 5-cycle of the cost model's plan on
+// ways, leaf mode 4 with a memo) 481 and 31 ms; 5-cycle of the cost model's plan on
 // R-MAT (20,000 vertices, 160K edges) 100 and 11.5 ms; 6-cycle on Chung-Lu (3,000
 // vertices, 30K edges) 199 and 24 ms.
 bool table_form(const gpint::DeviceGraph& g, const GpPlanDesc& d) {
@@ -202,8 +202,8 @@ bool table_rule(const gpint::DeviceGraph& g, const GpPlanDesc& d) {
 
 // With inclusion-exclusion a table is filled once for all of p's roots, so a sparse
 // sample pays for the fills: taken while the heaviest endpoint keeps 1,024 sampled
-// roots. House with and without the table, every 1st and 7th root of R-MAT 17: 10.4 and
-// 15.6, 4.4 and 3.8 ms; every 60th, 237th and 1,001st of R-MAT 22 (largest degree
+// roots. House with and without the table, every 1st and 7th root of R-MAT 17: 10.3 and
+// 15.5, 4.4 and 3.8 ms; every 60th, 237th and 1,001st of R-MAT 22 (largest degree
 // 95,042): 221 and 504, 144 and 200, 116 and 68 ms.
 bool table_sample(const gpint::DeviceGraph& g, const GpPlanDesc& d, int64_t stride) {
     return !d.iep || stride <= 1 || stride * 1024 <= g.max_deg;

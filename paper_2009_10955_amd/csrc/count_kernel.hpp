@@ -1112,7 +1112,8 @@ __device__ __forceinline__ void table_leaf(const GpPlanDesc& d, const Ctx<G>& c,
             for (uint32_t m = ex; m; m &= m - 1) sum -= c.edge(pick<K>(v, __builtin_ctz(m)), x) ? 1u : 0u;
         }
     }
-    // |N(x) & N(p)| < 2^16 and a lane takes fewer than 2^16 elements
+    // every unit of sum is an entry y of the list of a different x: fewer than the
+    // graph's 2^31 entries (a load refuses more)
     add_count(acc, (uint64_t)sum - (uint64_t)corr * taken, carry);
 }
 

@@ -21,7 +21,7 @@
 // The search reads lists in order and looks counts up in LDS: neither the
 // lists of x nor a table of 8-byte words per group in HBM are touched. What bounds
 // it now is reading the lists of the level-2 candidates, from L2: 5-cycle on
-// R-MAT 17 (971,517 edges) 31 ms, against 467 ms in leaf mode 4.
+// R-MAT 17 (971,517 edges) 31 ms, against 481 ms in leaf mode 4.
 #include "count_kernel.hpp"
 
 namespace gpcount {
@@ -218,7 +218,7 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(8))
 // hub bitmaps, which bounded the house count by memory lines (a 60th of
 // R-MAT 22: 3.9 TB of lines fetched in 507 ms; now 1.06 TB in 223 ms, most of
 // them for the pairs of term 3 that the memo does not hold yet. R-MAT 17 whole:
-// 16.3 ms, now 10.5).
+// 15.5 ms, 10.3 with the table).
 constexpr int kIepWaves = kIepTableWaves;
 
 template <int K, int MODE>

@@ -145,9 +145,10 @@ __device__ void list_last(const GpPlanDesc& d, const gpcount::Ctx<G>& c, const L
     }
 }
 
-// Write pass: every lane walks its own last level one candidate per step, and a ballot per step places the step's embeddings at rows pos,
-// pos + 1, ... in lane order (one walk, no count first). Lanes without a
-// binding (have false) only join the ballots.
+// Write pass: every lane walks its own last level one candidate per step, and a
+// ballot per step places the step's embeddings at rows pos, pos + 1, ... in
+// lane order (one walk, no count first). Lanes without a binding (have false)
+// only join the ballots.
 template <int K>
 __device__ void last_lockstep(const GpPlanDesc& d, const gpcount::Ctx<G>& c, const ListArgs& a,
                               const int32_t (&w)[K], bool have, uint64_t& pos, Stage& st) {
