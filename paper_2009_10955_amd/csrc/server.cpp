@@ -499,7 +499,8 @@ void worker_main(gp_server* S) {
             }
             // next slice: this query's rate times its fair share of the target
             const double t_q = (double)r[4 * i + 2] * tick_s / groups;
-            q->slice = gpint::next_slice(q->split, L.firsts[i], L.slices[i], t_q, q->launched, fair);
+            q->slice = gpint::next_slice(q->split, L.firsts[i], L.slices[i], t_q, q->launched, fair,
+                                         q->n_tasks);
         }
     }
     for (int i = 0; i < 2 * ng; ++i) {

@@ -27,10 +27,13 @@ struct TaskSplit {
 
 // The next slice of a query, from task `next` on: its share of the target iteration
 // (fair seconds) at the rate of a slice of n tasks from `first` that took `seconds`. The
-// first roots are the heaviest, so the rate errs low: it may grow fast.
-inline int64_t next_slice(const TaskSplit& split, int64_t first, int64_t n, double seconds, int64_t next, double fair) {
+// first roots are the heaviest, so the rate errs low: it may grow fast. total: the
+// query's tasks (0: not known); a rest of up to two shares goes at once.
+inline int64_t next_slice(const TaskSplit& split, int64_t first, int64_t n, double seconds, int64_t next, double fair,
+                          int64_t total = 0) {
     const double roots = split.roots(first, n);
     const double want = std::min(roots / std::max(1e-7, seconds) * fair, 32.0 * roots + 1);
+    if (next < total && split.roots(next, total - next) <= 2 * want) return total - next;
     return std::max<int64_t>(64, split.tasks_of(next, want));
 }
 

@@ -12,8 +12,9 @@ PROGRAM = r"""
 #include <cstdlib>
 #include <vector>
 #include "slices.hpp"
-// argv: roots, split roots, ways, seconds of the first and of the last root, target
-int main(int, char** a) {
+// argv: roots, split roots, ways, seconds of the first and of the last root, target,
+// whether slices know the query's end
+int main(int argc, char** a) {
     const int64_t roots = atoll(a[1]), split_roots = atoll(a[2]);
     gpint::TaskSplit sp;
     sp.ways = atoi(a[3]);
@@ -35,7 +36,7 @@ int main(int, char** a) {
         const int64_t n = std::min(slice, n_tasks - at);
         const double s = end[at + n] - end[at];
         printf("%.4f\n", s / target);
-        slice = gpint::next_slice(sp, at, n, s, at + n, target);
+        slice = gpint::next_slice(sp, at, n, s, at + n, target, argc > 7 ? n_tasks : 0);
         at += n;
         if (++iterations > 10000) return 2;
     }
@@ -77,3 +78,15 @@ def test_lighter_roots_come_later(program):
     past it."""
     times = _serve(program, 1_000_000, 5_000, 16, 4e-5, 1e-7, 0.025)
     assert max(times[1:]) <= 1.01 and len(times) < 2000
+
+
+@pytest.mark.parametrize("roots,split,ways", [(10_000, 256, 16), (9_000, 0, 1), (400_000, 10_000, 16)])
+def test_a_short_rest_goes_at_once(program, roots, split, ways):
+    """A rest of up to two shares is one slice: the last iteration takes between one and two
+    targets where two would have run, and no other goes past its own."""
+    cut = _serve(program, roots, split, ways, 1e-5, 1e-5, 0.025)
+    times = _serve(program, roots, split, ways, 1e-5, 1e-5, 0.025, 1)
+    assert sum(times) == pytest.approx(sum(cut), abs=1e-3 * len(cut))
+    assert max(times[1:-1], default=0) <= 1.01 and times[-1] <= 2.01
+    # the last two of the cut iterations are one, unless the first slice was all there is to one target
+    assert len(times) == len(cut) - (1 if len(cut) > 2 else 0)
